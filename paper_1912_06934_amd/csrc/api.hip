@@ -288,8 +288,7 @@ msrsb_status refresh_values(msrsb_ctx *c)
     hipStream_t s = c->stream;
     if (c->a_off.n > 0) launch_csr_to_dia(s, c->n, c->a_off.n, c->rp, c->a_slot, c->a, c->a_dia, nullptr);
     if (c->a_ns.n > 0)
-        launch_csr_to_nbs(s, c->n, c->a_ns.n * c->a_ns.bs, c->rp, c->ns_slot, c->a, c->a_ns_val,
-                          nullptr);
+        launch_csr_to_nbs(s, c->n, c->a_ns, c->rp, c->ns_slot, c->a, c->a_ns_val, nullptr);
     hipMemsetAsync(c->dev_flag, 0, sizeof(int), s);
     launch_check_symmetric(s, c->n, c->rp, c->ci, c->a, c->dev_flag);
     int flag = 1;
@@ -307,6 +306,10 @@ msrsb_status refresh_values(msrsb_ctx *c)
         bool pairs = d.n > 0 && (d.n & 1) && d.off[d.n / 2] == 0;
         for (int o = 0; pairs && o < d.n; ++o) pairs = d.off[o] == -d.off[d.n - 1 - o];
         c->a_off.sym = c->a_symmetric && pairs ? 1 : 0;
+        const NodeStencil &m = c->a_ns;
+        pairs = m.n > 0 && (m.n & 1) && m.off[m.n / 2] == 0;
+        for (int o = 0; pairs && o < m.n; ++o) pairs = m.off[o] == -m.off[m.n - 1 - o];
+        c->a_ns.sym = c->a_symmetric && pairs ? 1 : 0;
     }
     c->smoother_valid = c->smoother32_valid = false;
     c->smoother_t_valid = c->smoother32_t_valid = false;

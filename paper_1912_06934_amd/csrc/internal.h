@@ -56,16 +56,26 @@ struct Status {
 // Node-block stencil (NBS) form of a vector operator with interleaved dofs
 // (dof = bs * node + l): every row reaches, for each of at most 27 node
 // offsets, the bs dofs of that neighbour node.  Values are stored as
-// [n_off * bs][n] "diagonals" (slot o * bs + l' of row r holds the entry in
-// column bs * (r / bs + off[o]) + l'), zero where a row has no such entry, so
-// the kernels read no indices and every slot is one coalesced stream.
+// n_off * bs streams of n values: stream o * bs + l' holds every row's entry
+// in column bs * (r / bs + off[o]) + l' (zero where a row has no such entry),
+// the rows ordered by component and then by node (nbs_pos), so the kernels
+// read no indices and consecutive nodes are one coalesced stream, also where
+// an entry is read at the neighbour's row (see k_nbs_* in k_krylov.hip).
 constexpr int kMaxNodeOffsets = 27;
 struct NodeStencil {
     int n = 0;      // node offsets (0: no NBS form)
     int bs = 1;
     int nn = 0;     // nodes
     int off[kMaxNodeOffsets] = {};
+    // 1: the operator is symmetric (to the bit), so the entries at the lower
+    // offsets may be read from the upper ones at the neighbour's rows
+    int sym = 0;
 };
+// place of row r (of nn nodes, bs components each) in NBS stream st
+__host__ __device__ __forceinline__ int64_t nbs_pos(int st, int r, int bs, int nn)
+{
+    return (static_cast<int64_t>(st) * bs + r % bs) * nn + r / bs;
+}
 
 // Launch segment of a level-scheduled triangular sweep: one wide level (a
 // launch across the GPU) or a run of narrow levels (one work-group).
@@ -507,8 +517,8 @@ void launch_diag_inverses(hipStream_t s, int n, const int *rp, const int *ci, co
 void launch_gather_values(hipStream_t s, int64_t m, const int *src, const double *a, double *out);
 
 // ---- node-block stencil kernels (k_krylov.hip) ----
-void launch_csr_to_nbs(hipStream_t s, int n, int nslot, const int *rp, const int8_t *slot,
-                       const double *a, double *v64, float *v32);
+void launch_csr_to_nbs(hipStream_t s, int n, const NodeStencil &ns, const int *rp,
+                       const int8_t *slot, const double *a, double *v64, float *v32);
 void launch_nbs_spmv(hipStream_t s, int n, const NodeStencil &ns, const double *v, const double *x,
                      double *y);
 // r = f - A x; with v32 (non-null) the FP32 values and arithmetic

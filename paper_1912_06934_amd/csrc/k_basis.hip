@@ -1151,7 +1151,7 @@ __global__ __launch_bounds__(kBlock) void k_filter_jacobi_nbs(int n, int filter,
     if (i >= n) return;
     const int ic = i % BS;
     auto coef = [&](int o) {
-        double g = nsv[static_cast<int64_t>(o * BS + ic) * n + i];
+        double g = nsv[nbs_pos(o * BS + ic, i, BS, ns.nn)];
         if (filter && g > 0.0) g = 0.0;
         return g;
     };

@@ -424,7 +424,7 @@ __global__ __launch_bounds__(NT) void k_rap_ell(int n, int nc, int maxnb,
 // ---------------------------------------------------------------------------
 // R A P for a node-block stencil A (NodeStencil: BS components per node,
 // coefficient of row r at node offset o and column component l in
-// v[(o BS + l) n + r], zero where the row has no such entry) and P in its
+// stream o BS + l at nbs_pos, zero where the row has no such entry) and P in its
 // row-major ELL form (8 slots, 16-bit columns).  Fine row i of R's row j
 // reaches, through A, the P rows BS (node(i) + off[o]) + l; their columns
 // are A_c's columns of row j.  Same structure as the DIA form above: the
@@ -457,7 +457,7 @@ __global__ __launch_bounds__(128) void k_rap_nbs_cols(int n, int nc, const int *
             cvec cc[BS];
 #pragma unroll
             for (int l = 0; l < BS; ++l) {
-                a[l] = in ? av[static_cast<int64_t>(o * BS + l) * n + i] : 0.0;
+                a[l] = in ? av[nbs_pos(o * BS + l, i, BS, ns.nn)] : 0.0;
                 cc[l] = *reinterpret_cast<const cvec *>(
                     pcol + static_cast<int64_t>(in ? nb * BS + l : i) * 8);
             }
@@ -533,7 +533,7 @@ __global__ __launch_bounds__(64) void k_rap_nbs(int n, int nc, int maxnb,
             const bool in = nb >= 0 && nb < ns.nn && pe[e] != 0.0;
 #pragma unroll
             for (int l = 0; l < BS; ++l) {
-                a[b][e][l] = in ? av[static_cast<int64_t>(o * BS + l) * n + ie[e]] : 0.0;
+                a[b][e][l] = in ? av[nbs_pos(o * BS + l, ie[e], BS, ns.nn)] : 0.0;
                 load_prow<T>(pv, pcol, in ? nb * BS + l : ie[e], v[b][e][l], cl[b][e][l]);
             }
         }
@@ -2027,7 +2027,8 @@ __global__ __launch_bounds__(kRapBoxMaxThreads) void k_rap_box_nbs(
                     continue;
                 const double r =
                     static_cast<double>(rj[(ix - x0) + bx * ((iy - y0) + by * (iz - z0))]);
-                const int64_t row = 3 * static_cast<int64_t>(k - (ox + nx * oy + nxy * oz)) + cj;
+                const int64_t row = static_cast<int64_t>(cj) * (n / 3) + k -
+                                    (ox + nx * oy + nxy * oz);  // nbs_pos in a stream
 #pragma unroll
                 for (int q = 0; q < 3; ++q)
                     ra[q] += r * av[static_cast<int64_t>(o * 3 + q) * n + row];

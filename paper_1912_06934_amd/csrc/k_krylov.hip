@@ -567,117 +567,196 @@ __global__ __launch_bounds__(kFinThreads) void k_fin_beta(int nb, const double *
 }
 
 // ---------------------------------------------------------------------------
-// Node-block stencil (NBS) kernels: thread per row r = bs * node + l, the
-// row's entries visited by node offset, then component (ascending columns,
-// the CSR order); an offset that leaves the node range, or reaches a node that
-// is no neighbour (a wrap at a grid line), has zero values.
+// Node-block stencil (NBS) kernels: a thread takes a node's BS rows, the rows'
+// entries visited by node offset, then component (ascending columns, the CSR
+// order); an offset that leaves the node range, or reaches a node that is no
+// neighbour (a wrap at a grid line), has zero values.  The BS rows share the
+// BS gathered values of x per offset: with a thread per row the three-lane
+// gathers kept the texture addresser busy for half the kernel's time.
+//
+// SYM: with a symmetric operator only the diagonal blocks and the upper
+// offsets stream from memory; an entry at a lower offset is its transposed
+// entry at the neighbour's row, A(r, c) = A(c, r).  The offsets are visited in
+// pairs +-off, so that a stream's value is read at the node and as the mirror
+// of the node at +off about the same time: all wavefronts of an XCD walk the
+// pairs together (its range of nodes is in flight at once), and one pair's
+// streams are 2.5 MB per XCD at 275k nodes, which its L2 holds.  (Visited in
+// ascending order, the mirrored reads missed the L2: 580 MB fetched for the
+// 290 MB of upper entries, against 418 MB in pairs.)  Bound by memory: one
+// product of the 3D Q1 operator at 275k nodes took 109 us reading all 534 MB
+// of entries, a thread per row, and takes 65 us; at 23k nodes 12.3 -> 8.7 us.
+//
+// A work-group covers kNbsNodes nodes (each XCD one contiguous range) with KS
+// threads each: the thread's part of the offsets is one of KS nearly equal
+// ones, and the KS sums are added in order.
 // ---------------------------------------------------------------------------
-template <int BS, typename MT>
-__device__ __forceinline__ MT nbs_dot(int r, int n, const NodeStencil &ns,
-                                      const MT *__restrict__ v, const double *__restrict__ x)
+constexpr int kNbsNodes = 64;
+
+__device__ __forceinline__ int nbs_node()
 {
-    const int node = r / BS;
-    MT s = MT(0);
-#pragma unroll 3
-    for (int o = 0; o < ns.n; ++o) {
-        const int nb = node + ns.off[o];
-        const bool in = nb >= 0 && nb < ns.nn;
-        const int base = (in ? nb : node) * BS;
-        MT a[BS];
-        double xv[BS];
+    return xcd_group(blockIdx.x, gridDim.x) * kNbsNodes + (threadIdx.x & (kNbsNodes - 1));
+}
+
+inline int nbs_grid(const NodeStencil &ns) { return (ns.nn + kNbsNodes - 1) / kNbsNodes; }
+
+// s[c] += the products of the node's row c: the offsets part, part + KS, ...,
+// or with SYM the diagonal block (part 0) and the pairs part, part + KS, ...
+template <int BS, bool SYM, int KS, typename MT>
+__device__ __forceinline__ void nbs_part(int part, int node, const NodeStencil &ns,
+                                         const MT *__restrict__ v, const double *__restrict__ x,
+                                         MT (&s)[BS])
+{
+    const int64_t nn = ns.nn;
+    // the BS x BS block at (stream set o, node k): transposed for a mirror,
+    // whose row is the stored block's column
+    auto block = [&](int o, int k, bool mirror, MT(&a)[BS][BS]) {
+        const MT *m = v + static_cast<int64_t>(o) * (BS * BS) * nn + k;
 #pragma unroll
-        for (int l = 0; l < BS; ++l) {
-            a[l] = v[static_cast<int64_t>(o * BS + l) * n + r];
-            xv[l] = x[base + l];
+        for (int l = 0; l < BS; ++l)
+#pragma unroll
+            for (int c = 0; c < BS; ++c) {
+                if (mirror) a[l][c] = m[(l * BS + c) * nn];
+                else a[c][l] = m[(l * BS + c) * nn];
+            }
+    };
+    auto vec = [&](int k, MT(&xv)[BS]) {
+#pragma unroll
+        for (int l = 0; l < BS; ++l) xv[l] = static_cast<MT>(x[static_cast<int64_t>(k) * BS + l]);
+    };
+    auto add = [&](bool in, const MT(&a)[BS][BS], const MT(&xv)[BS]) {
+#pragma unroll
+        for (int c = 0; c < BS; ++c)
+#pragma unroll
+            for (int l = 0; l < BS; ++l) s[c] += in ? a[c][l] * xv[l] : MT(0);
+    };
+    if constexpr (SYM) {
+        const int mid = ns.n / 2;
+        if (part == 0) {
+            MT a[BS][BS], xv[BS];
+            block(mid, node, false, a);
+            vec(node, xv);
+            add(true, a, xv);
         }
-#pragma unroll
-        for (int l = 0; l < BS; ++l) s += in ? a[l] * static_cast<MT>(xv[l]) : MT(0);
-    }
-    return s;
-}
-
-template <int BS>
-__global__ __launch_bounds__(kBlock) void k_nbs_spmv(int n, NodeStencil ns,
-                                                     const double *__restrict__ v,
-                                                     const double *__restrict__ x,
-                                                     double *__restrict__ y)
-{
-    const int r = blockIdx.x * kBlock + threadIdx.x;
-    if (r < n) y[r] = nbs_dot<BS, double>(r, n, ns, v, x);
-}
-
-template <int BS, typename MT>
-__global__ __launch_bounds__(kBlock) void k_nbs_residual(int n, NodeStencil ns,
-                                                         const MT *__restrict__ v,
-                                                         const double *__restrict__ f,
-                                                         const double *__restrict__ x,
-                                                         double *__restrict__ res)
-{
-    const int r = blockIdx.x * kBlock + threadIdx.x;
-    if (r < n)
-        res[r] = static_cast<double>(static_cast<MT>(f[r]) - nbs_dot<BS, MT>(r, n, ns, v, x));
-}
-
-// z_out = z_in + D^{-1} (v - A z_in) (Jacobi-type sweep), or D^{-1} v from zero
-template <int BS, typename MT>
-__global__ __launch_bounds__(kBlock) void k_nbs_sweep(int n, NodeStencil ns,
-                                                      const MT *__restrict__ a,
-                                                      const MT *__restrict__ dinv,
-                                                      const double *__restrict__ vin,
-                                                      const double *__restrict__ zin,
-                                                      double *__restrict__ zout, int zero_start)
-{
-    const int r = blockIdx.x * kBlock + threadIdx.x;
-    if (r >= n) return;
-    if (zero_start) {
-        zout[r] = static_cast<double>(dinv[r] * static_cast<MT>(vin[r]));
-        return;
-    }
-    const MT s = nbs_dot<BS, MT>(r, n, ns, a, zin);
-    zout[r] = zin[r] + static_cast<double>(dinv[r] * (static_cast<MT>(vin[r]) - s));
-}
-
-// p = z + beta p_old (p = z when beta = 0), q = A p, and the p.q partials
-template <int BS>
-__global__ __launch_bounds__(kBlock) void k_nbs_pcg_p_spmv(
-    int n, NodeStencil ns, const double *__restrict__ v, const double *__restrict__ z,
-    const double *__restrict__ pold, double *__restrict__ pnew, double *__restrict__ q,
-    double *__restrict__ part, const double *__restrict__ scal)
-{
-    const int r = blockIdx.x * kBlock + threadIdx.x;
-    const double beta = scal[S_BETA];
-    const bool restart = beta == 0.0;
-    double pq[1] = {0.0};
-    if (r < n) {
-        const int node = r / BS;
-        double s = 0.0;
+#pragma unroll 1
+        for (int o = mid + 1 + part; o < ns.n; o += KS) {
+            const int up = node + ns.off[o], lo = node - ns.off[o];
+            const bool inu = up < ns.nn, inl = lo >= 0;
+            const int ku = inu ? up : node, kl = inl ? lo : node;
+            MT au[BS][BS], al[BS][BS], xu[BS], xl[BS];
+            block(o, node, false, au);
+            block(o, kl, true, al);
+            vec(ku, xu);
+            vec(kl, xl);
+            add(inl, al, xl);
+            add(inu, au, xu);
+        }
+    } else {
 #pragma unroll 3
-        for (int o = 0; o < ns.n; ++o) {
+        for (int o = part; o < ns.n; o += KS) {
             const int nb = node + ns.off[o];
             const bool in = nb >= 0 && nb < ns.nn;
-            const int base = (in ? nb : node) * BS;
-            double a[BS], pk[BS];
-#pragma unroll
-            for (int l = 0; l < BS; ++l) {
-                a[l] = v[static_cast<int64_t>(o * BS + l) * n + r];
-                pk[l] = restart ? z[base + l] : z[base + l] + beta * pold[base + l];
-            }
-#pragma unroll
-            for (int l = 0; l < BS; ++l) s += in ? a[l] * pk[l] : 0.0;
+            const int k = in ? nb : node;
+            MT a[BS][BS], xv[BS];
+            block(o, node, false, a);
+            vec(k, xv);
+            add(in, a, xv);
         }
-        const double pr = restart ? z[r] : z[r] + beta * pold[r];
-        pnew[r] = pr;
-        q[r] = s;
-        pq[0] = pr * s;
     }
-    block_partials<1>(pq, part);
 }
 
-// The same in two passes, for operators whose rows gather many columns:
-// p = z + beta p_old once per row, then q = A p with the p.q partials, so
-// each of a row's columns is gathered from one vector instead of two (at
-// 81 columns per row that halves the gathered bytes).  Same arithmetic and
-// order as k_nbs_pcg_p_spmv.
+// the products of the node's rows, valid in the first kNbsNodes threads (all
+// threads must call it; node >= ns.nn where the thread has no node)
+template <int BS, bool SYM, int KS, typename MT>
+__device__ __forceinline__ void nbs_dot(int node, const NodeStencil &ns,
+                                        const MT *__restrict__ v, const double *__restrict__ x,
+                                        MT (&s)[BS])
+{
+#pragma unroll
+    for (int c = 0; c < BS; ++c) s[c] = MT(0);
+    if constexpr (KS == 1) {
+        if (node < ns.nn) nbs_part<BS, SYM, 1, MT>(0, node, ns, v, x, s);
+    } else {
+        __shared__ MT sh[KS - 1][BS][kNbsNodes];
+        const int part = __builtin_amdgcn_readfirstlane(threadIdx.x / kNbsNodes);
+        const int lane = threadIdx.x & (kNbsNodes - 1);
+        if (node < ns.nn) nbs_part<BS, SYM, KS, MT>(part, node, ns, v, x, s);
+        if (part > 0) {
+#pragma unroll
+            for (int c = 0; c < BS; ++c) sh[part - 1][c][lane] = s[c];
+        }
+        __syncthreads();
+        if (part == 0) {
+#pragma unroll
+            for (int q = 1; q < KS; ++q)
+#pragma unroll
+                for (int c = 0; c < BS; ++c) s[c] += sh[q - 1][c][lane];
+        }
+    }
+}
+
+template <int BS, bool SYM, int KS>
+__global__ __launch_bounds__(KS *kNbsNodes) void k_nbs_spmv(NodeStencil ns,
+                                                            const double *__restrict__ v,
+                                                            const double *__restrict__ x,
+                                                            double *__restrict__ y)
+{
+    const int node = nbs_node();
+    double s[BS];
+    nbs_dot<BS, SYM, KS, double>(node, ns, v, x, s);
+    if (node >= ns.nn || threadIdx.x >= kNbsNodes) return;
+#pragma unroll
+    for (int c = 0; c < BS; ++c) y[static_cast<int64_t>(node) * BS + c] = s[c];
+}
+
+template <int BS, bool SYM, int KS, typename MT>
+__global__ __launch_bounds__(KS *kNbsNodes) void k_nbs_residual(NodeStencil ns,
+                                                                const MT *__restrict__ v,
+                                                                const double *__restrict__ f,
+                                                                const double *__restrict__ x,
+                                                                double *__restrict__ res)
+{
+    const int node = nbs_node();
+    MT s[BS];
+    nbs_dot<BS, SYM, KS, MT>(node, ns, v, x, s);
+    if (node >= ns.nn || threadIdx.x >= kNbsNodes) return;
+#pragma unroll
+    for (int c = 0; c < BS; ++c) {
+        const int64_t r = static_cast<int64_t>(node) * BS + c;
+        res[r] = static_cast<double>(static_cast<MT>(f[r]) - s[c]);
+    }
+}
+
+// z_out = z_in + D^{-1} (v - A z_in) (Jacobi-type sweep)
+template <int BS, bool SYM, int KS, typename MT>
+__global__ __launch_bounds__(KS *kNbsNodes) void k_nbs_sweep(
+    NodeStencil ns, const MT *__restrict__ a, const MT *__restrict__ dinv,
+    const double *__restrict__ vin, const double *__restrict__ zin, double *__restrict__ zout)
+{
+    const int node = nbs_node();
+    MT s[BS];
+    nbs_dot<BS, SYM, KS, MT>(node, ns, a, zin, s);
+    if (node >= ns.nn || threadIdx.x >= kNbsNodes) return;
+#pragma unroll
+    for (int c = 0; c < BS; ++c) {
+        const int64_t r = static_cast<int64_t>(node) * BS + c;
+        zout[r] = zin[r] + static_cast<double>(dinv[r] * (static_cast<MT>(vin[r]) - s[c]));
+    }
+}
+
+// the same from z_in = 0: D^{-1} v
+template <typename MT>
+__global__ __launch_bounds__(kBlock) void k_scale_rows(int n, const MT *__restrict__ dinv,
+                                                       const double *__restrict__ vin,
+                                                       double *__restrict__ zout)
+{
+    const int r = blockIdx.x * kBlock + threadIdx.x;
+    if (r < n) zout[r] = static_cast<double>(dinv[r] * static_cast<MT>(vin[r]));
+}
+
+// PCG direction and product in two passes: p = z + beta p_old once per row
+// (p = z when beta = 0), then q = A p with the p.q partials, so each of a
+// row's columns is gathered from one vector instead of two (at 81 columns per
+// row that halves the gathered bytes).
 __global__ __launch_bounds__(kBlock) void k_p_update(int n, const double *__restrict__ z,
                                                      const double *__restrict__ pold,
                                                      double *__restrict__ pnew,
@@ -689,25 +768,34 @@ __global__ __launch_bounds__(kBlock) void k_p_update(int n, const double *__rest
     pnew[r] = beta == 0.0 ? z[r] : z[r] + beta * pold[r];
 }
 
-template <int BS>
-__global__ __launch_bounds__(kBlock) void k_nbs_spmv_dot(int n, NodeStencil ns,
-                                                         const double *__restrict__ v,
-                                                         const double *__restrict__ p,
-                                                         double *__restrict__ q,
-                                                         double *__restrict__ part)
+// (one partial per work-group: its nodes are one wavefront)
+template <int BS, bool SYM, int KS>
+__global__ __launch_bounds__(KS *kNbsNodes) void k_nbs_spmv_dot(NodeStencil ns,
+                                                                const double *__restrict__ v,
+                                                                const double *__restrict__ p,
+                                                                double *__restrict__ q,
+                                                                double *__restrict__ part)
 {
-    const int r = blockIdx.x * kBlock + threadIdx.x;
-    double pq[1] = {0.0};
-    if (r < n) {
-        const double s = nbs_dot<BS, double>(r, n, ns, v, p);
-        q[r] = s;
-        pq[0] = p[r] * s;
+    const int node = nbs_node();
+    double s[BS];
+    nbs_dot<BS, SYM, KS, double>(node, ns, v, p, s);
+    if (threadIdx.x >= kNbsNodes) return;
+    double pq = 0.0;
+    if (node < ns.nn) {
+#pragma unroll
+        for (int c = 0; c < BS; ++c) {
+            const int64_t r = static_cast<int64_t>(node) * BS + c;
+            q[r] = s[c];
+            pq += p[r] * s[c];
+        }
     }
-    block_partials<1>(pq, part);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) pq += __shfl_xor(pq, off, 64);
+    if (threadIdx.x == 0) part[blockIdx.x] = pq;
 }
 
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_csr_to_nbs(int n, int nslot,
+__global__ __launch_bounds__(kBlock) void k_csr_to_nbs(int n, int bs, int nslot,
                                                        const int *__restrict__ rp,
                                                        const int8_t *__restrict__ slot,
                                                        const double *__restrict__ a,
@@ -715,9 +803,10 @@ __global__ __launch_bounds__(kBlock) void k_csr_to_nbs(int n, int nslot,
 {
     const int r = blockIdx.x * kBlock + threadIdx.x;
     if (r >= n) return;
-    for (int t = 0; t < nslot; ++t) v[static_cast<int64_t>(t) * n + r] = T(0);
+    const int64_t at = nbs_pos(0, r, bs, n / bs);
+    for (int t = 0; t < nslot; ++t) v[static_cast<int64_t>(t) * n + at] = T(0);
     for (int e = rp[r]; e < rp[r + 1]; ++e)
-        v[static_cast<int64_t>(slot[e]) * n + r] = static_cast<T>(a[e]);
+        v[static_cast<int64_t>(slot[e]) * n + at] = static_cast<T>(a[e]);
 }
 
 template <int ND, bool SYM>
@@ -1683,37 +1772,57 @@ void launch_check_symmetric(hipStream_t s, int n, const int *rp, const int *ci, 
 
 
 // ---- node-block stencil launchers ----
+// f(BS, SYM, KS) as integral constants, and the work-group size.  The
+// 27-offset operators take three threads per node below kNbsSplitNodes, where
+// a thread per node leaves fewer than two wavefronts per SIMD; above it the
+// three parts' streams only compete for the L2 (a product at 275k nodes: 72 us
+// with three threads per node, 66 us with one).
+constexpr int kNbsSplitNodes = 131072;
 template <typename F>
-void with_bs(int bs, F &&f)
+void with_ns(const NodeStencil &ns, F &&f)
 {
-    if (bs == 2) f(std::integral_constant<int, 2>{});
-    else f(std::integral_constant<int, 3>{});
+    using std::integral_constant;
+    auto sym = [&](auto bs, auto ks) {
+        constexpr int threads = decltype(ks)::value * kNbsNodes;
+        if (ns.sym) f(bs, integral_constant<bool, true>{}, ks, threads);
+        else f(bs, integral_constant<bool, false>{}, ks, threads);
+    };
+    if (ns.bs == 2)
+        sym(integral_constant<int, 2>{}, integral_constant<int, 1>{});
+    else if (ns.n == 27 && ns.nn < kNbsSplitNodes)
+        sym(integral_constant<int, 3>{}, integral_constant<int, 3>{});
+    else
+        sym(integral_constant<int, 3>{}, integral_constant<int, 1>{});
 }
 
-void launch_csr_to_nbs(hipStream_t s, int n, int nslot, const int *rp, const int8_t *slot,
-                       const double *a, double *v64, float *v32)
+void launch_csr_to_nbs(hipStream_t s, int n, const NodeStencil &ns, const int *rp,
+                       const int8_t *slot, const double *a, double *v64, float *v32)
 {
-    if (v64) k_csr_to_nbs<double><<<grid_for(n), kBlock, 0, s>>>(n, nslot, rp, slot, a, v64);
-    if (v32) k_csr_to_nbs<float><<<grid_for(n), kBlock, 0, s>>>(n, nslot, rp, slot, a, v32);
+    const int nslot = ns.n * ns.bs;
+    if (v64)
+        k_csr_to_nbs<double><<<grid_for(n), kBlock, 0, s>>>(n, ns.bs, nslot, rp, slot, a, v64);
+    if (v32)
+        k_csr_to_nbs<float><<<grid_for(n), kBlock, 0, s>>>(n, ns.bs, nslot, rp, slot, a, v32);
 }
 
 void launch_nbs_spmv(hipStream_t s, int n, const NodeStencil &ns, const double *v, const double *x,
                      double *y)
 {
-    with_bs(ns.bs, [&](auto b) {
-        k_nbs_spmv<decltype(b)::value><<<grid_for(n), kBlock, 0, s>>>(n, ns, v, x, y);
+    with_ns(ns, [&](auto b, auto sy, auto ks, int threads) {
+        k_nbs_spmv<b.value, sy.value, ks.value><<<nbs_grid(ns), threads, 0, s>>>(ns, v, x, y);
     });
 }
 
 void launch_nbs_residual(hipStream_t s, int n, const NodeStencil &ns, const double *v,
                          const float *v32, const double *f, const double *x, double *r)
 {
-    with_bs(ns.bs, [&](auto b) {
-        constexpr int BS = decltype(b)::value;
+    with_ns(ns, [&](auto b, auto sy, auto ks, int threads) {
         if (v32)
-            k_nbs_residual<BS, float><<<grid_for(n), kBlock, 0, s>>>(n, ns, v32, f, x, r);
+            k_nbs_residual<b.value, sy.value, ks.value, float>
+                <<<nbs_grid(ns), threads, 0, s>>>(ns, v32, f, x, r);
         else
-            k_nbs_residual<BS, double><<<grid_for(n), kBlock, 0, s>>>(n, ns, v, f, x, r);
+            k_nbs_residual<b.value, sy.value, ks.value, double>
+                <<<nbs_grid(ns), threads, 0, s>>>(ns, v, f, x, r);
     });
 }
 
@@ -1721,14 +1830,18 @@ void launch_nbs_sweep(hipStream_t s, int n, const NodeStencil &ns, bool fp32, co
                       const float *v32, const double *dinv, const float *dinv32,
                       const double *vin, const double *zin, double *zout, bool zero_start)
 {
-    with_bs(ns.bs, [&](auto b) {
-        constexpr int BS = decltype(b)::value;
+    if (zero_start) {
+        if (fp32) k_scale_rows<float><<<grid_for(n), kBlock, 0, s>>>(n, dinv32, vin, zout);
+        else k_scale_rows<double><<<grid_for(n), kBlock, 0, s>>>(n, dinv, vin, zout);
+        return;
+    }
+    with_ns(ns, [&](auto b, auto sy, auto ks, int threads) {
         if (fp32)
-            k_nbs_sweep<BS, float><<<grid_for(n), kBlock, 0, s>>>(n, ns, v32, dinv32, vin, zin,
-                                                                  zout, zero_start ? 1 : 0);
+            k_nbs_sweep<b.value, sy.value, ks.value, float>
+                <<<nbs_grid(ns), threads, 0, s>>>(ns, v32, dinv32, vin, zin, zout);
         else
-            k_nbs_sweep<BS, double><<<grid_for(n), kBlock, 0, s>>>(n, ns, v, dinv, vin, zin, zout,
-                                                                   zero_start ? 1 : 0);
+            k_nbs_sweep<b.value, sy.value, ks.value, double>
+                <<<nbs_grid(ns), threads, 0, s>>>(ns, v, dinv, vin, zin, zout);
     });
 }
 
@@ -1739,10 +1852,11 @@ void launch_nbs_pcg_p_spmv(hipStream_t s, int n, const NodeStencil &ns, const do
     // two passes (k_p_update, k_nbs_spmv_dot): 157 -> 5 + 115 us per call on
     // the 3D Q1 operator at 824k rows
     k_p_update<<<grid_for(n), kBlock, 0, s>>>(n, z, pold, pnew, scal);
-    with_bs(ns.bs, [&](auto b) {
-        k_nbs_spmv_dot<decltype(b)::value><<<grid_for(n), kBlock, 0, s>>>(n, ns, v, pnew, q, part);
+    with_ns(ns, [&](auto b, auto sy, auto ks, int threads) {
+        k_nbs_spmv_dot<b.value, sy.value, ks.value>
+            <<<nbs_grid(ns), threads, 0, s>>>(ns, v, pnew, q, part);
     });
-    k_fin_alpha<<<1, kFinThreads, 0, s>>>(grid_for(n), part, scal);
+    k_fin_alpha<<<1, kFinThreads, 0, s>>>(nbs_grid(ns), part, scal);
 }
 
 }  // namespace msrsb

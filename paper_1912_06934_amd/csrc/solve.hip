@@ -297,8 +297,8 @@ msrsb_status ensure_smoother(msrsb_ctx *c, const msrsb_solve_opts *o, bool trans
             if (fp32 && noff > 0)
                 launch_csr_to_dia(s, c->n, noff, c->rp, c->a_slot, c->a, nullptr, c->a_dia32);
             if (fp32 && nslot > 0)
-                launch_csr_to_nbs(s, c->n, static_cast<int>(nslot), c->rp, c->ns_slot, c->a,
-                                  nullptr, c->a_ns_val32);
+                launch_csr_to_nbs(s, c->n, c->a_ns, c->rp, c->ns_slot, c->a, nullptr,
+                                  c->a_ns_val32);
             c->smoother_valid = true;
             c->smoother32_valid = fp32;
         }
