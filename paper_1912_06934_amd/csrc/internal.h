@@ -149,7 +149,7 @@ struct msrsb_ctx {
     int *at_rp = nullptr, *at_ci = nullptr, *at_src = nullptr, *at_diag = nullptr;
     double *at = nullptr;
     bool at_pattern = false;
-    bool a_symmetric_pattern_checked = false;
+    int a_pattern_symmetric = -1;       // A's pattern (-1: not looked at yet)
 
     // NBS form of A (vector operators whose node pattern is a stencil)
     msrsb::NodeStencil a_ns;
@@ -511,14 +511,17 @@ void launch_dot(hipStream_t s, int n, const double *x, const double *y, double *
                 double *out);
 void launch_copy(hipStream_t s, int n, const double *x, double *y);
 void launch_axpy(hipStream_t s, int n, double alpha_host, const double *x, double *y);
+// from the stencil form when there is one (d.n or ns.n > 0), else from the
+// CSR rows; a32: FP32 copy of the CSR values (CSR form only, may be null)
 void launch_diag_inverses(hipStream_t s, int n, const int *rp, const int *ci, const double *a,
-                          double *dj, double *dl1, float *dj32, float *dl1_32, float *a32,
-                          int64_t nnz, int *flag);
+                          const DiaOffsets &d, const double *ad, const NodeStencil &ns,
+                          const double *nv, double *dj, double *dl1, float *dj32, float *dl1_32,
+                          float *a32, int *flag);
 void launch_gather_values(hipStream_t s, int64_t m, const int *src, const double *a, double *out);
 
 // ---- node-block stencil kernels (k_krylov.hip) ----
 void launch_csr_to_nbs(hipStream_t s, int n, const NodeStencil &ns, const int *rp,
-                       const int8_t *slot, const double *a, double *v64, float *v32);
+                       const int8_t *slot, const double *a, double *v);
 void launch_nbs_spmv(hipStream_t s, int n, const NodeStencil &ns, const double *v, const double *x,
                      double *y);
 // r = f - A x; with v32 (non-null) the FP32 values and arithmetic
@@ -585,10 +588,13 @@ void launch_prolong_ell(hipStream_t s, int n, int pw, const int *pcol, const uin
                         double *z, bool zero,
                         const ProlongAxes &axes = ProlongAxes{});
 void launch_csr_to_dia(hipStream_t s, int n, int noff, const int *rp, const int8_t *slot,
-                       const double *a, double *ad64, float *ad32);
+                       const double *a, double *ad);
 
 void launch_check_symmetric(hipStream_t s, int n, const int *rp, const int *ci, const double *a,
                             int *flag);
+// the values alone, from A's stencil form (pattern known to be symmetric)
+void launch_check_symmetric_stencil(hipStream_t s, int n, const DiaOffsets &d, const double *ad,
+                                    const NodeStencil &ns, const double *nv, int *flag);
 
 // ---- GMRES helpers (k_krylov.hip) ----
 void launch_multi_dot(hipStream_t s, int n, int k, const double *V, int64_t ldv,

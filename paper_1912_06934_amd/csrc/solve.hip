@@ -285,20 +285,23 @@ msrsb_status ensure_smoother(msrsb_ctx *c, const msrsb_solve_opts *o, bool trans
     if (!trans) {
         if (!c->smoother_valid || (fp32 && !c->smoother32_valid)) {
             if (dev_alloc(&c->dinv_jac, n) || dev_alloc(&c->dinv_l1, n)) return MSRSB_E_NOMEM;
+            // A's FP32 values: of its stencil form, or of the CSR entries
+            const size_t nslot = static_cast<size_t>(c->a_ns.n) * c->a_ns.bs;
+            const bool csr = noff == 0 && nslot == 0;
             if (fp32 && (dev_alloc(&c->dinv_jac32, n) || dev_alloc(&c->dinv_l1_32, n) ||
-                         dev_alloc(&c->a32, static_cast<size_t>(c->nnz))))
+                         (csr && dev_alloc(&c->a32, static_cast<size_t>(c->nnz)))))
                 return MSRSB_E_NOMEM;
             if (fp32 && noff > 0 && dev_alloc(&c->a_dia32, n * noff)) return MSRSB_E_NOMEM;
-            const size_t nslot = static_cast<size_t>(c->a_ns.n) * c->a_ns.bs;
             if (fp32 && nslot > 0 && dev_alloc(&c->a_ns_val32, n * nslot)) return MSRSB_E_NOMEM;
-            launch_diag_inverses(s, c->n, c->rp, c->ci, c->a, c->dinv_jac, c->dinv_l1,
+            launch_diag_inverses(s, c->n, c->rp, c->ci, c->a, c->a_off, c->a_dia, c->a_ns,
+                                 c->a_ns_val, c->dinv_jac, c->dinv_l1,
                                  fp32 ? c->dinv_jac32 : nullptr, fp32 ? c->dinv_l1_32 : nullptr,
-                                 fp32 ? c->a32 : nullptr, c->nnz, c->dev_flag);
+                                 fp32 && csr ? c->a32 : nullptr, c->dev_flag);
             if (fp32 && noff > 0)
-                launch_csr_to_dia(s, c->n, noff, c->rp, c->a_slot, c->a, nullptr, c->a_dia32);
+                launch_p_convert_down(s, static_cast<int64_t>(n) * noff, c->a_dia, c->a_dia32);
             if (fp32 && nslot > 0)
-                launch_csr_to_nbs(s, c->n, c->a_ns, c->rp, c->ns_slot, c->a, nullptr,
-                                  c->a_ns_val32);
+                launch_p_convert_down(s, static_cast<int64_t>(n * nslot), c->a_ns_val,
+                                      c->a_ns_val32);
             c->smoother_valid = true;
             c->smoother32_valid = fp32;
         }
@@ -306,16 +309,16 @@ msrsb_status ensure_smoother(msrsb_ctx *c, const msrsb_solve_opts *o, bool trans
         if (!c->smoother_t_valid || (fp32 && !c->smoother32_t_valid)) {
             if (dev_alloc(&c->dinv_jac_t, n) || dev_alloc(&c->dinv_l1_t, n)) return MSRSB_E_NOMEM;
             if (fp32 && (dev_alloc(&c->dinv_jac32_t, n) || dev_alloc(&c->dinv_l1_32_t, n) ||
-                         dev_alloc(&c->at32, static_cast<size_t>(c->nnz))))
+                         (noff == 0 && dev_alloc(&c->at32, static_cast<size_t>(c->nnz)))))
                 return MSRSB_E_NOMEM;
             if (fp32 && noff > 0 && dev_alloc(&c->at_dia32, n * noff)) return MSRSB_E_NOMEM;
-            launch_diag_inverses(s, c->n, c->at_rp, c->at_ci, c->at, c->dinv_jac_t, c->dinv_l1_t,
+            launch_diag_inverses(s, c->n, c->at_rp, c->at_ci, c->at, c->at_off, c->at_dia,
+                                 NodeStencil(), nullptr, c->dinv_jac_t, c->dinv_l1_t,
                                  fp32 ? c->dinv_jac32_t : nullptr,
-                                 fp32 ? c->dinv_l1_32_t : nullptr, fp32 ? c->at32 : nullptr,
-                                 c->nnz, c->dev_flag);
+                                 fp32 ? c->dinv_l1_32_t : nullptr,
+                                 fp32 && noff == 0 ? c->at32 : nullptr, c->dev_flag);
             if (fp32 && noff > 0)
-                launch_csr_to_dia(s, c->n, noff, c->at_rp, c->at_slot, c->at, nullptr,
-                                  c->at_dia32);
+                launch_p_convert_down(s, static_cast<int64_t>(n) * noff, c->at_dia, c->at_dia32);
             c->smoother_t_valid = true;
             c->smoother32_t_valid = fp32;
         }
