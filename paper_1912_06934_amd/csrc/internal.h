@@ -84,27 +84,57 @@ struct TriSegment {
     bool wide;
 };
 
+// One triangle (the earlier or the later entries) of a sweep order, packed by
+// dependency level: position u = lev[l] + t holds row[u], and its entries
+// k < width[l] sit at off[l] + k * (rows of level l) + t.
+struct TriSide {
+    std::vector<int> lev;        // level pointers
+    std::vector<int> width;      // most entries of a level's rows
+    std::vector<int64_t> off;    // first packed place of a level (and the total)
+    std::vector<TriSegment> seg;
+    bool merged = false;         // levels 0 and 1 go in one launch (kTriFirst)
+    int max_w = 0, max_cnt = 0;  // widest row, largest level
+    int *d_lev = nullptr, *d_width = nullptr;  // device copies
+    int64_t *d_off = nullptr;
+    int *row = nullptr;
+    int *col = nullptr;          // columns; kTriFirst marks a level-0 column of a
+                                 // level-1 row when the two are merged; padding:
+                                 // the row itself, marked
+    int *src = nullptr;          // their CSR entries (-1: padding)
+    int *fold = nullptr;         // lower side: the diagonal's entry for rows with
+                                 // nothing on the upper side, else -1
+};
+
+// Values of one smoother on the packed sides: the entries, the diagonal's
+// reciprocals, the folded ones and the single-wavefront records.
+struct TriValues {
+    double *val[2] = {nullptr, nullptr}, *dinv[2] = {nullptr, nullptr}, *fold = nullptr;
+    void *wave[2] = {nullptr, nullptr};
+    void *slab = nullptr;  // the allocation they all lie in
+    bool ok = false;
+};
+enum { TRI_ILU = 0, TRI_IC = 1, TRI_GS = 2 };
+
 // Symbolic data of the triangular smoothers for one sweep order (k_tri.hip):
-// formed from A's pattern only.
+// formed from A's pattern only.  The values (TriValues) are packed once per
+// factorisation, or for SGS once per set of A's values.
 struct TriOrder {
     bool built = false;
     bool sym_pattern = false;  // A_ij stored <=> A_ji stored
     int ncolours = 0;          // multicolour order: number of colours
     int n = 0;                 // rows
     const int *rp = nullptr, *ci = nullptr, *dpos = nullptr;  // A's pattern (not owned)
-    int *rank = nullptr;       // position of each row in the order
     int8_t *side = nullptr;    // per entry: -1 earlier column, 0 diagonal, +1 later
     int *lord = nullptr;       // earlier entries of each row sorted by the column's rank
     int *nlow = nullptr;       // their count per row
     int *tpos = nullptr;       // index of the transposed entry, -1 if not stored
-    int *rows_l = nullptr, *rows_u = nullptr;  // rows by level (lower / upper)
-    int *ptr_l = nullptr, *ptr_u = nullptr;    // level pointers (device copies)
-    std::vector<int> h_lev_l, h_lev_u;
-    std::vector<TriSegment> seg_l, seg_u;
-    void *packed = nullptr;    // natural order: per level position, the row's
-                               // entries on the solved side (k_tri.hip)
-    int max_lo = 0, max_up = 0;            // most entries of a row on each side
-    int max_w_l = 0, max_w_u = 0;          // widest level of each triangle
+    TriSide s[2];              // 0: earlier (lower), 1: later (upper) entries
+    void *slab = nullptr;      // the allocation all the above lie in
+    int max_row = 0;           // most entries of a row
+    int4 *ilu_at = nullptr;    // what ILU(0) reads of a row's earlier neighbours
+    int8_t *ilu_map = nullptr; // (k_ilu_map), natural order
+    bool wave = false;         // the solves run in one wavefront (k_tri_wave)
+    TriValues v[3];            // TRI_*
 };
 
 // P's rows in two halves for the smoothing iteration, when the supports are
@@ -613,10 +643,13 @@ void free_tri_order(TriOrder &t);
 // ILU(0) or IC(0) factors in the order; E_BREAKDOWN on a zero (ILU) or
 // non-positive (IC) pivot
 msrsb_status tri_factor(msrsb_ctx *c, int ordering, int kind);
-// z += M^{-1} res for ILU(0) / IC(0); res is overwritten
-void tri_apply(msrsb_ctx *c, int ordering, int kind, double *res, double *z);
-// z += (D + L)^{-1} res (lower) or (D + U)^{-1} res, A's values; res overwritten
-void tri_gs_half(msrsb_ctx *c, int ordering, bool lower, double *res, double *z);
+// z += M^{-1} res for ILU(0) / IC(0), or z = M^{-1} res with set; x: n values
+// of scratch (neither res nor z)
+void tri_apply(msrsb_ctx *c, int ordering, int kind, const double *res, double *z, bool set,
+               double *x);
+// the same with (D + L)^{-1} (lower) or (D + U)^{-1}, A's values
+void tri_gs_half(msrsb_ctx *c, int ordering, bool lower, const double *res, double *z, bool set,
+                 double *x);
 // R's values of the MsFV restriction: 1 where the entry's fine row lies in
 // the coarse row's block, else 0
 void launch_r_indicator(hipStream_t s, int nc, int64_t rnnz, const int *rrp, const int *rci,

@@ -4,9 +4,10 @@
 // order (first-fit colouring in ascending row order on the symmetrised
 // pattern, rows sorted by colour, ascending within a colour).
 //
-// Everything runs on A's own CSR pattern in its original numbering; the
+// The factorisations run on A's own CSR pattern in its original numbering; the
 // order only decides which stored entries count as "earlier" (lower) or
-// "later" (upper).  Rows are grouped into dependency levels of the lower and
+// "later" (upper).  The solves read the factors (or A) packed level by level.
+// Rows are grouped into dependency levels of the lower and
 // of the upper triangle in that order.  A level with many rows is one launch
 // across the whole GPU (thread per row); consecutive levels with few rows are
 // walked by a single work-group with a barrier between levels.  In the
@@ -17,6 +18,7 @@
 // rounding of the sums).
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <numeric>
 
 #include "internal.h"
@@ -99,39 +101,22 @@ __device__ void ic_row(const TriArgs &t, int i, const double *__restrict__ a,
     l[t.dpos[i]] = sqrt(s);
 }
 
-// x_i <- (x_i - sum over the stored entries on one side of vals x) / d_i
-__device__ __forceinline__ void solve_row(const TriArgs &t, int i, int side, bool unit,
-                                          const double *__restrict__ vals,
-                                          double *__restrict__ x)
-{
-    double s = x[i];
-    for (int e = t.rp[i]; e < t.rp[i + 1]; ++e)
-        if (t.side[e] == side) s -= vals[e] * x[t.ci[e]];
-    x[i] = unit ? s : s / vals[t.dpos[i]];
-}
+// --- factorisation kernels: wide (one level, thread per row) and narrow
+// (levels walked by one work-group) ---
 
-// --- kernels: wide (one level, thread per row) and narrow (levels walked by
-// one work-group) ---
-
-enum { OP_ILU = 0, OP_IC = 1, OP_LOWER = 2, OP_UPPER = 3 };
+enum { OP_ILU = 0, OP_IC = 1 };
 
 struct RowOp {
-    int op = OP_LOWER;
-    bool unit = false;
+    int op = OP_ILU;
     const double *a = nullptr;  // IC(0): A's values
-    double *f = nullptr;        // factor values (ILU, IC) or solve values
-    double *x = nullptr;        // solve vector
+    double *f = nullptr;        // factor values
     int *flag = nullptr;
 };
 
 __device__ __forceinline__ void do_row(const TriArgs &t, const RowOp &r, int i)
 {
-    switch (r.op) {
-    case OP_ILU: ilu_row(t, i, r.f, r.flag); break;
-    case OP_IC: ic_row(t, i, r.a, r.f, r.flag); break;
-    case OP_LOWER: solve_row(t, i, -1, r.unit, r.f, r.x); break;
-    default: solve_row(t, i, 1, r.unit, r.f, r.x); break;
-    }
+    if (r.op == OP_ILU) ilu_row(t, i, r.f, r.flag);
+    else ic_row(t, i, r.a, r.f, r.flag);
 }
 
 __global__ __launch_bounds__(256) void k_tri_wide(TriArgs t, RowOp r,
@@ -153,208 +138,399 @@ __global__ __launch_bounds__(kNarrowThreads) void k_tri_narrow(TriArgs t, RowOp 
     }
 }
 
-// The triangular solves of a run of narrow levels in the natural order, for
-// systems of at most kNarrowLdsRows rows: x lives in LDS for the whole run,
-// and a row's entries on the solved side (contiguous in the natural order:
-// the columns before or after the diagonal) are loaded into registers while
-// the previous level is still being solved, so a level costs LDS reads and
-// one barrier instead of a chain of memory round trips.  The arithmetic and
-// its order are those of solve_row.  A thread's first row of a level takes
-// this path; further rows (levels wider than the work-group) and rows with
-// more than kRowRegs entries on the side read their data from memory.
+// ILU(0) of a run of narrow levels by one work-group, kIluLanes lanes per row
+// (rows of at most that many entries, at most kIluLow of them earlier): a lane
+// holds one entry of its row, and everything the row needs of its earlier
+// neighbours (the pivots and the entries that meet the row's columns, found
+// once per pattern by k_ilu_map) is loaded at once when the level starts.  A
+// thread per row walked the neighbours' rows with a search per entry: 6.17 ms
+// for the 298 levels of 100 x 100 cells and nine entries, bound by the chain
+// of dependent loads; 0.68 ms this way.  Same operations in the same order.
+constexpr int kIluLanes = 16;
+constexpr int kIluLow = 8;
+
+// of row position u's w-th earlier neighbour k: the row's entry of that
+// column, k's diagonal entry and first entry (at[u * kIluLow + w], x < 0:
+// none), and per entry f of the row the offset in row k of its column when
+// that comes later than k, else -1 (map[(u * kIluLow + w) * kIluLanes + f])
+__global__ __launch_bounds__(256) void k_ilu_map(TriArgs t, const int *__restrict__ rows, int n,
+                                                 int4 *__restrict__ at, int8_t *__restrict__ map)
+{
+    const int64_t g = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    const int f = static_cast<int>(g % kIluLanes);
+    const int64_t uw = g / kIluLanes;
+    const int u = static_cast<int>(uw / kIluLow), w = static_cast<int>(uw % kIluLow);
+    if (u >= n) return;
+    const int i = rows[u], e0 = t.rp[i], len = t.rp[i + 1] - e0;
+    int m = -1;
+    int4 a = make_int4(-1, 0, 0, 0);
+    if (w < t.nlow[i]) {
+        const int e = t.lord[e0 + w], k = t.ci[e], k0 = t.rp[k];
+        a = make_int4(e - e0, t.dpos[k], k0, 0);
+        if (f < len) {
+            const int q = find_col(t.ci, k0, t.rp[k + 1], t.ci[e0 + f]);
+            if (q >= 0 && t.side[q] > 0) m = q - k0;
+        }
+    }
+    map[g] = static_cast<int8_t>(m);
+    if (f == 0) at[uw] = a;
+}
+
+template <int LOW>
+__global__ __launch_bounds__(kNarrowThreads) void k_ilu_run(TriArgs t,
+                                                            const int *__restrict__ rows,
+                                                            const int *__restrict__ lev, int lev0,
+                                                            int lev1,
+                                                            const int4 *__restrict__ at,
+                                                            const int8_t *__restrict__ map,
+                                                            double *lu, int *__restrict__ flag)
+{
+    const int f = threadIdx.x % kIluLanes, g = threadIdx.x / kIluLanes;
+    constexpr int ROWS = kNarrowThreads / kIluLanes;
+    for (int l = lev0; l < lev1; ++l) {
+        for (int u = lev[l] + g; u < lev[l + 1]; u += ROWS) {
+            const int i = rows[u], e0 = t.rp[i], len = t.rp[i + 1] - e0;
+            const bool own = f < len;
+            int4 a[LOW];
+            int m[LOW];
+#pragma unroll
+            for (int w = 0; w < LOW; ++w) {
+                const int64_t uw = static_cast<int64_t>(u) * kIluLow + w;
+                a[w] = at[uw];
+                m[w] = map[uw * kIluLanes + f];
+            }
+            double v = own ? lu[e0 + f] : 0.0;
+            double piv[LOW], x[LOW];
+#pragma unroll
+            for (int w = 0; w < LOW; ++w) {
+                piv[w] = a[w].x >= 0 ? lu[a[w].y] : 1.0;
+                x[w] = m[w] >= 0 ? lu[a[w].z + m[w]] : 0.0;
+            }
+#pragma unroll
+            for (int w = 0; w < LOW; ++w) {
+                if (a[w].x < 0) continue;  // the same for a row's lanes
+                if (piv[w] == 0.0) flag[0] = 1;
+                const double lik = __shfl(v, a[w].x, kIluLanes) / piv[w];
+                if (f == a[w].x) v = lik;
+                else if (m[w] >= 0) v -= lik * x[w];
+            }
+            if (own) lu[e0 + f] = v;
+        }
+        __syncthreads();
+    }
+}
+
+// --- solves on the packed sides (TriSide, TriValues) ---
+//
+// One side's pass: x_i = (in_i - sum val x_col) dinv, with `in` the right-hand
+// side of the first pass or the first pass's x for the second.  A level's
+// columns, values and rows are packed level by level, so a row costs two
+// memory round trips (its packed data, then x at its columns) instead of four
+// dependent ones through the CSR arrays.  Three launches fewer per
+// application than a launch per level and triangle plus the copy and the sum:
+// - rows of the second level take what they need of the first from `in`
+//   (marked columns; the first level's division is folded into the values),
+//   so the first two levels go together;
+// - a row with nothing on the upper side (the upper triangle's first level)
+//   needs no second pass: the first one ends with its division (fold);
+// - the last pass adds x to z (or sets it).
+// The coloured ILU(0) on 65,536 rows of nine entries: 8 launches of 5.2 us, a
+// copy and a sum -> 6 launches of 3.1 us per application; the coloured IC(0)
+// on 215,025 rows of seven: 4 launches of 7.9 us, a copy and a sum -> 2 of 6.2.
+constexpr int kTriFirst = INT32_MIN;
+
+struct TriPass {
+    const int *row, *col;
+    const double *val, *dinv, *fold;  // fold: null unless this pass ends some rows
+    const double *in;
+    double *x, *z;
+    bool last;  // every row of the pass ends here (z is written)
+    bool set;   // z = x instead of z += x
+};
+
+__device__ __forceinline__ void tri_end(const TriPass &p, int i, double s)
+{
+    p.z[i] = p.set ? s : p.z[i] + s;
+}
+
+// positions [u0, u0 + skip + cnt): `skip` rows without entries (level 0, when
+// the first two levels go together), then the cnt rows of one level with their
+// entries from place `at` on.  W: the width, or 0 for any.  FIRST: a first
+// pass (marked columns are read from `in`; a second pass has in = x).
+template <int W, bool FIRST>
+__global__ __launch_bounds__(256) void k_tri_level(TriPass p, int u0, int skip, int cnt,
+                                                   int64_t at, int width)
+{
+    const int tt = blockIdx.x * 256 + threadIdx.x, t = tt - skip;
+    if (t >= cnt) return;
+    const int u = u0 + tt, i = p.row[u];
+    const double di = p.dinv[u], fo = p.fold ? p.fold[u] : 0.0;
+    double s = p.in[i];
+    constexpr int C = W > 0 ? W : 8;  // entries per step
+    const int n = t < 0 ? 0 : W > 0 ? W : width;
+    for (int k0 = 0; k0 < n; k0 += C) {
+        int c[C];
+        double v[C], xv[C];
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            // a step past the width repeats its last entry with value 0
+            const int kk = W > 0 ? k : min(k0 + k, width - 1);
+            const int64_t e = at + static_cast<int64_t>(kk) * cnt + t;
+            c[k] = p.col[e];
+            v[k] = W > 0 || k0 + k < width ? p.val[e] : 0.0;
+        }
+#pragma unroll
+        for (int k = 0; k < C; ++k)
+            xv[k] = FIRST && c[k] < 0 ? p.in[c[k] & ~kTriFirst] : p.x[c[k] & ~kTriFirst];
+#pragma unroll
+        for (int k = 0; k < C; ++k) s -= v[k] * xv[k];
+    }
+    s *= di;
+    const bool end = p.last || fo != 0.0;
+    if (fo != 0.0) s *= fo;
+    p.x[i] = s;
+    if (end) tri_end(p, i, s);
+}
+
+// a run of narrow levels by one work-group with a barrier between levels; x
+// in LDS for systems of at most kNarrowLdsRows rows.  The first kRowRegs
+// entries of a thread's first row of a level are loaded while the previous
+// level is still being solved.
 constexpr int kNarrowLdsRows = 16384;  // 128 KB of LDS
 constexpr int kRowRegs = 8;
 
-struct SolveRow {
-    int i, ne;
-    int c[kRowRegs];
-    double v[kRowRegs];
-    double d;
-};
-
-__global__ __launch_bounds__(kNarrowThreads) void k_tri_narrow_lds(TriArgs t, RowOp r,
-                                                                   const int *__restrict__ lev_ptr,
-                                                                   const int *__restrict__ rows,
-                                                                   int lev0, int lev1, int n)
+template <bool LDS>
+__global__ __launch_bounds__(kNarrowThreads) void k_tri_run(TriPass p,
+                                                            const int *__restrict__ lev,
+                                                            const int *__restrict__ width,
+                                                            const int64_t *__restrict__ off,
+                                                            int lev0, int lev1, int n, bool second)
 {
     extern __shared__ double sx[];
     const int tid = threadIdx.x;
-    const bool lower = r.op == OP_LOWER;
-    const int side = lower ? -1 : 1;
-    for (int i = tid; i < n; i += kNarrowThreads) sx[i] = r.x[i];
-    auto load = [&](int l, SolveRow &q) {
+    double *x = LDS ? sx : p.x;
+    if (LDS && (lev0 > 0 || second)) {
+        for (int i = tid; i < n; i += kNarrowThreads) sx[i] = p.x[i];
+        __syncthreads();
+    }
+    const double *in = second ? x : p.in;
+    struct Row {
+        int i, c[kRowRegs];
+        double v[kRowRegs], d, fo;
+    };
+    auto load = [&](int l, int t, Row &q) {
         q.i = -1;
-        q.ne = 0;
         if (l >= lev1) return;
-        const int u = lev_ptr[l] + tid;
-        if (u >= lev_ptr[l + 1]) return;
-        const int i = rows[u];
-        const int dp = t.dpos[i];
-        const int b = lower ? t.rp[i] : dp + 1, e = lower ? dp : t.rp[i + 1];
-        q.i = i;
-        q.ne = e - b;
+        const int u0 = lev[l], cnt = lev[l + 1] - u0, w = width[l];
+        if (t >= cnt) return;
+        const int64_t at = off[l] + t;
+        q.i = p.row[u0 + t];
+        q.d = p.dinv[u0 + t];
+        q.fo = p.fold ? p.fold[u0 + t] : 0.0;
 #pragma unroll
         for (int k = 0; k < kRowRegs; ++k) {
-            const int idx = b + k < e ? b + k : dp;
-            q.c[k] = t.ci[idx];
-            q.v[k] = r.f[idx];
+            // (marked: padding; the first level's columns are marked in wide
+            // levels only)
+            q.c[k] = k < w ? p.col[at + static_cast<int64_t>(k) * cnt] : kTriFirst;
+            q.v[k] = k < w ? p.val[at + static_cast<int64_t>(k) * cnt] : 0.0;
         }
-        q.d = r.unit ? 1.0 : r.f[dp];
     };
-    auto slow = [&](int i) {
-        double s = sx[i];
-        for (int e = t.rp[i]; e < t.rp[i + 1]; ++e)
-            if (t.side[e] == side) s -= r.f[e] * sx[t.ci[e]];
-        sx[i] = r.unit ? s : s / r.f[t.dpos[i]];
-    };
-    SolveRow cur, nxt;
-    load(lev0, cur);
-    __syncthreads();
-    for (int l = lev0; l < lev1; ++l) {
-        load(l + 1, nxt);  // independent of x: in flight while this level is solved
-        if (cur.i >= 0) {
-            if (cur.ne <= kRowRegs) {
-                double s = sx[cur.i];
+    auto solve = [&](int l, int t, const Row &q) {
+        double s = in[q.i];
+        const int w = width[l];
 #pragma unroll
-                for (int k = 0; k < kRowRegs; ++k)
-                    if (k < cur.ne) s -= cur.v[k] * sx[cur.c[k]];
-                sx[cur.i] = r.unit ? s : s / cur.d;
-            } else {
-                slow(cur.i);
+        for (int k = 0; k < kRowRegs; ++k)
+            if (q.c[k] >= 0) s -= q.v[k] * x[q.c[k]];
+        if (w > kRowRegs) {
+            const int cnt = lev[l + 1] - lev[l];
+            for (int k = kRowRegs; k < w; ++k) {
+                const int64_t e = off[l] + static_cast<int64_t>(k) * cnt + t;
+                const int c = p.col[e];
+                if (c >= 0) s -= p.val[e] * x[c];
             }
         }
-        for (int u = lev_ptr[l] + tid + kNarrowThreads; u < lev_ptr[l + 1]; u += kNarrowThreads)
-            slow(rows[u]);
+        s *= q.d;
+        const bool end = p.last || q.fo != 0.0;
+        if (q.fo != 0.0) s *= q.fo;
+        x[q.i] = s;
+        if (LDS) p.x[q.i] = s;
+        if (end) tri_end(p, q.i, s);
+    };
+    Row cur, nxt;
+    load(lev0, tid, cur);
+    for (int l = lev0; l < lev1; ++l) {
+        load(l + 1, tid, nxt);  // independent of x
+        if (cur.i >= 0) solve(l, tid, cur);
+        for (int t = tid + kNarrowThreads; t < lev[l + 1] - lev[l]; t += kNarrowThreads) {
+            Row q;
+            load(l, t, q);
+            solve(l, t, q);
+        }
         __syncthreads();
         cur = nxt;
     }
-    for (int i = tid; i < n; i += kNarrowThreads) r.x[i] = sx[i];
 }
 
-// A run of narrow levels in the natural order solved by one wavefront, with
-// no barrier between levels: a wavefront's LDS operations complete in
-// order, so a level reads the x values the previous levels wrote.  Each
-// lane takes up to two rows of a level (levels of at most kTriWaveRows rows,
-// rows of at most kTriWaveW entries on the solved side), whose entries are
-// packed beforehand (k_tri_pack) and loaded kTriDepth levels ahead, so a
-// level costs LDS reads, its products and one division.  The arithmetic and
-// its order are those of solve_row.
-// levels loaded ahead and steps per loop trip, by row width (the ring of
-// loaded rows has to fit the registers); the solve takes rows of at most
-// kTriWaveW entries on the solved side (2D 9-point stencils and narrower)
-template <int W> constexpr int kTriDepth = W <= 4 ? 6 : 3;
-template <int W> constexpr int kTriUnroll = W <= 4 ? 4 : 8;
+// Both triangles (or one) of a system of narrow levels in the natural order
+// by one wavefront, with no barrier between levels: a wavefront's LDS
+// operations complete in order, so a level reads the x values the previous
+// levels wrote.  Levels of at most 64 rows per H, rows of at most kTriWaveW
+// entries per side (2D 9-point stencils and narrower): each level is H x 64
+// records of 64 bytes (LDS offsets, values, the diagonal's reciprocal; lanes
+// without a row work on the spare slot), stored lane by lane and loaded
+// kTriDepth levels ahead, so a level costs one LDS round trip, its products
+// and the instructions of one row per lane: the wavefront is alone on its
+// SIMD and bound by their issue.  The other wavefronts of the work-group only
+// move x in and z out.
+// 2 x 134 us (rows of two per lane, 128-byte records with counts and level
+// pointers, a division per row) + 2 x 5.8 us (records packed on each call) ->
+// 69 us per application of ILU(0) on 100 x 100 cells (298 levels a side).
 constexpr int kTriWaveW = 4;
-constexpr int kTriWaveRows = 128;       // rows per level (two per lane)
-constexpr size_t kTriWaveLds = 160 * 1024;  // x, the spare slot and the level pointers
+constexpr int kTriDepth = 6;    // levels loaded ahead
+constexpr int kTriTrip = 24;    // levels per loop trip (a multiple of kTriDepth)
 
-struct alignas(16) PackedRow {
-    int i, ne, b, pad;     // row; its entries on the solved side: count, first
-    int c[kRowRegs];       // their columns (at most kRowRegs kept)
-    double v[kRowRegs];    // their values
-    double d, pad2;        // the diagonal (1 for a unit diagonal)
+struct alignas(16) WaveRec {
+    int c[4];       // LDS byte offsets of the columns
+    double v[4];
+    double d;
+    int i, pad;     // LDS byte offset of the row
+};
+// the records' four 16-byte quarters of the 64 lanes one after another
+struct WaveLevel {
+    int4 q[4][64];
 };
 
-__global__ __launch_bounds__(256) void k_tri_pack(TriArgs t, RowOp r,
-                                                  const int *__restrict__ rows, int u0, int u1,
-                                                  PackedRow *__restrict__ rec)
+template <int H>
+__device__ __forceinline__ void tri_wave_side(char *sx, const WaveLevel *__restrict__ rec,
+                                              int nlev)
 {
-    const int u = u0 + static_cast<int>(blockIdx.x) * 256 + static_cast<int>(threadIdx.x);
-    if (u >= u1) return;
-    const int i = rows[u];
-    const int dp = t.dpos[i];
-    const bool lower = r.op == OP_LOWER;
-    const int b = lower ? t.rp[i] : dp + 1, e = lower ? dp : t.rp[i + 1];
-    PackedRow q;
-    q.i = i;
-    q.ne = e - b;
-    q.b = b;
-    q.pad = 0;
-#pragma unroll
-    for (int k = 0; k < kRowRegs; ++k) {
-        const int idx = b + k < e ? b + k : dp;
-        q.c[k] = t.ci[idx];
-        q.v[k] = r.f[idx];
-    }
-    q.d = r.unit ? 1.0 : r.f[dp];
-    q.pad2 = 0.0;
-    rec[u] = q;
-}
-
-// One packed row (at most kRowRegs entries): s = x_i - (its entries times
-// x), x_i = s or s / d, in solve_row's order.  The slots past the row's
-// count hold its own column (a valid index) and add zero, and a lane
-// without a row (ok false) writes its duplicate's value to the spare slot
-// sx[n]: no branch, so the loads kTriDepth levels ahead stay in flight.
-template <int W>
-__device__ __forceinline__ void tri_wave_solve(const RowOp &r, double *sx, int n,
-                                               const PackedRow &q, bool ok)
-{
-    double s = sx[q.i];
-#pragma unroll
-    for (int k = 0; k < W; ++k) {
-        const double xv = sx[q.c[k]];
-        s -= (k < q.ne ? q.v[k] : 0.0) * xv;
-    }
-    sx[ok ? q.i : n] = r.unit ? s : s / q.d;
-}
-
-// W: the most entries of a row on the solved side (4 or kRowRegs); only
-// those slots of the packed rows are loaded and used
-template <int W>
-__global__ __launch_bounds__(64) void k_tri_wave(RowOp r, const int *__restrict__ lev_ptr,
-                                                 const PackedRow *__restrict__ rec, int lev0,
-                                                 int lev1, int n)
-{
-    // n + 1 values: x and a spare slot; then the run's level pointers, kept
-    // in LDS so that no other memory load sits between the rows' loads (a
-    // wait for one would wait for all rows loaded before it)
-    extern __shared__ double sx[];
-    int *slev = reinterpret_cast<int *>(sx + n + 1);
     const int lane = threadIdx.x;
-    for (int i = lane; i < n; i += 64) sx[i] = r.x[i];
-    for (int l = lev0 + lane; l <= lev1; l += 64) slev[l - lev0] = lev_ptr[l];
-    // the first kTriWaveRows rows of level l (positions clamped to the level,
-    // and a level past the run to the last one: every load is in bounds)
-    auto load = [&](int l, PackedRow (&q)[2], bool (&ok)[2]) {
-        const int lc = min(l, lev1 - 1) - lev0;
-        const int u0 = slev[lc], u1 = slev[lc + 1];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int u = u0 + lane + 64 * h;
-            ok[h] = l < lev1 && u < u1;
-            const PackedRow &g = rec[min(u, u1 - 1)];
-            q[h].i = g.i;
-            q[h].ne = g.ne;
-#pragma unroll
-            for (int k = 0; k < W; ++k) {
-                q[h].c[k] = g.c[k];
-                q[h].v[k] = g.v[k];
-            }
-            q[h].d = g.d;
-        }
+    union Slot {
+        int4 q[4];
+        WaveRec r;
+        __device__ Slot() {}
     };
-    PackedRow ring[kTriDepth<W>][2];
-    bool rok[kTriDepth<W>][2];
+    Slot ring[kTriDepth][H];
+    auto load = [&](int l, Slot(&s)[H]) {
 #pragma unroll
-    for (int k = 0; k < kTriDepth<W>; ++k) load(lev0 + k, ring[k], rok[k]);
-    // kTriUnroll steps of kTriDepth levels per loop trip: the compiler waits
-    // for every row in flight where the loop closes, so it closes rarely
-    for (int l = lev0; l < lev1; l += kTriDepth<W> * kTriUnroll<W>) {
+        for (int h = 0; h < H; ++h)
 #pragma unroll
-        for (int kk = 0; kk < kTriDepth<W> * kTriUnroll<W>; ++kk) {
-            const int k = kk % kTriDepth<W>;
-            // (levels past the run: their rows are marked, nothing is written;
-            // the scheduling barriers keep a later level's arithmetic, and
-            // with it the wait for its rows, below this level's)
+            for (int k = 0; k < 4; ++k) s[h].q[k] = rec[l * H + h].q[k][lane];
+    };
+#pragma unroll
+    for (int k = 0; k < kTriDepth; ++k) load(k, ring[k]);
+    // the records hold a multiple of kTriTrip levels and kTriDepth more
+    for (int l = 0; l < nlev; l += kTriTrip) {
+#pragma unroll
+        for (int kk = 0; kk < kTriTrip; ++kk) {
+            Slot(&cur)[H] = ring[kk % kTriDepth];
+            // (the scheduling barriers keep a later level's arithmetic, and
+            // with it the wait for its records, below this level's)
             __builtin_amdgcn_sched_barrier(0);
-            tri_wave_solve<W>(r, sx, n, ring[k][0], rok[k][0]);
-            tri_wave_solve<W>(r, sx, n, ring[k][1], rok[k][1]);
-            load(l + kk + kTriDepth<W>, ring[k], rok[k]);
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+                const WaveRec &r = cur[h].r;
+                double s = *reinterpret_cast<double *>(sx + r.i);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    s -= r.v[k] * *reinterpret_cast<double *>(sx + r.c[k]);
+                *reinterpret_cast<double *>(sx + r.i) = s * r.d;
+            }
+            load(l + kk + kTriDepth, cur);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    for (int i = lane; i < n; i += 64) r.x[i] = sx[i];
+}
+
+template <int H>
+__global__ __launch_bounds__(256) void k_tri_wave(int n, const double *__restrict__ in,
+                                                  double *__restrict__ z, bool set,
+                                                  const WaveLevel *__restrict__ rec0, int nlev0,
+                                                  const WaveLevel *__restrict__ rec1, int nlev1)
+{
+    extern __shared__ double sx[];  // x and a spare slot
+    for (int i = threadIdx.x; i < n; i += 256) sx[i] = in[i];
+    if (threadIdx.x == 0) sx[n] = 0.0;
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        if (rec0) tri_wave_side<H>(reinterpret_cast<char *>(sx), rec0, nlev0);
+        if (rec1) tri_wave_side<H>(reinterpret_cast<char *>(sx), rec1, nlev1);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += 256) z[i] = set ? sx[i] : z[i] + sx[i];
+}
+
+// --- packing of the values ---
+
+// entries: f's value, with scale (first passes with a diagonal) the first
+// level's division folded into the marked columns' values; padding: 0
+__global__ __launch_bounds__(256) void k_tri_pack(int64_t m, const int *__restrict__ src,
+                                                  const int *__restrict__ col,
+                                                  const int *__restrict__ dpos, bool scale,
+                                                  const double *__restrict__ f,
+                                                  double *__restrict__ val)
+{
+    const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (e >= m) return;
+    const int q = src[e], c = col[e];
+    double v = q < 0 ? 0.0 : f[q];
+    if (q >= 0 && c < 0 && scale) v /= f[dpos[c & ~kTriFirst]];
+    val[e] = v;
+}
+
+__global__ __launch_bounds__(256) void k_tri_pack_diag(int n, const int *__restrict__ row,
+                                                       const int *__restrict__ dpos,
+                                                       const int *__restrict__ foldsrc, bool unit,
+                                                       const double *__restrict__ f,
+                                                       double *__restrict__ dinv,
+                                                       double *__restrict__ fold)
+{
+    const int u = blockIdx.x * 256 + threadIdx.x;
+    if (u >= n) return;
+    dinv[u] = unit ? 1.0 : 1.0 / f[dpos[row[u]]];
+    if (fold) fold[u] = foldsrc[u] < 0 ? 0.0 : 1.0 / f[foldsrc[u]];
+}
+
+// the wavefront's records of level blockIdx.x (levels past nlev: no rows)
+template <int H>
+__global__ __launch_bounds__(64 * H) void k_tri_pack_wave(int n, int nlev,
+                                                          const int *__restrict__ lev,
+                                                          const int *__restrict__ width,
+                                                          const int64_t *__restrict__ off,
+                                                          const int *__restrict__ row,
+                                                          const int *__restrict__ col,
+                                                          const double *__restrict__ val,
+                                                          const double *__restrict__ dinv,
+                                                          WaveLevel *__restrict__ rec)
+{
+    const int l = blockIdx.x, t = threadIdx.x;
+    union {
+        int4 q[4];
+        WaveRec r;
+    } s;
+    s.r.i = 8 * n;
+    s.r.pad = 0;
+    s.r.d = 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        s.r.c[k] = 8 * n;
+        s.r.v[k] = 0.0;
+    }
+    if (l < nlev && t < lev[l + 1] - lev[l]) {
+        const int u = lev[l] + t, cnt = lev[l + 1] - lev[l], w = width[l];
+        s.r.i = 8 * row[u];
+        s.r.d = dinv[u];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t e = off[l] + static_cast<int64_t>(k) * cnt + t;
+            if (k < w && val[e] != 0.0) {
+                s.r.c[k] = 8 * (col[e] & ~kTriFirst);
+                s.r.v[k] = val[e];
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) rec[l * H + t / 64].q[k][t & 63] = s.q[k];
 }
 
 // upper entries of the IC(0) array take the factor value of their transpose
@@ -371,13 +547,6 @@ __global__ __launch_bounds__(256) void k_copy_vals(int64_t m, const double *__re
 {
     const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     if (t < m) b[t] = a[t];
-}
-
-__global__ __launch_bounds__(256) void k_add(int n, const double *__restrict__ x,
-                                             double *__restrict__ z)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n) z[i] += x[i];
 }
 
 // --- host: colouring, levels, launch segments ---
@@ -451,55 +620,218 @@ void segments(const std::vector<int> &ptr, std::vector<TriSegment> &seg)
     }
 }
 
-template <typename T>
-bool upload(T *&d, const std::vector<T> &h)
+// Arrays that live and die together, in one device allocation (the host
+// vectors must outlive upload()).
+struct Slab {
+    struct Place {
+        void **dst;
+        const void *src;
+        size_t at, len;
+    };
+    std::vector<Place> places;
+    size_t bytes = 0;
+    template <typename T>
+    void add(T **dst, const std::vector<T> &h)
+    {
+        places.push_back({reinterpret_cast<void **>(dst), h.data(), bytes, h.size() * sizeof(T)});
+        bytes += (h.size() * sizeof(T) + 255) / 256 * 256;
+    }
+    bool upload(void **slab)
+    {
+        bool ok = hipMalloc(slab, std::max<size_t>(bytes, 1)) == hipSuccess;
+        for (const Place &p : places) {
+            if (!ok) break;
+            *p.dst = static_cast<char *>(*slab) + p.at;
+            ok = p.len == 0 || hipMemcpy(*p.dst, p.src, p.len, hipMemcpyHostToDevice) == hipSuccess;
+        }
+        return ok;
+    }
+};
+
+// the maps of k_ilu_run, once per pattern: natural order, rows that fit its
+// lanes, and at most 512 MB of them
+bool ilu_maps(hipStream_t s, TriOrder &t)
 {
-    if (hipMalloc(&d, std::max<size_t>(h.size(), 1) * sizeof(T)) != hipSuccess) return false;
-    return hipMemcpy(d, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice) == hipSuccess;
+    if (t.ilu_at || t.ncolours > 0 || t.max_row > kIluLanes || t.s[0].max_w > kIluLow ||
+        static_cast<int64_t>(t.n) * kIluLow * kIluLanes > (int64_t(1) << 29))
+        return true;
+    const int64_t m = static_cast<int64_t>(t.n) * kIluLow;
+    if (hipMalloc(&t.ilu_at, m * sizeof(int4)) != hipSuccess ||
+        hipMalloc(&t.ilu_map, m * kIluLanes) != hipSuccess)
+        return false;
+    const TriArgs a{t.rp, t.ci, t.dpos, t.side, t.lord, t.nlow};
+    k_ilu_map<<<static_cast<int>((m * kIluLanes + 255) / 256), 256, 0, s>>>(
+        a, t.s[0].row, t.n, t.ilu_at, t.ilu_map);
+    return true;
 }
 
-void run_levels(hipStream_t s, const TriOrder &t, bool lower, const RowOp &r)
+void run_factor(hipStream_t s, const TriOrder &t, const RowOp &r)
 {
     const TriArgs a{t.rp, t.ci, t.dpos, t.side, t.lord, t.nlow};
-    const std::vector<int> &ptr = lower ? t.h_lev_l : t.h_lev_u;
-    const std::vector<TriSegment> &seg = lower ? t.seg_l : t.seg_u;
-    const int *rows = lower ? t.rows_l : t.rows_u;
-    const int *dptr = lower ? t.ptr_l : t.ptr_u;
-    for (const TriSegment &g : seg) {
+    const TriSide &q = t.s[0];
+    for (const TriSegment &g : q.seg) {
         if (g.wide) {
-            const int cnt = ptr[g.lev0 + 1] - ptr[g.lev0];
-            k_tri_wide<<<(cnt + 255) / 256, 256, 0, s>>>(a, r, rows + ptr[g.lev0], cnt);
-        } else if (t.ncolours == 0 && (r.op == OP_LOWER || r.op == OP_UPPER) &&
-                   t.n <= kNarrowLdsRows && t.packed &&
-                   (lower ? t.max_lo : t.max_up) <= kTriWaveW &&
-                   (lower ? t.max_w_l : t.max_w_u) <= kTriWaveRows &&
-                   static_cast<size_t>(t.n + 1) * sizeof(double) +
-                           static_cast<size_t>(g.lev1 - g.lev0 + 1) * sizeof(int) <=
-                       kTriWaveLds) {
-            const size_t sh = static_cast<size_t>(t.n + 1) * sizeof(double) +
-                              static_cast<size_t>(g.lev1 - g.lev0 + 1) * sizeof(int);
-            auto *rec = static_cast<PackedRow *>(t.packed);
-            const int u0 = ptr[g.lev0], u1 = ptr[g.lev1];
-            k_tri_pack<<<(u1 - u0 + 255) / 256, 256, 0, s>>>(a, r, rows, u0, u1, rec);
-            auto wave = [&](auto kern) {
-                if (sh > 65536)
-                    hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        static_cast<int>(sh));
-                kern<<<1, 64, sh, s>>>(r, dptr, rec, g.lev0, g.lev1, t.n);
-            };
-            wave(k_tri_wave<kTriWaveW>);
-        } else if (t.ncolours == 0 && (r.op == OP_LOWER || r.op == OP_UPPER) &&
-                   t.n <= kNarrowLdsRows) {
-            const size_t sh = static_cast<size_t>(t.n) * sizeof(double);
+            const int cnt = q.lev[g.lev0 + 1] - q.lev[g.lev0];
+            k_tri_wide<<<(cnt + 255) / 256, 256, 0, s>>>(a, r, q.row + q.lev[g.lev0], cnt);
+        } else if (r.op == OP_ILU && t.ilu_map) {
+            auto kern = q.max_w <= 4 ? k_ilu_run<4> : k_ilu_run<kIluLow>;
+            kern<<<1, kNarrowThreads, 0, s>>>(a, q.row, q.d_lev, g.lev0, g.lev1, t.ilu_at,
+                                              t.ilu_map, r.f, r.flag);
+        } else {
+            k_tri_narrow<<<1, kNarrowThreads, 0, s>>>(a, r, q.d_lev, q.row, g.lev0, g.lev1);
+        }
+    }
+}
+
+// levels of a side's records: its own, rounded up to whole loop trips
+int wave_levels(const TriSide &q)
+{
+    const int nlev = static_cast<int>(q.lev.size()) - 1;
+    return (nlev + kTriTrip - 1) / kTriTrip * kTriTrip;
+}
+int wave_rows(const TriOrder &t) { return std::max(t.s[0].max_cnt, t.s[1].max_cnt) <= 64 ? 1 : 2; }
+
+void launch_level(hipStream_t s, const TriPass &p, bool first, int u0, int skip, int cnt,
+                  int64_t at, int width)
+{
+    auto go = [&](auto w) {
+        constexpr int W = decltype(w)::value;
+        const int nb = (skip + cnt + 255) / 256;
+        if (first) k_tri_level<W, true><<<nb, 256, 0, s>>>(p, u0, skip, cnt, at, width);
+        else k_tri_level<W, false><<<nb, 256, 0, s>>>(p, u0, skip, cnt, at, width);
+    };
+    using std::integral_constant;
+    switch (width) {
+    case 1: go(integral_constant<int, 1>{}); break;
+    case 2: go(integral_constant<int, 2>{}); break;
+    case 3: go(integral_constant<int, 3>{}); break;
+    case 4: go(integral_constant<int, 4>{}); break;
+    case 5: go(integral_constant<int, 5>{}); break;
+    case 6: go(integral_constant<int, 6>{}); break;
+    case 7: go(integral_constant<int, 7>{}); break;
+    case 8: go(integral_constant<int, 8>{}); break;
+    default: go(integral_constant<int, 0>{}); break;
+    }
+}
+
+// one side's pass; second: the other side's pass came first (p.in == p.x) and,
+// with a symmetric pattern, has ended the rows of this side's level 0
+void run_side(hipStream_t s, const TriOrder &t, const TriSide &q, const TriPass &p, bool second)
+{
+    const int from = second && t.sym_pattern ? 1 : 0;
+    for (const TriSegment &g : q.seg) {
+        const int lev0 = std::max(g.lev0, from);
+        if (lev0 >= g.lev1) continue;
+        if (g.wide) {
+            const bool merged = q.merged && !second;
+            if (merged && lev0 == 0) continue;  // in level 1's launch
+            const int skip = merged && lev0 == 1 ? q.lev[1] : 0;
+            launch_level(s, p, !second, q.lev[lev0] - skip, skip, q.lev[lev0 + 1] - q.lev[lev0],
+                         q.off[lev0], q.width[lev0]);
+            continue;
+        }
+        const size_t sh = t.n <= kNarrowLdsRows ? static_cast<size_t>(t.n) * sizeof(double) : 0;
+        if (sh > 65536)
+            hipFuncSetAttribute(reinterpret_cast<const void *>(k_tri_run<true>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(sh));
+        if (sh)
+            k_tri_run<true><<<1, kNarrowThreads, sh, s>>>(p, q.d_lev, q.d_width, q.d_off, lev0,
+                                                          g.lev1, t.n, second);
+        else
+            k_tri_run<false><<<1, kNarrowThreads, 0, s>>>(p, q.d_lev, q.d_width, q.d_off, lev0,
+                                                          g.lev1, t.n, second);
+    }
+}
+
+// room for the packed sides' values of one smoother, allocated once
+bool alloc_values(const TriOrder &t, TriValues &v)
+{
+    if (v.slab) return true;
+    size_t bytes = 0;
+    auto place = [&](size_t m) {
+        const size_t at = bytes;
+        bytes += (m + 255) / 256 * 256;
+        return at;
+    };
+    size_t val[2], dinv[2], wave[2];
+    for (int side = 0; side < 2; ++side) {
+        const TriSide &q = t.s[side];
+        val[side] = place(q.off.back() * sizeof(double));
+        dinv[side] = place(t.n * sizeof(double));
+        wave[side] = place(!t.wave ? 0
+                                   : static_cast<size_t>(wave_levels(q) + kTriDepth) *
+                                         wave_rows(t) * sizeof(WaveLevel));
+    }
+    const size_t fold = place(t.n * sizeof(double));
+    if (hipMalloc(&v.slab, bytes) != hipSuccess) return false;
+    char *base = static_cast<char *>(v.slab);
+    for (int side = 0; side < 2; ++side) {
+        v.val[side] = reinterpret_cast<double *>(base + val[side]);
+        v.dinv[side] = reinterpret_cast<double *>(base + dinv[side]);
+        v.wave[side] = base + wave[side];
+    }
+    v.fold = reinterpret_cast<double *>(base + fold);
+    return true;
+}
+
+void pack_values(hipStream_t s, TriOrder &t, int kind, const double *f)
+{
+    TriValues &v = t.v[kind];
+    for (int side = 0; side < 2; ++side) {
+        const TriSide &q = t.s[side];
+        const bool unit = kind == TRI_ILU && side == 0;
+        const bool first = side == 0 || kind == TRI_GS;
+        const int64_t m = q.off.back();
+        if (m > 0)
+            k_tri_pack<<<static_cast<int>((m + 255) / 256), 256, 0, s>>>(
+                m, q.src, q.col, t.dpos, first && !unit, f, v.val[side]);
+        const bool fold = side == 0 && kind != TRI_GS && t.sym_pattern;
+        k_tri_pack_diag<<<(t.n + 255) / 256, 256, 0, s>>>(t.n, q.row, t.dpos, q.fold, unit, f,
+                                                          v.dinv[side], fold ? v.fold : nullptr);
+        if (!t.wave) continue;
+        const int nlev = static_cast<int>(q.lev.size()) - 1, nl = wave_levels(q) + kTriDepth;
+        auto *rec = static_cast<WaveLevel *>(v.wave[side]);
+        if (wave_rows(t) == 1)
+            k_tri_pack_wave<1><<<nl, 64, 0, s>>>(t.n, nlev, q.d_lev, q.d_width, q.d_off, q.row,
+                                                 q.col, v.val[side], v.dinv[side], rec);
+        else
+            k_tri_pack_wave<2><<<nl, 128, 0, s>>>(t.n, nlev, q.d_lev, q.d_width, q.d_off, q.row,
+                                                  q.col, v.val[side], v.dinv[side], rec);
+    }
+    v.ok = true;
+}
+
+// z (+)= the solve of the sides [side0, side1] with the values of a kind
+void run_solve(hipStream_t s, const TriOrder &t, int kind, int side0, int side1,
+               const double *res, double *z, bool set, double *x)
+{
+    const TriValues &v = t.v[kind];
+    if (t.wave) {
+        const size_t sh = static_cast<size_t>(t.n + 1) * sizeof(double);
+        const bool both = side0 != side1;
+        auto go = [&](auto kern) {
             if (sh > 65536)
-                hipFuncSetAttribute(reinterpret_cast<const void *>(k_tri_narrow_lds),
+                hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                     hipFuncAttributeMaxDynamicSharedMemorySize,
                                     static_cast<int>(sh));
-            k_tri_narrow_lds<<<1, kNarrowThreads, sh, s>>>(a, r, dptr, rows, g.lev0, g.lev1, t.n);
-        } else {
-            k_tri_narrow<<<1, kNarrowThreads, 0, s>>>(a, r, dptr, rows, g.lev0, g.lev1);
-        }
+            kern<<<1, 256, sh, s>>>(t.n, res, z, set,
+                                    static_cast<const WaveLevel *>(v.wave[side0]),
+                                    wave_levels(t.s[side0]),
+                                    both ? static_cast<const WaveLevel *>(v.wave[side1]) : nullptr,
+                                    both ? wave_levels(t.s[side1]) : 0);
+        };
+        if (wave_rows(t) == 1) go(k_tri_wave<1>);
+        else go(k_tri_wave<2>);
+        return;
+    }
+    for (int side = side0;; side = side1) {
+        const TriSide &q = t.s[side];
+        const bool second = side != side0, last = side == side1;
+        const TriPass p{q.row, q.col, v.val[side], v.dinv[side],
+                        !last && t.sym_pattern ? v.fold : nullptr,
+                        second ? x : res, x, z, last, set};
+        run_side(s, t, q, p, second);
+        if (last) break;
     }
 }
 
@@ -507,11 +839,8 @@ void run_levels(hipStream_t s, const TriOrder &t, bool lower, const RowOp &r)
 
 void free_tri_order(TriOrder &t)
 {
-    for (void *p : {static_cast<void *>(t.rank), static_cast<void *>(t.side),
-                    static_cast<void *>(t.lord), static_cast<void *>(t.nlow),
-                    static_cast<void *>(t.tpos), static_cast<void *>(t.rows_l),
-                    static_cast<void *>(t.rows_u), static_cast<void *>(t.ptr_l),
-                    static_cast<void *>(t.ptr_u), t.packed})
+    for (void *p : {t.slab, static_cast<void *>(t.ilu_at), static_cast<void *>(t.ilu_map),
+                    t.v[0].slab, t.v[1].slab, t.v[2].slab})
         if (p) hipFree(p);
     t = TriOrder();
 }
@@ -540,56 +869,101 @@ msrsb_status tri_order_setup(msrsb_ctx *c, int ordering)
     const int64_t nnz = c->nnz;
     std::vector<int8_t> side(nnz);
     std::vector<int> lord(nnz, 0), nlow(n, 0), tpos(nnz, -1);
+    std::vector<std::pair<int, int>> low;
+    std::vector<int> count[2];  // entries of a row on each side
+    count[0].assign(n, 0);
+    count[1].assign(n, 0);
     for (int i = 0; i < n; ++i) {
-        std::vector<std::pair<int, int>> low;
+        low.clear();
         for (int e = rp[i]; e < rp[i + 1]; ++e) {
             const int j = ci[e];
             side[e] = j == i ? 0 : (rank[j] < rank[i] ? -1 : 1);
             if (side[e] < 0) low.emplace_back(rank[j], e);
             // the transposed entry (j, i), when stored
-            const auto b = ci.begin() + rp[j], en = ci.begin() + rp[j + 1];
-            const auto it = std::lower_bound(b, en, i);
-            if (it != en && *it == i) tpos[e] = static_cast<int>(it - ci.begin());
+            const int *b = ci.data() + rp[j], *en = ci.data() + rp[j + 1];
+            const int *it = std::lower_bound(b, en, i);
+            if (it != en && *it == i) tpos[e] = static_cast<int>(it - ci.data());
         }
-        std::sort(low.begin(), low.end());
+        if (t.ncolours > 0) std::sort(low.begin(), low.end());  // (ascending already if natural)
+        t.max_row = std::max(t.max_row, rp[i + 1] - rp[i]);
         nlow[i] = static_cast<int>(low.size());
         for (size_t u = 0; u < low.size(); ++u) lord[rp[i] + u] = low[u].second;
+        count[0][i] = nlow[i];
+        count[1][i] = rp[i + 1] - rp[i] - 1 - nlow[i];
     }
     t.sym_pattern = std::all_of(tpos.begin(), tpos.end(), [](int p) { return p >= 0; });
-    std::vector<int> pl, rl, pu, ru;
-    level_sets(n, rp, ci, order, rank, true, pl, rl);
-    level_sets(n, rp, ci, order, rank, false, pu, ru);
-    segments(pl, t.seg_l);
-    segments(pu, t.seg_u);
-    for (int i = 0; i < n; ++i) {
-        int lo = 0, up = 0;
-        for (int e = rp[i]; e < rp[i + 1]; ++e) {
-            lo += side[e] < 0 ? 1 : 0;
-            up += side[e] > 0 ? 1 : 0;
+    Slab slab;
+    std::vector<int> rows_of[2], col_of[2], src_of[2], fold;
+    slab.add(&t.side, side);
+    slab.add(&t.lord, lord);
+    slab.add(&t.nlow, nlow);
+    slab.add(&t.tpos, tpos);
+    for (int sd = 0; sd < 2; ++sd) {
+        TriSide &q = t.s[sd];
+        const int8_t want = sd == 0 ? -1 : 1;
+        std::vector<int> &rows = rows_of[sd], &col = col_of[sd], &src = src_of[sd];
+        level_sets(n, rp, ci, order, rank, sd == 0, q.lev, rows);
+        segments(q.lev, q.seg);
+        const int nlev = static_cast<int>(q.lev.size()) - 1;
+        q.merged = nlev >= 2 && q.seg[0].wide && q.seg[1].wide;
+        std::vector<int> level(q.merged ? n : 0);
+        if (q.merged)
+            for (int u = 0; u < q.lev[1]; ++u) level[rows[u]] = 1;  // marks level 0
+        q.width.assign(nlev, 0);
+        q.off.assign(nlev + 1, 0);
+        for (int l = 0; l < nlev; ++l) {
+            for (int u = q.lev[l]; u < q.lev[l + 1]; ++u)
+                q.width[l] = std::max(q.width[l], count[sd][rows[u]]);
+            const int cnt = q.lev[l + 1] - q.lev[l];
+            q.off[l + 1] = q.off[l] + static_cast<int64_t>(cnt) * q.width[l];
+            q.max_w = std::max(q.max_w, q.width[l]);
+            q.max_cnt = std::max(q.max_cnt, cnt);
         }
-        t.max_lo = std::max(t.max_lo, lo);
-        t.max_up = std::max(t.max_up, up);
-    }
-    for (size_t l = 0; l + 1 < pl.size(); ++l) t.max_w_l = std::max(t.max_w_l, pl[l + 1] - pl[l]);
-    for (size_t l = 0; l + 1 < pu.size(); ++l) t.max_w_u = std::max(t.max_w_u, pu[l + 1] - pu[l]);
-    t.h_lev_l = pl;
-    t.h_lev_u = pu;
-    if (!upload(t.rank, rank) || !upload(t.side, side) || !upload(t.lord, lord) ||
-        !upload(t.nlow, nlow) || !upload(t.tpos, tpos) || !upload(t.rows_l, rl) ||
-        !upload(t.rows_u, ru) || !upload(t.ptr_l, pl) || !upload(t.ptr_u, pu)) {
-        free_tri_order(t);
-        return MSRSB_E_NOMEM;
-    }
-    // natural order on a system small enough for x in LDS: the solves' rows
-    // packed by level position (one row per position of either triangle)
-    if (t.ncolours == 0 && n <= kNarrowLdsRows &&
-        hipMalloc(&t.packed, static_cast<size_t>(n) * sizeof(PackedRow)) != hipSuccess) {
-        free_tri_order(t);
-        return MSRSB_E_NOMEM;
+        col.resize(q.off[nlev]);
+        src.assign(q.off[nlev], -1);
+        for (int l = 0; l < nlev; ++l) {
+            const int cnt = q.lev[l + 1] - q.lev[l];
+            const bool marks = q.merged && l == 1;
+            for (int u = 0; u < cnt; ++u) {
+                const int i = rows[q.lev[l] + u];
+                int64_t at = q.off[l] + u;
+                for (int e = rp[i]; e < rp[i + 1]; ++e) {
+                    if (side[e] != want) continue;
+                    col[at] = marks && level[ci[e]] ? ci[e] | kTriFirst : ci[e];
+                    src[at] = e;
+                    at += cnt;
+                }
+                for (int k = count[sd][i]; k < q.width[l]; ++k, at += cnt) col[at] = i | kTriFirst;
+            }
+        }
+        if (sd == 0) {
+            fold.assign(n, -1);
+            for (int u = 0; u < n; ++u) {
+                const int i = rows[u];
+                if (count[1][i] > 0) continue;
+                for (int e = rp[i]; e < rp[i + 1]; ++e)
+                    if (side[e] == 0) fold[u] = e;
+            }
+            slab.add(&q.fold, fold);
+        }
+        slab.add(&q.d_lev, q.lev);
+        slab.add(&q.d_width, q.width);
+        slab.add(&q.d_off, q.off);
+        slab.add(&q.row, rows);
+        slab.add(&q.col, col);
+        slab.add(&q.src, src);
     }
     t.rp = c->rp;
     t.ci = c->ci;
     t.dpos = c->diag_pos;
+    // one wavefront walks both triangles of a small system in the natural order
+    t.wave = t.ncolours == 0 && n <= kNarrowLdsRows &&
+             std::max(t.s[0].max_w, t.s[1].max_w) <= kTriWaveW &&
+             std::max(t.s[0].max_cnt, t.s[1].max_cnt) <= 128;
+    if (!slab.upload(&t.slab) || !alloc_values(t, t.v[TRI_GS])) {
+        free_tri_order(t);
+        return MSRSB_E_NOMEM;
+    }
     t.built = true;
     return MSRSB_OK;
 }
@@ -598,66 +972,49 @@ msrsb_status tri_factor(msrsb_ctx *c, int ordering, int kind)
 {
     hipStream_t s = c->stream;
     TriOrder &t = c->tri[ordering];
-    double *&f = kind == MSRSB_SMOOTH_ILU0 ? c->ilu_f[ordering] : c->ic_f[ordering];
+    const int k = kind == MSRSB_SMOOTH_ILU0 ? TRI_ILU : TRI_IC;
+    double *&f = k == TRI_ILU ? c->ilu_f[ordering] : c->ic_f[ordering];
     if (!f && hipMalloc(&f, c->nnz * sizeof(double)) != hipSuccess) return MSRSB_E_NOMEM;
+    if (!alloc_values(t, t.v[k])) return MSRSB_E_NOMEM;
     int *flag = c->dev_flag;
     hipMemsetAsync(flag, 0, sizeof(int), s);
     RowOp r;
     r.f = f;
     r.flag = flag;
     const int nb = static_cast<int>((c->nnz + 255) / 256);
-    if (kind == MSRSB_SMOOTH_ILU0) {
+    if (k == TRI_ILU) {
+        if (!ilu_maps(s, t)) return MSRSB_E_NOMEM;
         k_copy_vals<<<nb, 256, 0, s>>>(c->nnz, c->a, f);
         r.op = OP_ILU;
-        run_levels(s, t, true, r);
+        run_factor(s, t, r);
     } else {
         r.op = OP_IC;
         r.a = c->a;
-        run_levels(s, t, true, r);
+        run_factor(s, t, r);
         k_ic_mirror<<<nb, 256, 0, s>>>(c->nnz, t.side, t.tpos, f);
     }
+    pack_values(s, t, k, f);
     int hflag = 0;
     hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, s);
     if (hipStreamSynchronize(s) != hipSuccess) return MSRSB_E_HIP;
     return hflag ? MSRSB_E_BREAKDOWN : MSRSB_OK;
 }
 
-// z += M^{-1} res for ILU(0) / IC(0) (res is overwritten); one half of a
-// Gauss-Seidel sweep: (D + L)^{-1} (lower) or (D + U)^{-1} (upper) with A's
-// own values
-void tri_apply(msrsb_ctx *c, int ordering, int kind, double *res, double *z)
+void tri_apply(msrsb_ctx *c, int ordering, int kind, const double *res, double *z, bool set,
+               double *x)
 {
-    hipStream_t s = c->stream;
-    const TriOrder &t = c->tri[ordering];
-    RowOp r;
-    r.x = res;
-    if (kind == MSRSB_SMOOTH_ILU0) {
-        r.f = c->ilu_f[ordering];
-        r.op = OP_LOWER;
-        r.unit = true;
-        run_levels(s, t, true, r);
-        r.op = OP_UPPER;
-        r.unit = false;
-        run_levels(s, t, false, r);
-    } else if (kind == MSRSB_SMOOTH_IC0) {
-        r.f = c->ic_f[ordering];
-        r.op = OP_LOWER;
-        run_levels(s, t, true, r);
-        r.op = OP_UPPER;
-        run_levels(s, t, false, r);
-    }
-    k_add<<<(c->n + 255) / 256, 256, 0, s>>>(c->n, res, z);
+    run_solve(c->stream, c->tri[ordering], kind == MSRSB_SMOOTH_ILU0 ? TRI_ILU : TRI_IC, 0, 1, res,
+              z, set, x);
 }
 
-void tri_gs_half(msrsb_ctx *c, int ordering, bool lower, double *res, double *z)
+// A's values are packed by the first half sweep after they change
+void tri_gs_half(msrsb_ctx *c, int ordering, bool lower, const double *res, double *z, bool set,
+                 double *x)
 {
-    hipStream_t s = c->stream;
-    RowOp r;
-    r.x = res;
-    r.f = c->a;
-    r.op = lower ? OP_LOWER : OP_UPPER;
-    run_levels(s, c->tri[ordering], lower, r);
-    k_add<<<(c->n + 255) / 256, 256, 0, s>>>(c->n, res, z);
+    TriOrder &t = c->tri[ordering];
+    if (!t.v[TRI_GS].ok) pack_values(c->stream, t, TRI_GS, c->a);
+    const int side = lower ? 0 : 1;
+    run_solve(c->stream, t, TRI_GS, side, side, res, z, set, x);
 }
 
 }  // namespace msrsb

@@ -223,18 +223,17 @@ void sweep(msrsb_ctx *c, const Op &o, int kind, bool fp32, const double *v, doub
         // residual, then the triangular solves in the order; SGS is a forward
         // sweep (D + L)^{-1} and a backward one (D + U)^{-1}, each on the
         // residual of the current iterate
-        if (zero) {
-            launch_copy(s, n, v, tmp);
-            launch_fill(s, n, *z, 0.0);
-        } else {
+        const double *res = v;
+        if (!zero) {
             op_residual(s, n, o, v, *z, tmp);
+            res = tmp;
         }
         if (kind == MSRSB_SMOOTH_SGS) {
-            tri_gs_half(c, ord, true, tmp, *z);
+            tri_gs_half(c, ord, true, res, *z, zero, *spare);
             op_residual(s, n, o, v, *z, tmp);
-            tri_gs_half(c, ord, false, tmp, *z);
+            tri_gs_half(c, ord, false, tmp, *z, false, *spare);
         } else {
-            tri_apply(c, ord, kind, tmp, *z);
+            tri_apply(c, ord, kind, res, *z, zero, *spare);
         }
     }
 }
