@@ -7,6 +7,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "internal.h"
 #include "solve.h"
@@ -14,61 +15,244 @@
 namespace msrsb {
 namespace {
 
-// --- GMRES small dense algebra (single thread; m <= 64) ---
+// --- GMRES orthogonalisation (classical Gram-Schmidt applied twice) ---
+//
+// For the first kOrthoCols columns of a cycle the whole step after w = A B v
+// is four launches (15 to 30 us a step on 65,536 rows from the first to the
+// 30th column, bound by the latency of the partial sums and by the vectors'
+// passes through the L2; a launch per product, sum, update and scalar took
+// eleven, 28 to 40 us):
+//   dots     part = V^T w by work-group
+//   update   h = the sum of part; w -= V h; part = V^T w again
+//   norm     h2 = the sum of part; w -= V h2; ||w||^2 by work-group
+//   finish   v_next = w / ||w||; one wavefront: the Hessenberg column h + h2,
+//            its Givens rotations and the residual posted to the host
+// A work-group holds kOrthoThreads rows per pass and at most kOrthoBlocks
+// work-groups share the rows, so that every consumer can add the producers'
+// partial sums by itself (at most 256 per column, read from the L2) instead
+// of waiting for a launch that does; sums in a fixed order (reproducible).
+constexpr int kOrthoCols = 32;
+constexpr int kOrthoThreads = 512;
+constexpr int kOrthoBlocks = 256;
+constexpr int kOrthoWaves = kOrthoThreads / 64;
+
+// v[q] summed over the wavefront for q < K (K a power of two up to 32): lane
+// pairs exchange halves of the values, so that lane l ends with the total of
+// value l / (64 / K) in v[0]
+template <int K, int M = K / 2, int OFF = 32>
+__device__ __forceinline__ void wave_sums(double (&v)[K])
+{
+    if constexpr (M >= 1) {
+        const bool hi = (threadIdx.x & OFF) != 0;
+#pragma unroll
+        for (int q = 0; q < M; ++q) {
+            const double keep = hi ? v[q + M] : v[q], send = hi ? v[q] : v[q + M];
+            v[q] = keep + __shfl_xor(send, OFF, 64);
+        }
+        wave_sums<K, M / 2, OFF / 2>(v);
+    } else if constexpr (OFF >= 1) {
+        v[0] += __shfl_xor(v[0], OFF, 64);
+        wave_sums<K, 0, OFF / 2>(v);
+    }
+}
+
+// part[t * gridDim.x + b] = the work-group's sum of acc[t], t < k
+template <int K>
+__device__ __forceinline__ void store_sums(double (&acc)[K], int k, double *__restrict__ part)
+{
+    __shared__ double sh[kOrthoWaves][K];
+    wave_sums<K>(acc);
+    constexpr int G = 64 / K;  // lanes per value
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (lane % G == 0) sh[w][lane / G] = acc[0];
+    __syncthreads();
+    if (static_cast<int>(threadIdx.x) < k) {
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < kOrthoWaves; ++q) s += sh[q][threadIdx.x];
+        part[static_cast<int64_t>(threadIdx.x) * gridDim.x + blockIdx.x] = s;
+    }
+}
+
+// h[t] = sum over the nb work-groups of part[t * nb + b] for t < k, 0 for the
+// other t < K, in LDS
+template <int K>
+__device__ __forceinline__ void load_sums(int k, int nb, const double *__restrict__ part,
+                                          double *__restrict__ h)
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    constexpr int T = (K + kOrthoWaves - 1) / kOrthoWaves;
+    double v[T];
+#pragma unroll
+    for (int q = 0; q < T; ++q) {
+        const int t = w + q * kOrthoWaves;
+        v[q] = 0.0;
+        if (t < k)
+#pragma unroll
+            for (int b = 0; b < kOrthoBlocks / 64; ++b)
+                if (lane + 64 * b < nb) v[q] += part[static_cast<int64_t>(t) * nb + lane + 64 * b];
+    }
+#pragma unroll
+    for (int q = 0; q < T; ++q) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v[q] += __shfl_xor(v[q], off, 64);
+        const int t = w + q * kOrthoWaves;
+        if (lane == 0 && t < K) h[t] = v[q];
+    }
+    __syncthreads();
+}
+
+// UPDATE: first w -= V h with h summed from pin (work-group 0 writes it to
+// hout, added to what is there with ADD).  DOTS: pout = V^T w, else ||w||^2.
+template <int K, bool UPDATE, bool ADD, bool DOTS>
+__global__ __launch_bounds__(kOrthoThreads) void k_ortho(int n, int k, int nbin, int64_t ldv,
+                                                         const double *__restrict__ V,
+                                                         double *__restrict__ w,
+                                                         const double *__restrict__ pin,
+                                                         double *__restrict__ hout,
+                                                         double *__restrict__ pout)
+{
+    __shared__ double h[K];
+    int i = blockIdx.x * kOrthoThreads + threadIdx.x;
+    double v[K], x;
+    // (columns past k repeat the last one: no branches between the loads)
+    auto load = [&](int r) {
+#pragma unroll
+        for (int t = 0; t < K; ++t) v[t] = V[min(t, k - 1) * ldv + r];
+        x = w[r];
+    };
+    // without products the registers hold the first rows while the sums are
+    // formed (9.2 -> 7.9 us at 32 columns; with them, they spill: 16 us)
+    constexpr bool AHEAD = UPDATE && !DOTS;
+    if constexpr (AHEAD) load(min(i, n - 1));
+    if constexpr (UPDATE) {
+        load_sums<K>(k, nbin, pin, h);
+        if (blockIdx.x == 0 && static_cast<int>(threadIdx.x) < k)
+            hout[threadIdx.x] = ADD ? hout[threadIdx.x] + h[threadIdx.x] : h[threadIdx.x];
+    }
+    constexpr int A = DOTS ? K : 1;
+    double acc[A];
+#pragma unroll
+    for (int t = 0; t < A; ++t) acc[t] = 0.0;
+    for (bool first = true; i < n; i += gridDim.x * kOrthoThreads, first = false) {
+        if (!AHEAD || !first) load(i);
+        if constexpr (UPDATE) {
+            double s = 0.0;
+#pragma unroll
+            for (int t = 0; t < K; ++t) s += h[t] * v[t];
+            x -= s;
+            w[i] = x;
+        }
+        if constexpr (DOTS) {
+#pragma unroll
+            for (int t = 0; t < K; ++t) acc[t] += v[t] * x;
+        } else {
+            acc[0] += x * x;
+        }
+    }
+    store_sums<A>(acc, DOTS ? k : 1, pout);
+}
+
 // Apply the previous Givens rotations to the new Hessenberg column (h[0..j]
-// from the Gram-Schmidt, ||w||^2 in nrm2), form the new rotation, update g
-// and write |g[j+1]| and the rotated diagonal to res.
+// from the Gram-Schmidt, the norm below), form the new rotation, update g and
+// write |g[j+1]| and the rotated diagonal to res.  One wavefront; lane i holds
+// entry i of the column (j < 64) and of the rotations, which thread by thread
+// follow each other through lane reads instead of memory.
 // With host_out (coherent pinned memory) the residual estimate and the
 // denominator also go to the host mailbox: the values, a system-scope fence,
 // then the step's tag the host waits for.
-__global__ void k_gmres_givens(int j, int m, double *__restrict__ H, const double *__restrict__ h,
-                               const double *__restrict__ nrm2, double *__restrict__ cs,
-                               double *__restrict__ sn, double *__restrict__ g,
-                               double *__restrict__ res, double *__restrict__ host_out,
-                               double tag)
+__device__ void gmres_givens(int j, int m, double *__restrict__ H, const double *__restrict__ h,
+                             double norm, double *__restrict__ cs, double *__restrict__ sn,
+                             double *__restrict__ g, double *__restrict__ res,
+                             double *__restrict__ host_out, double tag)
 {
-    if (threadIdx.x != 0) return;
-    double col[65];
-    for (int i = 0; i <= j; ++i) col[i] = h[i];
-    col[j + 1] = sqrt(nrm2[0]);
+    const int lane = threadIdx.x & 63;
+    const double hl = lane <= j ? h[lane] : 0.0;
+    const double cl = lane < j ? cs[lane] : 0.0, sl = lane < j ? sn[lane] : 0.0;
+    const double gj = g[j];
+    double a = __shfl(hl, 0, 64), mine = 0.0;  // a: the running entry i
     for (int i = 0; i < j; ++i) {
-        const double a = col[i], b = col[i + 1];
-        col[i] = cs[i] * a + sn[i] * b;
-        col[i + 1] = -sn[i] * a + cs[i] * b;
+        const double b = __shfl(hl, i + 1, 64), c = __shfl(cl, i, 64), s = __shfl(sl, i, 64);
+        const double top = c * a + s * b;
+        a = -s * a + c * b;
+        if (lane == i) mine = top;
     }
-    const double a = col[j], b = col[j + 1];
-    const double den = sqrt(a * a + b * b);
+    const double den = sqrt(a * a + norm * norm);
     double c = 1.0, s = 0.0;
     if (den > 0.0) {
         c = a / den;
-        s = b / den;
+        s = norm / den;
     }
+    if (lane == j) mine = den;
+    if (lane <= j) H[static_cast<int64_t>(lane) * m + j] = mine;
+    if (lane != 0) return;
     cs[j] = c;
     sn[j] = s;
-    col[j] = den;
-    col[j + 1] = 0.0;
-    for (int i = 0; i <= j; ++i) H[static_cast<int64_t>(i) * m + j] = col[i];
-    g[j + 1] = -s * g[j];
-    g[j] = c * g[j];
-    res[0] = fabs(g[j + 1]);
+    const double gn = -s * gj;
+    g[j + 1] = gn;
+    g[j] = c * gj;
+    res[0] = fabs(gn);
     res[1] = den;
     if (host_out == nullptr) return;
-    host_out[0] = res[0];
+    host_out[0] = fabs(gn);
     host_out[1] = den;
     __threadfence_system();
     host_out[2] = tag;
 }
 
-// y = H(0:k,0:k)^{-1} g(0:k) (upper triangular back substitution)
-__global__ void k_gmres_solve(int k, int m, const double *__restrict__ H,
-                              const double *__restrict__ g, double *__restrict__ y)
+struct GivensArgs {
+    int j, m;
+    double *H;
+    const double *h;
+    double *cs, *sn, *g, *res, *host_out;
+    double tag;
+};
+
+// (columns past kOrthoCols: the norm comes from launch_norm_scale)
+__global__ __launch_bounds__(64) void k_gmres_givens(GivensArgs a, const double *__restrict__ nrm2)
 {
-    if (threadIdx.x != 0) return;
-    for (int r = k - 1; r >= 0; --r) {
-        double s = g[r];
-        for (int c = r + 1; c < k; ++c) s -= H[static_cast<int64_t>(r) * m + c] * y[c];
-        y[r] = s / H[static_cast<int64_t>(r) * m + r];
+    gmres_givens(a.j, a.m, a.H, a.h, sqrt(nrm2[0]), a.cs, a.sn, a.g, a.res, a.host_out, a.tag);
+}
+
+// v = w / ||w|| (0 when the norm is 0), with ||w||^2 summed from nb partials;
+// the last work-group has no rows: its first wavefront does the Givens step
+__global__ __launch_bounds__(kOrthoThreads) void k_ortho_finish(int n, int nb,
+                                                                const double *__restrict__ part,
+                                                                const double *__restrict__ w,
+                                                                double *__restrict__ v,
+                                                                GivensArgs a)
+{
+    __shared__ double h[1];
+    load_sums<1>(1, nb, part, h);
+    const double nr = sqrt(h[0]);
+    const int rows = gridDim.x - 1;
+    if (static_cast<int>(blockIdx.x) == rows) {
+        if (threadIdx.x < 64)
+            gmres_givens(a.j, a.m, a.H, a.h, nr, a.cs, a.sn, a.g, a.res, a.host_out, a.tag);
+        return;
     }
+    for (int i = blockIdx.x * kOrthoThreads + threadIdx.x; i < n; i += rows * kOrthoThreads)
+        v[i] = nr > 0.0 ? w[i] / nr : 0.0;
+}
+
+// y = H(0:k,0:k)^{-1} g(0:k) (upper triangular back substitution): lane i
+// holds g_i and reads its row of H ahead of the column that needs it
+__global__ __launch_bounds__(64) void k_gmres_solve(int k, int m, const double *__restrict__ H,
+                                                    const double *__restrict__ g,
+                                                    double *__restrict__ y)
+{
+    __shared__ double U[64][65];
+    const int lane = threadIdx.x;
+    for (int r = 0; r < k; ++r)
+        if (lane < k) U[r][lane] = H[static_cast<int64_t>(r) * m + lane];
+    __syncthreads();
+    double s = lane < k ? g[lane] : 0.0;
+    for (int r = k - 1; r >= 0; --r) {
+        const double yr = __shfl(s, r, 64) / U[r][r];
+        if (lane < r) s -= U[lane][r] * yr;
+        if (lane == r) s = yr;
+    }
+    if (lane < k) y[lane] = s;
 }
 
 __global__ void k_gmres_init_g(int m, double *__restrict__ g, const double *__restrict__ nrm2)
@@ -82,6 +266,28 @@ __global__ void k_vec_add(int k, double *__restrict__ a, const double *__restric
 {
     const int t = threadIdx.x;
     if (t < k) a[t] += b[t];
+}
+
+// the orthogonalisation of one step with k <= kOrthoCols columns
+void ortho(hipStream_t s, int n, int k, int64_t ldv, const double *V, double *w, double *vnext, double *h,
+           double *const part[2], const GivensArgs &g)
+{
+    const int nb = std::min(kOrthoBlocks, (n + kOrthoThreads - 1) / kOrthoThreads);
+    auto go = [&](auto kk) {
+        constexpr int K = decltype(kk)::value;
+        k_ortho<K, false, false, true>
+            <<<nb, kOrthoThreads, 0, s>>>(n, k, nb, ldv, V, w, nullptr, nullptr, part[0]);
+        k_ortho<K, true, false, true>
+            <<<nb, kOrthoThreads, 0, s>>>(n, k, nb, ldv, V, w, part[0], h, part[1]);
+        k_ortho<K, true, true, false>
+            <<<nb, kOrthoThreads, 0, s>>>(n, k, nb, ldv, V, w, part[1], h, part[0]);
+    };
+    using std::integral_constant;
+    if (k <= 4) go(integral_constant<int, 4>{});
+    else if (k <= 8) go(integral_constant<int, 8>{});
+    else if (k <= 16) go(integral_constant<int, 16>{});
+    else go(integral_constant<int, kOrthoCols>{});
+    k_ortho_finish<<<nb + 1, kOrthoThreads, 0, s>>>(n, nb, part[0], w, vnext, g);
 }
 
 // out = a x + b y + c w (w may be null); out may alias x, y or w
@@ -444,6 +650,13 @@ void apply_two_stage(msrsb_ctx *c, const msrsb_solve_opts *o, const double *v, d
     if (pre_k == MSRSB_SMOOTH_NONE) pre_n = 0;
     if (post_k == MSRSB_SMOOTH_NONE) post_n = 0;
     double *z = b.z, *spare = b.spare, *tmp = b.tmp;
+    // the sweeps that exchange z and spare are known beforehand, so the last
+    // one can write zout itself (unless v, read until then, lies there)
+    if (zout + n <= v || v + n <= zout) {
+        int swaps = is_diag(post_k) ? post_n : 0;
+        if (is_diag(pre_k)) swaps += pre_n - (pre_n >= 2 && op.d.n > 0 ? 2 : 0);
+        (swaps & 1 ? spare : z) = zout;
+    }
     // precision form inside PCG with two Jacobi-type sweeps on each side of a
     // stencil operator: FP32 intermediate vectors (launch_prec_f32_*)
     const bool f32_path = fp32 && dots && o->use_multiscale && op.d.n > 0 && c->pcol16 &&
@@ -506,7 +719,7 @@ void apply_two_stage(msrsb_ctx *c, const msrsb_solve_opts *o, const double *v, d
     }
     if (zero)
         launch_fill(s, n, zout, 0.0);
-    else
+    else if (z != zout)
         launch_copy(s, n, z, zout);
     if (dots)
         launch_dots_beta(s, n, v, zout, dots->zold, dots->part, dots->scal, dots->part_rr,
@@ -648,12 +861,18 @@ msrsb_status gmres(msrsb_ctx *c, const double *f, double *x, const msrsb_solve_o
     const int n = c->n;
     const int m = std::max(1, std::min(o->restart, 64));
     const Op op = fine_op(c, trans);
+    // the basis vectors' stride: whole 256-byte blocks, an odd number of them,
+    // so that the same rows of all vectors spread over the memory channels and
+    // cache sets (at 65,536 rows a stride of 512 KB put them all in one set:
+    // 18 us per pass over 31 vectors)
+    const int64_t ldv = ((n + 31) / 32 | 1) * static_cast<int64_t>(32);
     if (c->gm_cap < m) {
         if (c->gm_v) hipFree(c->gm_v);
         if (c->gm_h) hipFree(c->gm_h);
         c->gm_v = c->gm_h = nullptr;
-        if (dev_alloc(&c->gm_v, static_cast<size_t>(m + 1) * n) ||
-            dev_alloc(&c->gm_h, static_cast<size_t>(m + 1) * m + 8 * (m + 2)))
+        if (dev_alloc(&c->gm_v, static_cast<size_t>(m + 1) * ldv) ||
+            dev_alloc(&c->gm_h, static_cast<size_t>(m + 1) * m + 8 * (m + 2) +
+                                    2 * kOrthoCols * kOrthoBlocks))
             return MSRSB_E_NOMEM;
         c->gm_cap = m;
     }
@@ -661,6 +880,8 @@ msrsb_status gmres(msrsb_ctx *c, const double *f, double *x, const msrsb_solve_o
     double *H = c->gm_h;                        // (m+1) x m
     double *cs = H + (m + 1) * m, *sn = cs + (m + 2), *g = sn + (m + 2), *y = g + (m + 2);
     double *hc = y + (m + 2), *h2 = hc + (m + 2), *gsc = h2 + (m + 2);  // gsc: 2 scalars
+    // partial sums of the orthogonalisation: two arrays in turn
+    double *part[2] = {gsc + (m + 2), gsc + (m + 2) + kOrthoCols * kOrthoBlocks};
     double *w = c->w[0], *zt = c->w[1], *r = c->w[2];
     double *sc = c->scal;
     // two mailbox slots in coherent pinned memory (steps alternate)
@@ -688,19 +909,24 @@ msrsb_status gmres(msrsb_ctx *c, const double *f, double *x, const msrsb_solve_o
         // one Arnoldi step: v_{j+1} and column j of H, its Givens rotation,
         // and the residual estimate posted to mailbox slot j mod 2 with tag
         auto step = [&](int jj, int tag) {
-            const double *vj = V + static_cast<int64_t>(jj) * n;
-            double *vn = V + static_cast<int64_t>(jj + 1) * n;
+            const double *vj = V + jj * ldv;
+            double *vn = V + (jj + 1) * ldv;
             apply_two_stage(c, o, vj, zt, trans, nullptr);
             op_spmv(s, n, op, zt, w);
             // CGS2: h = V^T w; w -= V h; h2 = V^T w; w -= V h2; h += h2
-            launch_multi_dot(s, n, jj + 1, V, n, w, c->partials, hc);
-            launch_multi_axpy(s, n, jj + 1, V, n, hc, w, -1.0);
-            launch_multi_dot(s, n, jj + 1, V, n, w, c->partials, h2);
-            launch_multi_axpy(s, n, jj + 1, V, n, h2, w, -1.0);
+            const GivensArgs ga{jj, m, H, hc, cs, sn, g, gsc, const_cast<double *>(mbox[jj & 1]),
+                                static_cast<double>(tag)};
+            if (jj < kOrthoCols) {
+                ortho(s, n, jj + 1, ldv, V, w, vn, hc, part, ga);
+                return;
+            }
+            launch_multi_dot(s, n, jj + 1, V, ldv, w, c->partials, hc);
+            launch_multi_axpy(s, n, jj + 1, V, ldv, hc, w, -1.0);
+            launch_multi_dot(s, n, jj + 1, V, ldv, w, c->partials, h2);
+            launch_multi_axpy(s, n, jj + 1, V, ldv, h2, w, -1.0);
             k_vec_add<<<1, 64, 0, s>>>(jj + 1, hc, h2);
             launch_norm_scale(s, n, w, vn, c->partials, sc + S_TMP1);
-            k_gmres_givens<<<1, 64, 0, s>>>(jj, m, H, hc, sc + S_TMP1, cs, sn, g, gsc,
-                                            const_cast<double *>(mbox[jj & 1]), tag);
+            k_gmres_givens<<<1, 64, 0, s>>>(ga, sc + S_TMP1);
         };
         int j = 0;
         bool brk = false;
@@ -724,7 +950,7 @@ msrsb_status gmres(msrsb_ctx *c, const double *f, double *x, const msrsb_solve_o
         if (j > 0) {
             k_gmres_solve<<<1, 64, 0, s>>>(j, m, H, g, y);
             launch_fill(s, n, w, 0.0);
-            launch_multi_axpy(s, n, j, V, n, y, w, 1.0);
+            launch_multi_axpy(s, n, j, V, ldv, y, w, 1.0);
             apply_two_stage(c, o, w, zt, trans, nullptr);
             launch_axpy(s, n, 1.0, zt, x);
         }
