@@ -34,17 +34,16 @@ struct DiaOffsets {
 enum Scalar {
     S_RR = 0,      // r.r
     S_PQ,          // p.A p
-    S_RZ,          // r.z (current)
-    S_RZ_OLD,      // r.z of the previous iteration
-    S_RZDIFF,      // r.(z - z_old)
     S_ALPHA,
     S_BETA,
     S_FF,          // f.f
-    S_BREAK,       // breakdown flag (non-zero = breakdown)
+    S_BREAK,       // step whose alpha broke down (0: none)
+    S_BREAK_BETA,  // step whose beta broke down (0: none)
     S_TMP0,
     S_TMP1,
     S_TMP2,
     S_TMP3,
+    S_RZ_SLOT,     // r.z of the even and of the odd PCG steps (two entries)
     S_COUNT = 32   // allocation size of the scalar array
 };
 
@@ -531,12 +530,13 @@ struct ProlongAxes {
     const int4 *wtab = nullptr;
     int64_t n8 = 0;
 };
+struct PostArgs;
 // xc = R x; columns from the boxes when given, else from rci, or (roff16
 // non-null) rbase[e / 64] + roff16[e]
 void launch_restrict(hipStream_t s, int nc, const int *rrp, const int *rci,
                      const uint16_t *roff16, const int *rbase, bool fp32, const double *r64,
-                     const float *r32, const double *x, double *xc,
-                     const RestrictBoxes &boxes = RestrictBoxes{});
+                     const float *r32, const double *x, double *xc, const RestrictBoxes &boxes,
+                     const PostArgs &post);
 void launch_dot(hipStream_t s, int n, const double *x, const double *y, double *partials,
                 double *out);
 void launch_copy(hipStream_t s, int n, const double *x, double *y);
@@ -550,6 +550,7 @@ void launch_diag_inverses(hipStream_t s, int n, const int *rp, const int *ci, co
 void launch_gather_values(hipStream_t s, int64_t m, const int *src, const double *a, double *out);
 
 // ---- node-block stencil kernels (k_krylov.hip) ----
+struct PcgSums;
 void launch_csr_to_nbs(hipStream_t s, int n, const NodeStencil &ns, const int *rp,
                        const int8_t *slot, const double *a, double *v);
 void launch_nbs_spmv(hipStream_t s, int n, const NodeStencil &ns, const double *v, const double *x,
@@ -560,9 +561,30 @@ void launch_nbs_residual(hipStream_t s, int n, const NodeStencil &ns, const doub
 void launch_nbs_sweep(hipStream_t s, int n, const NodeStencil &ns, bool fp32, const double *v,
                       const float *v32, const double *dinv, const float *dinv32,
                       const double *vin, const double *zin, double *zout, bool zero_start);
-void launch_nbs_pcg_p_spmv(hipStream_t s, int n, const NodeStencil &ns, const double *v,
-                           const double *z, const double *pold, double *pnew, double *q,
-                           double *part, double *scal);
+int launch_nbs_pcg_p_spmv(hipStream_t s, int n, const NodeStencil &ns, const double *v,
+                          const double *z, const double *pold, double *pnew, double *q,
+                          double *part, const PcgSums &sums);
+
+// ---- host mailbox of the Krylov drivers ----
+// Three values in coherent pinned memory and a word formed from all three, so
+// that the host knows when it has seen all of one post and the device needs
+// no system-scope fence between them (which writes back an XCD's L2).
+__host__ __device__ inline unsigned long long mail_word(double a, double b, double c)
+{
+    unsigned long long x[3];
+    const double v[3] = {a, b, c};
+    __builtin_memcpy(x, v, sizeof x);
+    return (x[0] ^ (x[1] << 21 | x[1] >> 43)) + 0x9E3779B97F4A7C15ull * (x[2] + 1);
+}
+__device__ inline void post_mail(double *__restrict__ box, double a, double b, double tag)
+{
+    const unsigned long long w = mail_word(a, b, tag);
+    __hip_atomic_store(box, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(box + 1, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(box + 2, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(reinterpret_cast<unsigned long long *>(box + 3), w, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // ---- DIA / fused PCG kernels (k_krylov.hip) ----
 void launch_dia_spmv(hipStream_t s, int n, const DiaOffsets &d, const double *a, const double *x,
@@ -580,39 +602,83 @@ struct UpdArgs {
     const double *p = nullptr, *q = nullptr;
     double *rout = nullptr;
     double *part = nullptr;
-    const double *scal = nullptr;
+    double *scal = nullptr;
+    // npq > 0: every work-group forms alpha itself, from the npq partials pq
+    // of p.q and the r.z in scal[rz] (see step_alpha)
+    const double *pq = nullptr;
+    int npq = 0, rz = 0;
+    double tag = 0.0;  // the step's number
 };
+// r.r of a step's residual update (nrr partials rr) and the breakdowns so far,
+// posted to the host's mailbox by a kernel between the update and the next
+// direction, so that the host queues the next step while this one runs.
+// host_out null: no post.
+struct PostArgs {
+    const double *rr = nullptr;
+    int nrr = 0;
+    const double *scal = nullptr;
+    double *host_out = nullptr;
+    double tag = 0.0;
+};
+// Where the next search direction's beta comes from: scal[S_BETA], or with
+// ndots > 0 the partials of r.z and r.(z - z_old) (dots[0 .. 2 ndots)), which
+// every work-group adds itself (see step_beta).
+struct PcgSums {
+    double *scal = nullptr;
+    int rz_old = 0, rz_new = 0;  // scal's places of the last and of this r.z
+    const double *dots = nullptr;
+    int ndots = 0;
+    double tag = 0.0;            // the step's number
+};
+// Most partials that the consumers of a PCG scalar add themselves (131,072
+// rows at one per kBlock rows).  Up to there the sum costs each work-group two
+// loads per lane and a reduction, about 1 us of a kernel, and saves a launch
+// of 4 us; the traffic grows with the square of the rows, and past it the
+// one-block sums (k_fin_alpha, k_fin_beta) are the cheaper way.
+constexpr int kSumBlocks = 512;
+// the p.q partials' place in the partial array of n rows (behind the dots')
+inline size_t pq_offset(size_t n) { return n / 64 + 16; }
 void launch_dia_sweep(hipStream_t s, int n, const DiaOffsets &d, bool fp32, const double *a64,
                       const float *a32, const double *dinv64, const float *dinv32,
                       const double *v, const double *zin, double *zout, bool zero2,
                       const UpdArgs *upd = nullptr);
-void launch_dia_sweep_dots(hipStream_t s, int n, const DiaOffsets &d, bool fp32,
-                           const double *a64, const float *a32, const double *dinv64,
-                           const float *dinv32, const double *r, const double *zin, double *zout,
-                           const double *zold, double *part, double *scal,
-                           const double *part_rr, double *host_out, int tag);
-// beta and, with host_out, the step's r.r mailbox (see k_fin_beta)
-void launch_dots_beta(hipStream_t s, int n, const double *r, const double *z, const double *zold,
-                      double *part, double *scal, const double *part_rr, double *host_out,
-                      int tag);
-void launch_pcg_p_spmv(hipStream_t s, int n, const DiaOffsets &d, const double *ad,
-                       const int *rp, const int *ci, const double *a, const double *z,
-                       const double *pold, double *pnew, double *q, double *part, double *scal);
-// x += alpha p, r -= alpha q; the r.r partials (one per block) go to
-// part_rr and are summed by the step's k_fin_beta
-void launch_pcg_update(hipStream_t s, int n, const UpdArgs &u);
+// the last sweep with the partials of r.z and r.(z - zold); these return the
+// number of partials per product
+int launch_dia_sweep_dots(hipStream_t s, int n, const DiaOffsets &d, bool fp32,
+                          const double *a64, const float *a32, const double *dinv64,
+                          const float *dinv32, const double *r, const double *zin, double *zout,
+                          const double *zold, double *part);
+int launch_nbs_sweep_dots(hipStream_t s, int n, const NodeStencil &ns, bool fp32, const double *v,
+                          const float *v32, const double *dinv, const float *dinv32,
+                          const double *r, const double *zin, double *zout, const double *zold,
+                          double *part);
+int launch_dots(hipStream_t s, int n, const double *r, const double *z, const double *zold,
+                double *part);
+// beta from the partials, then the post
+void launch_fin_beta(hipStream_t s, const PcgSums &p, const PostArgs &post);
+void launch_post(hipStream_t s, const PostArgs &post);
+// p = z + beta pold, q = A p and the p.q partials; returns their number
+int launch_pcg_p_spmv(hipStream_t s, int n, const DiaOffsets &d, const double *ad,
+                      const int *rp, const int *ci, const double *a, const double *z,
+                      const double *pold, double *pnew, double *q, double *part,
+                      const PcgSums &sums);
+// alpha = scal[rz] / p.q from nb partials
+void launch_fin_alpha(hipStream_t s, int nb, const double *part, double *scal, int rz,
+                      double tag);
+// x += alpha p, r -= alpha q; the r.r partials (one per block) go to u.part.
+// With z the first Jacobi-type sweep from zero as well: z = dinv r.
+void launch_pcg_update(hipStream_t s, int n, const UpdArgs &u, double *z = nullptr,
+                       const double *dinv = nullptr, const float *dinv32 = nullptr);
 void launch_prec_f32_pre(hipStream_t s, int n, const DiaOffsets &d, const float *a32,
                          const float *dinv32, const double *v, float *z1, float *tmp, int nc,
                          const int *rrp, const int *rci, const uint16_t *roff16,
                          const int *rbase, const float *r32, double *vc,
-                         const RestrictBoxes &boxes = RestrictBoxes{},
-                         const UpdArgs *upd = nullptr);
-void launch_prec_f32_post(hipStream_t s, int n, const DiaOffsets &d, const float *a32,
-                          const float *dinv32, const double *v, float *z1, float *z2, int pw,
-                          const uint16_t *pcol16, const float *p32, const double *wc,
-                          double *zout, const double *zold, double *partials, double *scal,
-                          const double *part_rr, double *host_out, int tag,
-                          const ProlongAxes &axes = ProlongAxes{});
+                         const RestrictBoxes &boxes, const UpdArgs *upd, const PostArgs &post);
+int launch_prec_f32_post(hipStream_t s, int n, const DiaOffsets &d, const float *a32,
+                         const float *dinv32, const double *v, float *z1, float *z2, int pw,
+                         const uint16_t *pcol16, const float *p32, const double *wc,
+                         double *zout, const double *zold, double *partials,
+                         const ProlongAxes &axes = ProlongAxes{});
 void launch_prolong_ell(hipStream_t s, int n, int pw, const int *pcol, const uint16_t *pcol16,
                         bool fp32, const double *p64, const float *p32, const double *wc,
                         double *z, bool zero,

@@ -1669,6 +1669,72 @@ __global__ __launch_bounds__(256) void k_symv_final(const double *__restrict__ p
         y[row] = ((sh[0][threadIdx.x] + sh[1][threadIdx.x]) + sh[2][threadIdx.x]) + sh[3][threadIdx.x];
 }
 
+// y = S x in one launch, both triangles read: a work-group takes 16 rows of a
+// tile row, kSymvTiles tiles per step.  From a tile (I, J), J <= I, thread t
+// takes four columns of row t / 16; from a tile (J, I), J > I, it takes row
+// t / 4 and four of the 16 columns, which are the result's rows.  The partial
+// sums are added over the lanes and then the wavefronts in a fixed order.
+constexpr int kSymvTiles = 8;
+
+__global__ __launch_bounds__(256) void k_symv_rows(const double *__restrict__ pk, int n, int nt,
+                                                   const double *__restrict__ x,
+                                                   double *__restrict__ y)
+{
+    typedef double d4 __attribute__((ext_vector_type(4)));
+    __shared__ double sh[4][16];
+    const int I = blockIdx.x >> 2, q = blockIdx.x & 3;  // rows 16 q .. of tile row I
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int g = t >> 4, h = t & 15;  // J <= I: row 16 q + g, columns 4 h ..
+    const int c = t >> 2, u = t & 3;   // J > I: row c, columns 16 q + 4 u ..
+    double low = 0.0;
+    d4 up = {0.0, 0.0, 0.0, 0.0};
+    for (int J0 = 0; J0 < nt; J0 += kSymvTiles) {
+        d4 m[kSymvTiles], xv[kSymvTiles];
+#pragma unroll
+        for (int k = 0; k < kSymvTiles; ++k) {
+            const int J = min(J0 + k, nt - 1);
+            const int64_t at = J <= I ? static_cast<int64_t>(I) * (I + 1) / 2 + J
+                                      : static_cast<int64_t>(J) * (J + 1) / 2 + I;
+            const int e = J <= I ? (16 * q + g) * kBP + 4 * h : c * kBP + 16 * q + 4 * u;
+            m[k] = *reinterpret_cast<const d4 *>(pk + at * kBP * kBP + e);
+            const int j = J * kBP + (J <= I ? 4 * h : c);
+#pragma unroll
+            for (int b = 0; b < 4; ++b) xv[k][b] = x[min(j + (J <= I ? b : 0), n - 1)];
+        }
+        // (the tiles hold zeros past n)
+#pragma unroll
+        for (int k = 0; k < kSymvTiles; ++k) {
+            if (J0 + k >= nt) break;
+            if (J0 + k <= I) {
+#pragma unroll
+                for (int b = 0; b < 4; ++b) low += m[k][b] * xv[k][b];
+            } else {
+#pragma unroll
+                for (int b = 0; b < 4; ++b) up[b] += m[k][b] * xv[k][b];
+            }
+        }
+    }
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) low += __shfl_xor(low, off, 64);
+#pragma unroll
+    for (int off = 32; off > 2; off >>= 1)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) up[b] += __shfl_xor(up[b], off, 64);
+    if (lane < 4) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) sh[w][4 * lane + b] = up[b];
+    }
+    __syncthreads();
+    const int row = I * kBP + 16 * q + g;
+    if (h == 0 && row < n) y[row] = low + (((sh[0][g] + sh[1][g]) + sh[2][g]) + sh[3][g]);
+}
+
+// most unknowns of the one-launch form: at 336 it takes 4.1 us against 6.6 for
+// tiles and sums, and a work-group's chain of tiles adds 0.38 us per 64
+// unknowns (12.7 against 8.7 us at 1,728; four groups of threads over the
+// tiles shorten that to 8.3, but make 336 slower, 5.7)
+constexpr int kSymvRowsMax = 640;
+
 // y = M x, one wavefront per row; lanes stride over the columns (two per
 // 16-byte load when n is even) and the 64 partial sums are added in a fixed
 // butterfly order.
@@ -2435,6 +2501,10 @@ void launch_symv_packed(hipStream_t s, int n, const double *pk, const double *x,
                         double *part)
 {
     const int nt = (n + kBP - 1) / kBP;
+    if (n <= kSymvRowsMax) {
+        k_symv_rows<<<4 * nt, 256, 0, s>>>(pk, n, nt, x, y);
+        return;
+    }
     k_symv_tiles<<<nt * (nt + 1) / 2, 256, 0, s>>>(pk, n, x, part);
     k_symv_final<<<nt, 256, 0, s>>>(part, n, y);
 }

@@ -108,6 +108,20 @@ __global__ __launch_bounds__(kBlock) void k_sweep32(int n, const int *__restrict
     zout[i] = zin[i] + static_cast<double>(dinv[i] * (static_cast<float>(v[i]) - s));
 }
 
+// a kBlock work-group's post (see PostArgs): r.r summed in a fixed order, the
+// first step that broke down
+__device__ inline void post_step(const PostArgs &p)
+{
+    double s = 0.0;
+#pragma unroll 8
+    for (int b = threadIdx.x; b < p.nrr; b += kBlock) s += p.rr[b];
+    s = block_sum(s);
+    if (threadIdx.x != 0) return;
+    const double bb = p.scal[S_BREAK_BETA], ba = p.scal[S_BREAK];
+    post_mail(p.host_out, s, bb != 0.0 ? bb : ba, p.tag);
+}
+__global__ __launch_bounds__(kBlock) void k_post(PostArgs p) { post_step(p); }
+
 // v_c = R x with R = P^T stored by coarse rows (padded to 64-entry groups,
 // pads of value 0): one work-group per coarse row (neighbouring coarse rows,
 // which share fine rows, on one XCD).  With R16 the columns are read as
@@ -126,10 +140,14 @@ __global__ __launch_bounds__(kBlock) void k_restrict_b(int nc, const int *__rest
                                                        const int *__restrict__ rbase,
                                                        const T *__restrict__ rv,
                                                        const XT *__restrict__ x,
-                                                       double *__restrict__ xc)
+                                                       double *__restrict__ xc, PostArgs post)
 {
-    const int j = xcd_group(blockIdx.x, gridDim.x);
-    if (j >= nc) return;
+    const int posts = post.host_out ? 1 : 0;  // the first work-group posts
+    if (static_cast<int>(blockIdx.x) < posts) {
+        post_step(post);
+        return;
+    }
+    const int j = xcd_group(blockIdx.x - posts, nc);
     double s = 0.0;
     const int t1 = rrp[j + 1];
     for (int t = rrp[j] + threadIdx.x; t < t1; t += U * kBlock) {
@@ -163,10 +181,14 @@ __global__ __launch_bounds__(kBlock) void k_restrict_box(int nc, const int *__re
                                                          const int *__restrict__ box, int nx,
                                                          int nxy, const T *__restrict__ rv,
                                                          const XT *__restrict__ x,
-                                                         double *__restrict__ xc)
+                                                         double *__restrict__ xc, PostArgs post)
 {
-    const int j = xcd_group(blockIdx.x, gridDim.x);
-    if (j >= nc) return;
+    const int posts = post.host_out ? 1 : 0;  // the first work-group posts
+    if (static_cast<int>(blockIdx.x) < posts) {
+        post_step(post);
+        return;
+    }
+    const int j = xcd_group(blockIdx.x - posts, nc);
     const int r0 = rrp[j];
     const int org = box[4 * j], bx = box[4 * j + 1], bxy = box[4 * j + 2];
     const int t1 = r0 + box[4 * j + 3];
@@ -542,53 +564,133 @@ __device__ inline void sum_partials_block(int nb, const double *__restrict__ par
     }
 }
 
-// alpha = (r.z)_old / (p.q), breakdown on p.q <= 0 or non-finite values
+// alpha = (r.z) / (p.q), 0 with a breakdown on p.q <= 0 or non-finite values
+__device__ inline double alpha_of(double rz, double pq, bool &bad)
+{
+    bad = !(pq > 0.0) || !isfinite(pq) || !isfinite(rz);
+    return bad ? 0.0 : rz / pq;
+}
+// flexible (Polak-Ribiere) beta = r.(z - z_old) / (r.z)_old, 0 with a
+// breakdown when not finite
+__device__ inline double beta_of(double rzdiff, double rz_old, bool &bad)
+{
+    const double b = rzdiff / rz_old;
+    bad = !isfinite(b);
+    return bad ? 0.0 : b;
+}
+
+// (the first step that breaks down is kept)
+__device__ inline void note_break(double *__restrict__ flag, double tag)
+{
+    if (flag[0] == 0.0) flag[0] = tag;
+}
+
 __global__ __launch_bounds__(kFinThreads) void k_fin_alpha(int nb, const double *__restrict__ part,
-                                                           double *__restrict__ scal)
+                                                           double *__restrict__ scal, int rzs,
+                                                           double tag)
 {
     // the scalar read first, so that its load overlaps the partials' loads
-    const double rz = scal[S_RZ_OLD];
+    const double rz = scal[rzs];
     double t[1];
     sum_partials_block<1>(nb, part, t);
     if (threadIdx.x != 0) return;
-    const double pq = t[0];
-    scal[S_PQ] = pq;
-    const bool bad = !(pq > 0.0) || !isfinite(pq) || !isfinite(rz);
-    if (bad) scal[S_BREAK] = 1.0;
-    scal[S_ALPHA] = bad ? 0.0 : rz / pq;
+    bool bad;
+    scal[S_ALPHA] = alpha_of(rz, t[0], bad);
+    scal[S_PQ] = t[0];
+    if (bad) note_break(scal + S_BREAK, tag);
 }
 
-// flexible (Polak-Ribiere) beta = r.(z - z_old) / (r.z)_old from the
-// partials [0, nb) of r.z and [nb, 2 nb) of r.(z - z_old).  With host_out
-// (inside PCG) also r.r of the step's residual update, from the partials
-// part_rr: written with the breakdown flag to a host mailbox (coherent
-// pinned memory), the values first and then, after a system-scope fence,
-// the iteration tag the host waits for.
-__global__ __launch_bounds__(kFinThreads) void k_fin_beta(int nb, const double *__restrict__ part,
-                                                          double *__restrict__ scal,
-                                                          const double *__restrict__ part_rr,
-                                                          double *__restrict__ host_out,
-                                                          double tag)
+// beta from the partials of r.z and r.(z - z_old); with post.host_out the
+// step is posted here (when no direction follows)
+__global__ __launch_bounds__(kFinThreads) void k_fin_beta(PcgSums p, PostArgs post)
 {
-    // the scalars read first, so that their loads overlap the partials' loads
-    const double rz_old = scal[S_RZ_OLD], brk = scal[S_BREAK];
-    // r.z, r.(z - z_old) and (inside PCG) r.r in one pass
-    double t[3];
-    sum_partials_block<3>(nb, part, t, host_out != nullptr ? part_rr : part);
+    // the scalar read first, so that its load overlaps the partials' loads
+    const double rz_old = p.scal[p.rz_old];
+    double t[2], rr[1] = {0.0};
+    sum_partials_block<2>(p.ndots, p.dots, t);
+    if (post.host_out) sum_partials_block<1>(post.nrr, post.rr, rr);
     if (threadIdx.x != 0) return;
-    scal[S_RZ] = t[0];
-    scal[S_RZDIFF] = t[1];
-    const double b = t[1] / rz_old;
-    const bool bad = !isfinite(b);
-    if (bad) scal[S_BREAK] = 1.0;
-    scal[S_BETA] = bad ? 0.0 : b;
-    scal[S_RZ_OLD] = t[0];
-    if (host_out == nullptr) return;
-    scal[S_RR] = t[2];
-    host_out[0] = t[2];
-    host_out[1] = bad ? 1.0 : brk;
-    __threadfence_system();
-    host_out[2] = tag;
+    bool bad;
+    p.scal[S_BETA] = beta_of(t[1], rz_old, bad);
+    if (bad) note_break(p.scal + S_BREAK_BETA, p.tag);
+    p.scal[p.rz_new] = t[0];
+    if (post.host_out) {
+        const double bb = p.scal[S_BREAK_BETA], ba = p.scal[S_BREAK];
+        post_mail(post.host_out, rr[0], bb != 0.0 ? bb : ba, post.tag);
+    }
+}
+
+// sums of NV arrays of partials over a kBlock work-group, the same in every
+// work-group (strided lanes, a butterfly, the wavefronts in order)
+template <int NV>
+__device__ __forceinline__ void group_totals(const double *const (&src)[NV], const int (&m)[NV],
+                                             double (&tot)[NV])
+{
+    __shared__ double sh[NV][kBlock / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        tot[q] = 0.0;
+#pragma unroll
+        for (int u = 0; u < kSumBlocks / kBlock; ++u) {
+            const int b = threadIdx.x + u * kBlock;
+            tot[q] += b < m[q] ? src[q][b] : 0.0;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) tot[q] += __shfl_xor(tot[q], off, 64);
+        if (lane == 0) sh[q][w] = tot[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        double t = 0.0;
+#pragma unroll
+        for (int u = 0; u < kBlock / 64; ++u) t += sh[q][u];
+        tot[q] = t;
+    }
+}
+
+// alpha of the update, from the partials or from scal (every thread of the
+// work-group calls it); work-group 0 records a breakdown
+__device__ __forceinline__ double step_alpha(const UpdArgs &u)
+{
+    if (u.npq == 0) return u.scal[S_ALPHA];
+    const double rz = u.scal[u.rz];
+    const double *const src[1] = {u.pq};
+    const int m[1] = {u.npq};
+    double t[1];
+    group_totals<1>(src, m, t);
+    bool bad;
+    const double alpha = alpha_of(rz, t[0], bad);
+    if (bad && blockIdx.x == 0 && threadIdx.x == 0) note_break(u.scal + S_BREAK, u.tag);
+    return alpha;
+}
+// whether the last step's beta broke down: its direction is not taken (the
+// host, which is told with this step's post, ends there)
+__device__ __forceinline__ bool step_stopped(const UpdArgs &u)
+{
+    return u.scal[S_BREAK_BETA] != 0.0;
+}
+
+// beta of the direction, likewise; work-group 0 keeps the new r.z
+__device__ __forceinline__ double step_beta(const PcgSums &p)
+{
+    if (p.ndots == 0) return p.scal[S_BETA];
+    const double rz_old = p.scal[p.rz_old];
+    const double *const src[2] = {p.dots, p.dots + p.ndots};
+    const int m[2] = {p.ndots, p.ndots};
+    double t[2];
+    group_totals<2>(src, m, t);
+    bool bad;
+    const double beta = beta_of(t[1], rz_old, bad);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        p.scal[p.rz_new] = t[0];
+        if (bad) note_break(p.scal + S_BREAK_BETA, p.tag);
+    }
+    return beta;
 }
 
 // ---------------------------------------------------------------------------
@@ -768,6 +870,38 @@ __global__ __launch_bounds__(KS *kNbsNodes) void k_nbs_sweep(
     }
 }
 
+// the same as the last sweep inside PCG, with the partials of r.z and
+// r.(z - z_old) (one per work-group: its nodes are one wavefront)
+template <int BS, bool SYM, int KS, typename MT>
+__global__ __launch_bounds__(KS *kNbsNodes) void k_nbs_sweep_dots(
+    NodeStencil ns, const MT *__restrict__ a, const MT *__restrict__ dinv,
+    const double *__restrict__ rv, const double *__restrict__ zin, double *__restrict__ zout,
+    const double *__restrict__ zold, double *__restrict__ part)
+{
+    const int node = nbs_node();
+    MT s[BS];
+    nbs_dot<BS, SYM, KS, MT>(node, ns, a, zin, s);
+    if (threadIdx.x >= kNbsNodes) return;
+    double v[2] = {0.0, 0.0};
+    if (node < ns.nn) {
+#pragma unroll
+        for (int c = 0; c < BS; ++c) {
+            const int64_t r = static_cast<int64_t>(node) * BS + c;
+            const double ri = rv[r];
+            const double z = zin[r] + static_cast<double>(dinv[r] * (static_cast<MT>(ri) - s[c]));
+            zout[r] = z;
+            v[0] += ri * z;
+            v[1] += ri * (z - zold[r]);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v[q] += __shfl_xor(v[q], off, 64);
+        if (threadIdx.x == 0) part[static_cast<int64_t>(q) * gridDim.x + blockIdx.x] = v[q];
+    }
+}
+
 // the same from z_in = 0: D^{-1} v
 template <typename MT>
 __global__ __launch_bounds__(kBlock) void k_scale_rows(int n, const MT *__restrict__ dinv,
@@ -784,12 +918,11 @@ __global__ __launch_bounds__(kBlock) void k_scale_rows(int n, const MT *__restri
 // row that halves the gathered bytes).
 __global__ __launch_bounds__(kBlock) void k_p_update(int n, const double *__restrict__ z,
                                                      const double *__restrict__ pold,
-                                                     double *__restrict__ pnew,
-                                                     const double *__restrict__ scal)
+                                                     double *__restrict__ pnew, PcgSums sums)
 {
     const int r = blockIdx.x * kBlock + threadIdx.x;
+    const double beta = step_beta(sums);
     if (r >= n) return;
-    const double beta = scal[S_BETA];
     pnew[r] = beta == 0.0 ? z[r] : z[r] + beta * pold[r];
 }
 
@@ -962,7 +1095,6 @@ __global__ __launch_bounds__(kBlock) void k_pcg_update_sweep2(int n, DiaOffsets 
     const int i = xcd_row();
     const int t = threadIdx.x;
     const int ic = i < n ? i : n - 1;
-    const double alpha = u.scal[S_ALPHA];
     const TileRows<ND> r(i, ic, t, n, d);
     TileCoefs<ND, SYM, MT> c;
     c.load(a, n, ic, t, r, sa);
@@ -975,9 +1107,11 @@ __global__ __launch_bounds__(kBlock) void k_pcg_update_sweep2(int n, DiaOffsets 
             vk[o] = u.rin[r.kk[o]];
             qk[o] = u.q[r.kk[o]];
         }
-    const double xi = u.x[ic], pi = u.p[ic];
-    const double vi = pcg_residual(u.rin[ic], u.q[ic], alpha);
+    const double xi = u.x[ic], pi = u.p[ic], ri = u.rin[ic], qi = u.q[ic];
     const MT di = dinv[ic];
+    const bool stop = step_stopped(u);
+    const double alpha = step_alpha(u);  // (after the loads, which it waits with)
+    const double vi = pcg_residual(ri, qi, alpha);
     sz1[t] = static_cast<MT>(static_cast<double>(di * static_cast<MT>(vi)));
     __syncthreads();
     c.finish(t, d, r, sa);
@@ -997,7 +1131,7 @@ __global__ __launch_bounds__(kBlock) void k_pcg_update_sweep2(int n, DiaOffsets 
     if (i < n) {
         const double z1i = static_cast<double>(di * static_cast<MT>(vi));
         zout[i] = static_cast<ZT>(z1i + static_cast<double>(di * (static_cast<MT>(vi) - s)));
-        u.x[i] = fma(alpha, pi, xi);
+        if (!stop) u.x[i] = fma(alpha, pi, xi);
         u.rout[i] = vi;
         rr[0] = vi * vi;
     }
@@ -1037,9 +1171,9 @@ __global__ __launch_bounds__(kBlock) void k_dia_sweep_dots(
     block_partials<2>(v, part);
 }
 
-// r.z and r.(z - z_old) with the flexible beta (when the last stage of the
-// preconditioner is not a fused DIA sweep)
-__global__ __launch_bounds__(kBlock) void k_dots_beta(int n, const double *__restrict__ r,
+// r.z and r.(z - z_old) (when the last stage of the preconditioner is not a
+// fused sweep)
+__global__ __launch_bounds__(kBlock) void k_dots(int n, const double *__restrict__ r,
                                                       const double *__restrict__ z,
                                                       const double *__restrict__ zold,
                                                       double *__restrict__ part)
@@ -1061,10 +1195,10 @@ __global__ __launch_bounds__(kBlock) void k_pcg_p_spmv(
     int n, DiaOffsets d, const double *__restrict__ ad, const int *__restrict__ rp,
     const int *__restrict__ ci, const double *__restrict__ a, const double *__restrict__ z,
     const double *__restrict__ pold, double *__restrict__ pnew, double *__restrict__ q,
-    double *__restrict__ part, const double *__restrict__ scal)
+    double *__restrict__ part, PcgSums sums)
 {
     const int i = xcd_row();
-    const double beta = scal[S_BETA];
+    const double beta = step_beta(sums);
     const bool restart = beta == 0.0;
     double v[1] = {0.0};
     if (i < n) {
@@ -1140,7 +1274,7 @@ template <int ND, bool SYM>
 __global__ __launch_bounds__(kBlock) void k_pcg_p_spmv_dia(
     int n, DiaOffsets d, const double *__restrict__ ad, const double *__restrict__ z,
     const double *__restrict__ pold, double *__restrict__ pnew, double *__restrict__ q,
-    double *__restrict__ part, const double *__restrict__ scal)
+    double *__restrict__ part, PcgSums sums)
 {
     constexpr int MID = ND / 2;  // the zero offset of a symmetric offset set
     __shared__ double sz[kBlock], sp[kBlock];
@@ -1148,7 +1282,9 @@ __global__ __launch_bounds__(kBlock) void k_pcg_p_spmv_dia(
     const int t = threadIdx.x;
     const int i = xcd_row();
     const int ic = i < n ? i : n - 1;
-    const double beta = scal[S_BETA];
+    // beta = 0 in scal: a restart, p_old is not read; a beta formed here from
+    // the partials comes after the loads, which it waits with
+    double beta = sums.ndots == 0 ? step_beta(sums) : 1.0;
     const bool restart = beta == 0.0;
     double av[ND], zk[ND], pk[ND];
     bool in[ND], loc[ND];
@@ -1173,6 +1309,7 @@ __global__ __launch_bounds__(kBlock) void k_pcg_p_spmv_dia(
 #pragma unroll
         for (int o = MID + 1; o < ND; ++o) sa[o - MID - 1][t] = av[o];
     }
+    if (sums.ndots > 0) beta = step_beta(sums);
     __syncthreads();
 #pragma unroll
     for (int o = 0; o < ND; ++o) {
@@ -1204,25 +1341,26 @@ __global__ __launch_bounds__(kBlock) void k_pcg_p_spmv_dia(
 }
 
 // x += alpha p, r_out = r_in - alpha q, and r.r (out of place, as the fused
-// form above)
-__global__ __launch_bounds__(kBlock) void k_pcg_update(int n, double *__restrict__ x,
-                                                       const double *__restrict__ rin,
-                                                       double *__restrict__ rout,
-                                                       const double *__restrict__ p,
-                                                       const double *__restrict__ q,
-                                                       double *__restrict__ part,
-                                                       const double *__restrict__ scal)
+// form above); with z also the first sweep from zero, z = D^{-1} r_out
+template <typename MT>
+__global__ __launch_bounds__(kBlock) void k_pcg_update(int n, UpdArgs u, double *__restrict__ z,
+                                                       const MT *__restrict__ dinv)
 {
-    const double alpha = scal[S_ALPHA];
     const int i = blockIdx.x * kBlock + threadIdx.x;
+    const int ic = i < n ? i : n - 1;
+    const double xi = u.x[ic], pi = u.p[ic], ri = u.rin[ic], qi = u.q[ic];
+    const MT di = z ? dinv[ic] : MT(0);
+    const bool stop = step_stopped(u);
+    const double alpha = step_alpha(u);
     double v[1] = {0.0};
     if (i < n) {
-        x[i] = fma(alpha, p[i], x[i]);
-        const double ri = pcg_residual(rin[i], q[i], alpha);
-        rout[i] = ri;
-        v[0] = ri * ri;
+        if (!stop) u.x[i] = fma(alpha, pi, xi);
+        const double r = pcg_residual(ri, qi, alpha);
+        u.rout[i] = r;
+        if (z) z[i] = static_cast<double>(di * static_cast<MT>(r));
+        v[0] = r * r;
     }
-    block_partials<1>(v, part);
+    block_partials<1>(v, u.part);
 }
 
 // z (+)= P w_c with P in row-major ELL layout; a row's values are read with
@@ -1513,30 +1651,32 @@ static void with_restrict_unroll(int maxlen, F &&f)
 template <typename T, typename XT>
 static void restrict_kernels(hipStream_t s, int nc, const int *rrp, const int *rci,
                              const uint16_t *roff16, const int *rbase, const T *rv, const XT *x,
-                             double *xc, const RestrictBoxes &boxes)
+                             double *xc, const RestrictBoxes &boxes, const PostArgs &post)
 {
     with_restrict_unroll(boxes.maxlen, [&](auto u) {
         constexpr int U = decltype(u)::value;
+        const int g = nc + (post.host_out ? 1 : 0);
         if (boxes.box)
-            k_restrict_box<T, XT, U><<<nc, kBlock, 0, s>>>(nc, rrp, boxes.box, boxes.nx, boxes.nxy,
-                                                           rv, x, xc);
+            k_restrict_box<T, XT, U><<<g, kBlock, 0, s>>>(nc, rrp, boxes.box, boxes.nx, boxes.nxy,
+                                                           rv, x, xc, post);
         else if (roff16)
-            k_restrict_b<T, XT, true, U><<<nc, kBlock, 0, s>>>(nc, rrp, rci, roff16, rbase, rv, x,
-                                                               xc);
+            k_restrict_b<T, XT, true, U><<<g, kBlock, 0, s>>>(nc, rrp, rci, roff16, rbase, rv, x,
+                                                              xc, post);
         else
-            k_restrict_b<T, XT, false, U><<<nc, kBlock, 0, s>>>(nc, rrp, rci, roff16, rbase, rv,
-                                                                x, xc);
+            k_restrict_b<T, XT, false, U><<<g, kBlock, 0, s>>>(nc, rrp, rci, roff16, rbase, rv,
+                                                               x, xc, post);
     });
 }
 
 void launch_restrict(hipStream_t s, int nc, const int *rrp, const int *rci,
                      const uint16_t *roff16, const int *rbase, bool fp32, const double *r64,
-                     const float *r32, const double *x, double *xc, const RestrictBoxes &boxes)
+                     const float *r32, const double *x, double *xc, const RestrictBoxes &boxes,
+                     const PostArgs &post)
 {
     if (fp32)
-        restrict_kernels<float, double>(s, nc, rrp, rci, roff16, rbase, r32, x, xc, boxes);
+        restrict_kernels<float, double>(s, nc, rrp, rci, roff16, rbase, r32, x, xc, boxes, post);
     else
-        restrict_kernels<double, double>(s, nc, rrp, rci, roff16, rbase, r64, x, xc, boxes);
+        restrict_kernels<double, double>(s, nc, rrp, rci, roff16, rbase, r64, x, xc, boxes, post);
 }
 
 void launch_dot(hipStream_t s, int n, const double *x, const double *y, double *partials,
@@ -1695,11 +1835,10 @@ void launch_dia_sweep(hipStream_t s, int n, const DiaOffsets &d, bool fp32, cons
     });
 }
 
-void launch_dia_sweep_dots(hipStream_t s, int n, const DiaOffsets &d, bool fp32,
-                           const double *a64, const float *a32, const double *dinv64,
-                           const float *dinv32, const double *r, const double *zin, double *zout,
-                           const double *zold, double *part, double *scal,
-                           const double *part_rr, double *host_out, int tag)
+int launch_dia_sweep_dots(hipStream_t s, int n, const DiaOffsets &d, bool fp32,
+                          const double *a64, const float *a32, const double *dinv64,
+                          const float *dinv32, const double *r, const double *zin, double *zout,
+                          const double *zold, double *part)
 {
     with_ndiag(d, [&](auto nd, auto sym) {
         if (fp32)
@@ -1709,7 +1848,7 @@ void launch_dia_sweep_dots(hipStream_t s, int n, const DiaOffsets &d, bool fp32,
             k_dia_sweep_dots<MSRSB_DIA_ARGS(nd, sym), double><<<grid_for(n), kBlock, 0, s>>>(
                 n, d, a64, dinv64, r, zin, zout, zold, part);
     });
-    k_fin_beta<<<1, kFinThreads, 0, s>>>(grid_for(n), part, scal, part_rr, host_out, tag);
+    return grid_for(n);
 }
 
 // The two-stage preconditioner of the precision form with FP32 intermediate
@@ -1721,7 +1860,7 @@ void launch_prec_f32_pre(hipStream_t s, int n, const DiaOffsets &d, const float 
                          const float *dinv32, const double *v, float *z1, float *tmp, int nc,
                          const int *rrp, const int *rci, const uint16_t *roff16,
                          const int *rbase, const float *r32, double *vc,
-                         const RestrictBoxes &boxes, const UpdArgs *upd)
+                         const RestrictBoxes &boxes, const UpdArgs *upd, const PostArgs &post)
 {
     with_ndiag(d, [&](auto nd, auto sym) {
         constexpr int ND = decltype(nd)::value;
@@ -1741,17 +1880,16 @@ void launch_prec_f32_pre(hipStream_t s, int n, const DiaOffsets &d, const float 
         k_dia_residual<MSRSB_DIA_ARGS(nd, sym), float, float, float>
             <<<grid_for(n), kBlock, 0, s>>>(n, d, a32, v, z1, tmp);
     });
-    restrict_kernels<float, float>(s, nc, rrp, rci, roff16, rbase, r32, tmp, vc, boxes);
+    restrict_kernels<float, float>(s, nc, rrp, rci, roff16, rbase, r32, tmp, vc, boxes, post);
 }
 
 // _post: z1 += P wc, z2 = sweep(z1), z = sweep(z2) with r.z, r.(z - zold)
 // and the flexible beta
-void launch_prec_f32_post(hipStream_t s, int n, const DiaOffsets &d, const float *a32,
-                          const float *dinv32, const double *v, float *z1, float *z2, int pw,
-                          const uint16_t *pcol16, const float *p32, const double *wc,
-                          double *zout, const double *zold, double *partials, double *scal,
-                          const double *part_rr, double *host_out, int tag,
-                          const ProlongAxes &axes)
+int launch_prec_f32_post(hipStream_t s, int n, const DiaOffsets &d, const float *a32,
+                         const float *dinv32, const double *v, float *z1, float *z2, int pw,
+                         const uint16_t *pcol16, const float *p32, const double *wc,
+                         double *zout, const double *zold, double *partials,
+                         const ProlongAxes &axes)
 {
     // (FP32 P is read in its padded rows: axes.wtab is not set for it)
     if (axes.tab && pw == 8)
@@ -1768,40 +1906,56 @@ void launch_prec_f32_post(hipStream_t s, int n, const DiaOffsets &d, const float
         k_dia_sweep_dots<MSRSB_DIA_ARGS(nd, sym), float, float><<<grid_for(n), kBlock, 0, s>>>(
             n, d, a32, dinv32, v, z2, zout, zold, partials);
     });
-    k_fin_beta<<<1, kFinThreads, 0, s>>>(grid_for(n), partials, scal, part_rr, host_out, tag);
+    return grid_for(n);
 }
 
-void launch_dots_beta(hipStream_t s, int n, const double *r, const double *z, const double *zold,
-                      double *part, double *scal, const double *part_rr, double *host_out,
-                      int tag)
+int launch_dots(hipStream_t s, int n, const double *r, const double *z, const double *zold,
+                double *part)
 {
-    k_dots_beta<<<grid_for(n), kBlock, 0, s>>>(n, r, z, zold, part);
-    k_fin_beta<<<1, kFinThreads, 0, s>>>(grid_for(n), part, scal, part_rr, host_out, tag);
+    k_dots<<<grid_for(n), kBlock, 0, s>>>(n, r, z, zold, part);
+    return grid_for(n);
 }
 
-void launch_pcg_p_spmv(hipStream_t s, int n, const DiaOffsets &d, const double *ad,
-                       const int *rp, const int *ci, const double *a, const double *z,
-                       const double *pold, double *pnew, double *q, double *part, double *scal)
+void launch_fin_beta(hipStream_t s, const PcgSums &p, const PostArgs &post)
+{
+    k_fin_beta<<<1, kFinThreads, 0, s>>>(p, post);
+}
+
+void launch_post(hipStream_t s, const PostArgs &post) { k_post<<<1, kBlock, 0, s>>>(post); }
+
+void launch_fin_alpha(hipStream_t s, int nb, const double *part, double *scal, int rz, double tag)
+{
+    k_fin_alpha<<<1, kFinThreads, 0, s>>>(nb, part, scal, rz, tag);
+}
+
+int launch_pcg_p_spmv(hipStream_t s, int n, const DiaOffsets &d, const double *ad,
+                      const int *rp, const int *ci, const double *a, const double *z,
+                      const double *pold, double *pnew, double *q, double *part,
+                      const PcgSums &sums)
 {
     if (d.n > 0)
         with_ndiag(d, [&](auto nd, auto sym) {
             constexpr int ND = decltype(nd)::value;
             if constexpr (ND > 0 && ND <= 9)
                 k_pcg_p_spmv_dia<MSRSB_DIA_ARGS(nd, sym)><<<grid_for(n), kBlock, 0, s>>>(
-                    n, d, ad, z, pold, pnew, q, part, scal);
+                    n, d, ad, z, pold, pnew, q, part, sums);
             else
                 k_pcg_p_spmv<MSRSB_DIA_ARGS(nd, sym)><<<grid_for(n), kBlock, 0, s>>>(
-                    n, d, ad, rp, ci, a, z, pold, pnew, q, part, scal);
+                    n, d, ad, rp, ci, a, z, pold, pnew, q, part, sums);
         });
     else
         k_pcg_p_spmv<-1, false><<<grid_for(n), kBlock, 0, s>>>(n, d, ad, rp, ci, a, z, pold, pnew,
-                                                               q, part, scal);
-    k_fin_alpha<<<1, kFinThreads, 0, s>>>(grid_for(n), part, scal);
+                                                               q, part, sums);
+    return grid_for(n);
 }
 
-void launch_pcg_update(hipStream_t s, int n, const UpdArgs &u)
+void launch_pcg_update(hipStream_t s, int n, const UpdArgs &u, double *z, const double *dinv,
+                       const float *dinv32)
 {
-    k_pcg_update<<<grid_for(n), kBlock, 0, s>>>(n, u.x, u.rin, u.rout, u.p, u.q, u.part, u.scal);
+    if (z && dinv32)
+        k_pcg_update<float><<<grid_for(n), kBlock, 0, s>>>(n, u, z, dinv32);
+    else
+        k_pcg_update<double><<<grid_for(n), kBlock, 0, s>>>(n, u, z, dinv);
 }
 
 template <typename T>
@@ -1948,18 +2102,34 @@ void launch_nbs_sweep(hipStream_t s, int n, const NodeStencil &ns, bool fp32, co
     });
 }
 
-void launch_nbs_pcg_p_spmv(hipStream_t s, int n, const NodeStencil &ns, const double *v,
-                           const double *z, const double *pold, double *pnew, double *q,
-                           double *part, double *scal)
+int launch_nbs_sweep_dots(hipStream_t s, int n, const NodeStencil &ns, bool fp32, const double *v,
+                          const float *v32, const double *dinv, const float *dinv32,
+                          const double *r, const double *zin, double *zout, const double *zold,
+                          double *part)
+{
+    with_ns(ns, [&](auto b, auto sy, auto ks, int threads) {
+        if (fp32)
+            k_nbs_sweep_dots<b.value, sy.value, ks.value, float>
+                <<<nbs_grid(ns), threads, 0, s>>>(ns, v32, dinv32, r, zin, zout, zold, part);
+        else
+            k_nbs_sweep_dots<b.value, sy.value, ks.value, double>
+                <<<nbs_grid(ns), threads, 0, s>>>(ns, v, dinv, r, zin, zout, zold, part);
+    });
+    return nbs_grid(ns);
+}
+
+int launch_nbs_pcg_p_spmv(hipStream_t s, int n, const NodeStencil &ns, const double *v,
+                          const double *z, const double *pold, double *pnew, double *q,
+                          double *part, const PcgSums &sums)
 {
     // two passes (k_p_update, k_nbs_spmv_dot): 157 -> 5 + 115 us per call on
-    // the 3D Q1 operator at 824k rows
-    k_p_update<<<grid_for(n), kBlock, 0, s>>>(n, z, pold, pnew, scal);
+    // the 3D Q1 operator at 824k rows, before its entries were halved
+    k_p_update<<<grid_for(n), kBlock, 0, s>>>(n, z, pold, pnew, sums);
     with_ns(ns, [&](auto b, auto sy, auto ks, int threads) {
         k_nbs_spmv_dot<b.value, sy.value, ks.value>
             <<<nbs_grid(ns), threads, 0, s>>>(ns, v, pnew, q, part);
     });
-    k_fin_alpha<<<1, kFinThreads, 0, s>>>(nbs_grid(ns), part, scal);
+    return nbs_grid(ns);
 }
 
 }  // namespace msrsb

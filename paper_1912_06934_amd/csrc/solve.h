@@ -5,15 +5,15 @@
 
 namespace msrsb {
 
-// Buffers for the r.z dot products and flexible beta computed at the end of
-// a preconditioner application inside PCG.
+// The r.z products formed at the end of a preconditioner application inside
+// PCG: their partials go to part (sums.dots), and with ndots left at 0 by the
+// application beta is in scal, else the next direction forms it from sums.
 struct PcgDots {
     const double *zold;
     double *part;
-    double *scal;
-    const double *part_rr;  // r.r partials of the step's update
-    double *host_out;       // r.r mailbox of the step (null: beta only)
-    int tag;           // the step's iteration number
+    bool last;      // no direction follows: beta is formed and the step posted at the end
+    PcgSums sums;
+    PostArgs post;
 };
 
 // Temporaries of one preconditioner application: three FP64 and three FP32
@@ -33,7 +33,7 @@ msrsb_status ensure_smoother(msrsb_ctx *c, const msrsb_solve_opts *o, bool trans
 // With upd, v is first produced by the PCG update upd (upd->rout == v).
 // bufs: the temporaries (null: the context's workspace).
 void apply_two_stage(msrsb_ctx *c, const msrsb_solve_opts *o, const double *v, double *zout,
-                     bool trans, const PcgDots *dots, const UpdArgs *upd = nullptr,
+                     bool trans, PcgDots *dots, const UpdArgs *upd = nullptr,
                      const ApplyBufs *bufs = nullptr);
 msrsb_status pcg(msrsb_ctx *c, const double *f, double *x, const msrsb_solve_opts *o,
                  msrsb_solve_info *info, bool trans);

@@ -159,8 +159,7 @@ __global__ __launch_bounds__(kOrthoThreads) void k_ortho(int n, int k, int nbin,
 // entry i of the column (j < 64) and of the rotations, which thread by thread
 // follow each other through lane reads instead of memory.
 // With host_out (coherent pinned memory) the residual estimate and the
-// denominator also go to the host mailbox: the values, a system-scope fence,
-// then the step's tag the host waits for.
+// denominator also go to the host's mailbox.
 __device__ void gmres_givens(int j, int m, double *__restrict__ H, const double *__restrict__ h,
                              double norm, double *__restrict__ cs, double *__restrict__ sn,
                              double *__restrict__ g, double *__restrict__ res,
@@ -193,11 +192,7 @@ __device__ void gmres_givens(int j, int m, double *__restrict__ H, const double 
     g[j] = c * gj;
     res[0] = fabs(gn);
     res[1] = den;
-    if (host_out == nullptr) return;
-    host_out[0] = fabs(gn);
-    host_out[1] = den;
-    __threadfence_system();
-    host_out[2] = tag;
+    if (host_out) post_mail(host_out, fabs(gn), den, tag);
 }
 
 struct GivensArgs {
@@ -384,14 +379,19 @@ void op_spmv(hipStream_t s, int n, const Op &o, const double *x, double *y)
         launch_spmv(s, n, o.rp, o.ci, o.a, x, y);
 }
 
-// p = z + beta p_old, q = A p, p.q and alpha (PCG)
-void p_spmv(hipStream_t s, int n, const Op &o, const double *z, const double *pold, double *pnew,
-            double *q, double *part, double *sc)
+// p = z + beta p_old, q = A p (PCG); returns the number of p.q partials left
+// for the update to add, 0 when alpha has been formed
+int p_spmv(hipStream_t s, int n, const Op &o, const double *z, const double *pold, double *pnew,
+           double *q, double *pq, const PcgSums &sums)
 {
+    int nb;
     if (o.d.n == 0 && o.ns.n > 0)
-        launch_nbs_pcg_p_spmv(s, n, o.ns, o.nv, z, pold, pnew, q, part, sc);
+        nb = launch_nbs_pcg_p_spmv(s, n, o.ns, o.nv, z, pold, pnew, q, pq, sums);
     else
-        launch_pcg_p_spmv(s, n, o.d, o.ad, o.rp, o.ci, o.a, z, pold, pnew, q, part, sc);
+        nb = launch_pcg_p_spmv(s, n, o.d, o.ad, o.rp, o.ci, o.a, z, pold, pnew, q, pq, sums);
+    if (nb <= kSumBlocks) return nb;
+    launch_fin_alpha(s, nb, pq, sums.scal, sums.rz_new, sums.tag + 1.0);
+    return 0;
 }
 
 template <typename T>
@@ -458,7 +458,8 @@ msrsb_status ensure_workspace(msrsb_ctx *c)
         if (dev_alloc(&p, n)) return MSRSB_E_NOMEM;
     for (auto &p : c->wf)
         if (dev_alloc(&p, n)) return MSRSB_E_NOMEM;
-    const size_t np = std::max<size_t>({2 * (n / kBlock + 2), 2 * static_cast<size_t>(kReduceBlocks),
+    // (PCG: two products' partials, then the p.q ones, at most one per 192 rows)
+    const size_t np = std::max<size_t>({pq_offset(n) + n / 128 + 16, 2 * static_cast<size_t>(kReduceBlocks),
                                         64 * static_cast<size_t>(std::max(c->nc, 1)) + 64,
                                         static_cast<size_t>(64 * 66),
                                         static_cast<size_t>(3 * 2048)});
@@ -634,7 +635,7 @@ static RestrictBoxes restrict_boxes(const msrsb_ctx *c)
 }
 
 void apply_two_stage(msrsb_ctx *c, const msrsb_solve_opts *o, const double *v, double *zout,
-                     bool trans, const PcgDots *dots, const UpdArgs *upd, const ApplyBufs *bufs)
+                     bool trans, PcgDots *dots, const UpdArgs *upd, const ApplyBufs *bufs)
 {
     const ApplyBufs b = bufs ? *bufs : ctx_apply_bufs(c);
     hipStream_t s = c->stream;
@@ -663,22 +664,44 @@ void apply_two_stage(msrsb_ctx *c, const msrsb_solve_opts *o, const double *v, d
                           c->p_is32 && (c->pw == 4 || c->pw == 8) && is_diag(pre_k) &&
                           pre_n == 2 && pre_k == post_k && post_n == 2;
     const bool sweep2 = pre_n >= 2 && is_diag(pre_k) && op.d.n > 0;
-    // the PCG update that produces v: inside the first two-sweep kernel, or
-    // on its own where the application starts otherwise
-    if (upd && !f32_path && !sweep2) launch_pcg_update(s, n, *upd);
+    // beta of the products just formed (nb partials each): left to the next
+    // direction's kernel when it can add them itself
+    auto finish = [&](int nb) {
+        dots->sums.dots = dots->part;
+        dots->sums.ndots = nb;
+        if (nb <= kSumBlocks && !dots->last) return;
+        launch_fin_beta(s, dots->sums, dots->last ? dots->post : PostArgs{});
+        dots->sums.ndots = 0;
+    };
+    // the step's post goes with the restriction, or right after the update
+    const PostArgs post = dots && !dots->last ? dots->post : PostArgs{};
     if (f32_path) {
         const float *dinv = pre_k == MSRSB_SMOOTH_L1JACOBI ? op.dl132 : op.dj32;
         float *z1 = b.f[0], *z2 = b.f[1], *tf = b.f[2];
         launch_prec_f32_pre(s, n, op.d, op.ad32, dinv, v, z1, tf, c->nc, c->rrp, c->rci,
-                            c->roff16, c->rbase, c->r32, b.vc, restrict_boxes(c), upd);
+                            c->roff16, c->rbase, c->r32, b.vc, restrict_boxes(c), upd, post);
         coarse_apply(c, trans, b);
-        launch_prec_f32_post(s, n, op.d, op.ad32, dinv, v, z1, z2, c->pw, c->pcol16,
-                             prolong_p32(c), b.wc, zout, dots->zold, dots->part, dots->scal,
-                             dots->part_rr, dots->host_out, dots->tag, prolong_axes(c));
+        finish(launch_prec_f32_post(s, n, op.d, op.ad32, dinv, v, z1, z2, c->pw, c->pcol16,
+                                    prolong_p32(c), b.wc, zout, dots->zold, dots->part,
+                                    prolong_axes(c)));
         return;
     }
     bool zero = true;
     int t = 0;
+    // the PCG update that produces v: inside the first two-sweep kernel, with
+    // the first Jacobi-type sweep from zero, or on its own
+    if (upd && !sweep2) {
+        if (pre_n > 0 && is_diag(pre_k)) {
+            const bool l1 = pre_k == MSRSB_SMOOTH_L1JACOBI;
+            launch_pcg_update(s, n, *upd, spare, l1 ? op.dl1 : op.dj,
+                              fp32 ? (l1 ? op.dl132 : op.dj32) : nullptr);
+            std::swap(z, spare);
+            zero = false;
+            t = 1;
+        } else {
+            launch_pcg_update(s, n, *upd);
+        }
+    }
     if (sweep2) {
         const bool l1 = pre_k == MSRSB_SMOOTH_L1JACOBI;
         launch_dia_sweep(s, n, op.d, fp32, op.ad, op.ad32, l1 ? op.dl1 : op.dj,
@@ -686,6 +709,7 @@ void apply_two_stage(msrsb_ctx *c, const msrsb_solve_opts *o, const double *v, d
         zero = false;
         t = 2;
     }
+    if (post.host_out && !o->use_multiscale) launch_post(s, post);
     for (; t < pre_n; ++t) {
         sweep(c, op, pre_k, fp32, v, &z, &spare, zero, tmp, o->ordering);
         zero = false;
@@ -697,7 +721,7 @@ void apply_two_stage(msrsb_ctx *c, const msrsb_solve_opts *o, const double *v, d
             res = tmp;
         }
         launch_restrict(s, c->nc, c->rrp, c->rci, c->roff16, c->rbase, c->p_is32, c->r64, c->r32,
-                        res, b.vc, restrict_boxes(c));
+                        res, b.vc, restrict_boxes(c), post);
         coarse_apply(c, trans, b);
         launch_prolong_ell(s, n, c->pw, c->pcol_ell, c->pcol16, c->p_is32, prolong_p64(c),
                            prolong_p32(c),
@@ -708,10 +732,16 @@ void apply_two_stage(msrsb_ctx *c, const msrsb_solve_opts *o, const double *v, d
         const bool last = t == post_n - 1;
         if (last && dots && is_diag(post_k) && op.d.n > 0 && !zero) {
             const bool l1 = post_k == MSRSB_SMOOTH_L1JACOBI;
-            launch_dia_sweep_dots(s, n, op.d, fp32, op.ad, op.ad32, l1 ? op.dl1 : op.dj,
-                                  l1 ? op.dl132 : op.dj32, v, z, zout, dots->zold,
-                                  dots->part, dots->scal, dots->part_rr, dots->host_out,
-                                  dots->tag);
+            finish(launch_dia_sweep_dots(s, n, op.d, fp32, op.ad, op.ad32, l1 ? op.dl1 : op.dj,
+                                         l1 ? op.dl132 : op.dj32, v, z, zout, dots->zold,
+                                         dots->part));
+            return;
+        }
+        if (last && dots && is_diag(post_k) && op.ns.n > 0 && !zero) {
+            const bool l1 = post_k == MSRSB_SMOOTH_L1JACOBI;
+            finish(launch_nbs_sweep_dots(s, n, op.ns, fp32, op.nv, op.nv32, l1 ? op.dl1 : op.dj,
+                                         l1 ? op.dl132 : op.dj32, v, z, zout, dots->zold,
+                                         dots->part));
             return;
         }
         sweep(c, op, post_k, fp32, v, &z, &spare, zero, tmp, o->ordering);
@@ -721,41 +751,42 @@ void apply_two_stage(msrsb_ctx *c, const msrsb_solve_opts *o, const double *v, d
         launch_fill(s, n, zout, 0.0);
     else if (z != zout)
         launch_copy(s, n, z, zout);
-    if (dots)
-        launch_dots_beta(s, n, v, zout, dots->zold, dots->part, dots->scal, dots->part_rr,
-                         dots->host_out, dots->tag);
+    if (dots) finish(launch_dots(s, n, v, zout, dots->zold, dots->part));
 }
 
-// Wait until the device has tagged the r.r mailbox mb with iteration tag
-// (mb[2]).  Only plain reads of pinned memory while the device works: a
+// Wait until the mailbox mb (two values, the step's tag and the word of all
+// three, see post_mail) holds the post tagged `tag`; val receives the values.
+// Only plain reads of pinned memory while the device works: a
 // stream query puts a marker into the stream, and the barrier behind it
 // leaves the device idle for several microseconds.  After a second without
-// the tag the stream is queried, and if it has finished or failed without
-// the tag arriving the wait reports failure instead of spinning on.  One
-// Krylov step takes milliseconds at most, so a tag still missing after
+// the post the stream is queried, and if it has finished or failed without
+// the post arriving the wait reports failure instead of spinning on.  One
+// Krylov step takes milliseconds at most, so a post still missing after
 // kMailboxDeadline means the device is stuck: the wait gives up with an
 // error rather than holding the host forever.
 constexpr auto kMailboxDeadline = std::chrono::seconds(120);
 
-static bool wait_mailbox(hipStream_t s, volatile double *mb, int tag)
+static bool wait_mailbox(hipStream_t s, volatile double *mb, int tag, double (&val)[2])
 {
     const double want = tag;
+    auto arrived = [&] {
+        if (mb[2] != want) return false;
+        val[0] = mb[0];
+        val[1] = mb[1];
+        const unsigned long long w = *reinterpret_cast<volatile unsigned long long *>(mb + 3);
+        return w == mail_word(val[0], val[1], want);
+    };
     const auto start = std::chrono::steady_clock::now();
     auto t0 = start;
     for (unsigned spin = 1;; ++spin) {
-        if (mb[2] == want) break;
+        if (arrived()) return true;
         if ((spin & 0xFFFFu) == 0 &&
             std::chrono::steady_clock::now() - t0 > std::chrono::seconds(1)) {
-            if (hipStreamQuery(s) != hipErrorNotReady) {
-                if (mb[2] == want) break;
-                return false;
-            }
+            if (hipStreamQuery(s) != hipErrorNotReady) return arrived();
             t0 = std::chrono::steady_clock::now();
             if (t0 - start > kMailboxDeadline) return false;
         }
     }
-    std::atomic_thread_fence(std::memory_order_acquire);
-    return true;
 }
 
 static msrsb_status read_scalars(msrsb_ctx *c, int first, int count)
@@ -766,8 +797,10 @@ static msrsb_status read_scalars(msrsb_ctx *c, int first, int count)
 }
 
 // Preconditioned CG with flexible beta.  f, x device pointers (x = x0 on entry).
-// Convergence of iteration k is read on the host while iteration k+1's
-// preconditioner is already queued, so the device never waits for the host.
+// r.r of iteration k is posted by the restriction of its preconditioner, and
+// the host queues iteration k+1 while the rest of iteration k (the coarse
+// solve, the post-sweeps and the next direction, 15 us and more) still runs,
+// so the device never waits for the host.
 msrsb_status pcg(msrsb_ctx *c, const double *f, double *x, const msrsb_solve_opts *o,
                  msrsb_solve_info *info, bool trans)
 {
@@ -790,10 +823,20 @@ msrsb_status pcg(msrsb_ctx *c, const double *f, double *x, const msrsb_solve_opt
     bool restart = true, queued = false;
     double *hist = info ? info->history : nullptr;
     const int hcap = info ? info->history_cap : 0;
-    PcgDots dots{zold, c->partials, sc, c->partials_rr, c->h_pinned + 8, 0};
-    // r.r, the breakdown flag and the iteration tag, written by the device
+    // r.r, the breakdown flag and the iteration tag, posted by the device
     volatile double *hmon = c->h_pinned + 8;
     hmon[2] = -1.0;
+    // r.z of step k in scal, and the partials of p.q behind those of the dots
+    auto rz = [](int k) { return S_RZ_SLOT + (k & 1); };
+    double *pq = c->partials + pq_offset(static_cast<size_t>(n));
+    int npq = 0;
+    PcgDots dots{};
+    dots.part = c->partials;
+    dots.sums.scal = sc;
+    dots.post.rr = c->partials_rr;
+    dots.post.nrr = (n + kBlock - 1) / kBlock;
+    dots.post.scal = sc;
+    dots.post.host_out = c->h_pinned + 8;
     while (it <= o->max_iter) {
         if (restart) {
             op_residual(s, n, op, f, x, r);
@@ -805,14 +848,18 @@ msrsb_status pcg(msrsb_ctx *c, const double *f, double *x, const msrsb_solve_opt
             if (rr <= thr2) { rc = MSRSB_OK; break; }
             if (it == o->max_iter) break;
             apply_two_stage(c, o, r, z, trans, nullptr);
-            launch_dot(s, n, r, z, c->partials, sc + S_RZ_OLD);
+            launch_dot(s, n, r, z, c->partials, sc + rz(it));
             launch_fill(s, 1, sc + S_BETA, 0.0);   // p = z
-            launch_fill(s, 1, sc + S_BREAK, 0.0);  // a queued-ahead step may have set it
+            launch_fill(s, 2, sc + S_BREAK, 0.0);  // a queued-ahead step may have set them
             restart = false;
             queued = false;
         }
         if (!queued) {
-            p_spmv(s, n, op, z, p, p2, q, c->partials, sc);
+            PcgSums first;
+            first.scal = sc;
+            first.rz_new = rz(it);
+            first.tag = it;
+            npq = p_spmv(s, n, op, z, p, p2, q, pq, first);
             std::swap(p, p2);
         }
         ++it;
@@ -821,24 +868,36 @@ msrsb_status pcg(msrsb_ctx *c, const double *f, double *x, const msrsb_solve_opt
         // the next step's p = z + beta p, q = A p, all queued while the host
         // waits for r.r (the last two touch neither x nor r, so their work is
         // merely dropped if this step turns out to be the last)
-        const UpdArgs upd{x, r, p, q, r2, c->partials_rr, sc};
+        const UpdArgs upd{x, r, p, q, r2, c->partials_rr, sc, pq, npq, rz(it - 1),
+                          static_cast<double>(it)};
         std::swap(r, r2);
         std::swap(z, zold);
-        dots.zold = zold;
-        dots.tag = it;
-        apply_two_stage(c, o, r, z, trans, &dots, &upd);
         queued = it < o->max_iter;
+        dots.zold = zold;
+        dots.last = !queued;
+        dots.sums.tag = dots.post.tag = it;
+        dots.sums.rz_old = rz(it - 1);
+        dots.sums.rz_new = rz(it);
+        apply_two_stage(c, o, r, z, trans, &dots, &upd);
         if (queued) {
-            p_spmv(s, n, op, z, p, p2, q, c->partials, sc);
+            npq = p_spmv(s, n, op, z, p, p2, q, pq, dots.sums);
             std::swap(p, p2);
         }
-        if (!wait_mailbox(s, hmon, it)) {
+        double mail[2];
+        if (!wait_mailbox(s, hmon, it, mail)) {
             c->err = "the device did not report the residual of a Krylov step";
             return MSRSB_E_HIP;
         }
-        const double rr = hmon[0], brk = hmon[1];
+        const double rr = mail[0];
+        // the step that broke down: this one, or the last one's beta
+        const int brk = static_cast<int>(mail[1]);
+        if (brk != 0 && brk < it) {
+            it = brk;
+            rc = MSRSB_E_BREAKDOWN;
+            break;
+        }
         if (hist && it < hcap) hist[it] = std::sqrt(rr) / fn;
-        if (brk != 0.0 || !std::isfinite(rr)) { rc = MSRSB_E_BREAKDOWN; break; }
+        if (brk != 0 || !std::isfinite(rr)) { rc = MSRSB_E_BREAKDOWN; break; }
         if (rr <= thr2) { restart = true; continue; }
         if (it >= o->max_iter) break;
     }
@@ -937,12 +996,13 @@ msrsb_status gmres(msrsb_ctx *c, const double *f, double *x, const msrsb_solve_o
             // j + 1 of H, g[j + 1 ..] and v_{j + 2}, none of which the solution
             // after step j uses
             if (j + 1 < m && it + 1 < o->max_iter) step(j + 1, it + 2);
-            if (!wait_mailbox(s, mbox[j & 1], it + 1)) {
+            double mail[2];
+            if (!wait_mailbox(s, mbox[j & 1], it + 1, mail)) {
                 c->err = "the device did not report the residual of a Krylov step";
                 return MSRSB_E_HIP;
             }
             ++it;
-            const double res = mbox[j & 1][0], den = mbox[j & 1][1];
+            const double res = mail[0], den = mail[1];
             if (hist && it < hcap) hist[it] = res / fn;
             if (!std::isfinite(res) || !(den > 0.0)) { brk = true; break; }
             if (res <= o->rtol * fn) { ++j; break; }

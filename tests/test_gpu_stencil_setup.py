@@ -118,3 +118,31 @@ def test_a_stored_zero_without_its_transposed_entry_is_not_symmetric(kind, m):
         data[keep][o]
     with pytest.raises(MsrsbError):
         _apply(_solver(B, bs), rng.standard_normal(A.shape[0]), (IC0, 1))
+
+
+# the coarse product's forms: one launch up to 640 coarse unknowns (11 rows of
+# 64 x 64 tiles, ragged last tiles), tiles and sums past that
+@pytest.mark.parametrize("blocks", [1, 16, 63, 64, 65, 320, 639, 640, 641, 700])
+def test_coarse_product_sizes(blocks):
+    """1D, non-overlapping supports: P is the block indicator and the
+    preconditioner without smoothing is P A_c^{-1} P^T; A_c is tridiagonal.
+    Tolerance: the inverse of a matrix of condition number below 10 and a sum
+    of at most 700 products, a few hundred roundings of 1.1e-16."""
+    from paper_1912_06934_amd import Msrsb
+    import torch
+    n = 3 * blocks
+    rng = np.random.default_rng(blocks)
+    off = -rng.uniform(0.2, 1.0, n - 1)
+    A = sp.diags([off, rng.uniform(2.5, 3.0, n), off], [-1, 0, 1]).tocsr()
+    A.sort_indices()
+    s = _solver(A, 1)
+    part = (np.arange(n) // 3).astype(np.int32)
+    s.set_coarse(blocks, part, np.arange(n + 1, dtype=np.int32), part, np.ones(n, dtype=np.uint8))
+    s.setup_basis(max_iter=1)
+    s.build_coarse()
+    P = sp.csr_matrix((np.ones(n), part, np.arange(n + 1)), shape=(n, blocks))
+    v = rng.standard_normal(n)
+    ref = P @ np.linalg.solve((P.T @ A @ P).toarray(), P.T @ v)
+    z = torch.empty(n, dtype=torch.float64, device="cuda")
+    s.apply(torch.from_numpy(v).cuda(), z, pre=(0, 0), post=(0, 0))
+    assert np.max(np.abs(z.cpu().numpy() - ref)) <= 1e-13 * np.max(np.abs(ref))
