@@ -322,6 +322,9 @@ struct msrsb_ctx {
     // two-stage preconditioner replaces the coarse inverse of this level
     msrsb_ctx *child = nullptr;
     bool dense_coarse = false;       // ac / acinv are allocated (last level)
+    bool child_full = false;         // every row of the child's pattern is the whole 27-node
+                                     // neighbourhood in the coarse grid (the box form writes it)
+    bool made_symmetric = false;     // (a child) the matrix was symmetric up to rounding only
     msrsb_basis_opts basis_opts = {};  // of the last setup_basis (used by the levels below)
     msrsb_solve_opts child_opts = {};  // the next level's apply options (set per solve)
 
@@ -467,6 +470,8 @@ struct RapBoxGeom {
 // neighbourhood gives A_c in the lexicographic coarse numbering
 bool rap_uses_box(const DiaOffsets &d, int pw, const RapBoxGeom *g);
 int rap_box_band(const RapBoxGeom &g);
+// the stored pairs A_ij, A_ji set to their mean; flag[0] = 1 if any differed
+void launch_symmetrise(hipStream_t s, int n, const int *rp, const int *ci, double *a, int *flag);
 void launch_rap(hipStream_t s, int n, int nc, int maxnb, const int *rrp, const int *rci,
                 bool fp32, const double *r64, const float *r32, const int *rp, const int *ci,
                 const double *a, const DiaOffsets &d, const double *ad, const int *prp,

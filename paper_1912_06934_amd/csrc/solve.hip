@@ -537,7 +537,8 @@ msrsb_status ensure_smoother(msrsb_ctx *c, const msrsb_solve_opts *o, bool trans
             return st;
         }
         for (int k : kinds) {
-            if (k == MSRSB_SMOOTH_IC0 && (!c->a_symmetric || !c->tri[ord].sym_pattern)) {
+            if (k == MSRSB_SMOOTH_IC0 &&
+                (!c->a_symmetric || c->made_symmetric || !c->tri[ord].sym_pattern)) {
                 c->err = "IC(0) needs a symmetric matrix";
                 return MSRSB_E_ARG;
             }
