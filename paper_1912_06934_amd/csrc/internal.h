@@ -591,6 +591,52 @@ __device__ inline void post_mail(double *__restrict__ box, double a, double b, d
                        __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// alpha = (r.z) / (p.q), 0 with a breakdown on p.q <= 0 or non-finite values
+__device__ inline double alpha_of(double rz, double pq, bool &bad)
+{
+    bad = !(pq > 0.0) || !isfinite(pq) || !isfinite(rz);
+    return bad ? 0.0 : rz / pq;
+}
+// flexible (Polak-Ribiere) beta = r.(z - z_old) / (r.z)_old, 0 with a
+// breakdown when not finite
+__device__ inline double beta_of(double rzdiff, double rz_old, bool &bad)
+{
+    const double b = rzdiff / rz_old;
+    bad = !isfinite(b);
+    return bad ? 0.0 : b;
+}
+
+// ---- PCG on small problems in one launch (k_small.hip) ----
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallRows = 2 * kSmallThreads;  // most rows: 2 per thread
+constexpr int kSmallCoarse = 64;               // most coarse unknowns: one tile of A_c^{-1}
+constexpr int kSmallSteps = 1024;              // steps per launch at most
+constexpr int kSmallDiags = 9;                 // most diagonals
+enum { kSmallDone = 0, kSmallMaxIter, kSmallBreakdown, kSmallMore };  // out[0]
+struct SmallPcg {
+    int n, nd, nc;
+    int off[kSmallDiags];
+    const double *ad;            // the operator's diagonals
+    const double *dpre, *dpost;  // the sweeps' diagonal inverses
+    int npre, npost;
+    bool coarse;                 // P (padded rows), R and the packed A_c^{-1}:
+    const double *p;
+    const uint16_t *pc;
+    const int *rrp, *rc;
+    const double *rv, *inv;
+    const double *f;
+    double *x;
+    double *state[3];            // r, z, p between launches
+    double *out;                 // code, step, f.f, r.r at exit, r.z, alpha's breakdown
+    double *hist;                // r.r of step it0 and of each after it
+    double rtol;
+    int it0, max_iter, steps;    // first step, the last allowed, most in this launch
+    bool fresh;                  // no state yet; the rest goes from launch to launch
+    bool bad_alpha;
+    double ff, rz;
+};
+void launch_pcg_small(hipStream_t s, const SmallPcg &a, int pw);
+
 // ---- DIA / fused PCG kernels (k_krylov.hip) ----
 void launch_dia_spmv(hipStream_t s, int n, const DiaOffsets &d, const double *a, const double *x,
                      double *y);

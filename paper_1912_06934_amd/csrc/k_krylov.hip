@@ -564,21 +564,6 @@ __device__ inline void sum_partials_block(int nb, const double *__restrict__ par
     }
 }
 
-// alpha = (r.z) / (p.q), 0 with a breakdown on p.q <= 0 or non-finite values
-__device__ inline double alpha_of(double rz, double pq, bool &bad)
-{
-    bad = !(pq > 0.0) || !isfinite(pq) || !isfinite(rz);
-    return bad ? 0.0 : rz / pq;
-}
-// flexible (Polak-Ribiere) beta = r.(z - z_old) / (r.z)_old, 0 with a
-// breakdown when not finite
-__device__ inline double beta_of(double rzdiff, double rz_old, bool &bad)
-{
-    const double b = rzdiff / rz_old;
-    bad = !isfinite(b);
-    return bad ? 0.0 : b;
-}
-
 // (the first step that breaks down is kept)
 __device__ inline void note_break(double *__restrict__ flag, double tag)
 {

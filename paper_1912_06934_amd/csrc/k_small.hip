@@ -1,0 +1,386 @@
+// PCG on small stencil problems in one launch: one work-group holds the whole
+// iteration, so a step costs work-group barriers and not kernel launches.
+//
+// A step on a few thousand rows is seven launches of 2 to 4 us each whatever
+// the size, of which the reads and the arithmetic are well below one.  Here
+// the vectors of the iteration live in registers (thread t has rows t and
+// t + T), neighbours are exchanged through two LDS buffers in turn (one
+// barrier per product or sweep), and sums go over the wavefront by DPP and
+// over the wavefronts through LDS.  With one row per thread (REG) the rows'
+// coefficients, P entries and the wavefront's part of R stay in registers as
+// well; with two the 128 registers a thread has do not hold them, and they are
+// read from the L2 in each product.  Bound by the barriers and the dependent
+// latencies between them.  Per step, no pre-sweep and one post-sweep / two and
+// two, launches against this kernel:
+//   32 x 32, 5 diagonals      20.3 / 28.8 us    4.2 /  6.0 us
+//   45 x 45, 5 diagonals      21.2 / 29.1      10.2 / 15.6
+//   10 x 10 x 10, 7 diagonals 22.2 / 31.0       6.5 /  9.2
+//   12 x 12 x 12, 7 diagonals 22.9 / 32.4      14.1 / 21.5
+// Four rows per thread were slower where P is wide (16 x 16 x 16: 24.2 / 34.1
+// us against 38.0 / 54.2) and little faster elsewhere (64 x 64: 21.7 / 29.9
+// against 17.5 / 27.4), and 256 coarse unknowns cost 20 us more than 64, so
+// the line lies at 2048 rows and 64 coarse unknowns.
+#include "internal.h"
+
+namespace msrsb {
+
+namespace {
+
+constexpr int kT = kSmallThreads;
+constexpr int kR = 6;       // entries of R a lane keeps
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v)
+{
+    union { double d; int i[2]; } a, b;
+    a.d = v;
+    b.i[0] = __builtin_amdgcn_update_dpp(0, a.i[0], CTRL, 0xf, 0xf, true);
+    b.i[1] = __builtin_amdgcn_update_dpp(0, a.i[1], CTRL, 0xf, 0xf, true);
+    return v + b.d;
+}
+// sum over each 16 lanes, the same bits in all of them
+__device__ __forceinline__ double row_sum(double v)
+{
+    v = dpp_add<0xB1>(v);   // lane ^ 1
+    v = dpp_add<0x4E>(v);   // lane ^ 2
+    v = dpp_add<0x141>(v);  // the other four of eight
+    return dpp_add<0x140>(v);  // the other eight of 16
+}
+__device__ __forceinline__ double lane_of(double v, int l)
+{
+    union { double d; int i[2]; } a;
+    a.d = v;
+    a.i[0] = __builtin_amdgcn_readlane(a.i[0], l);
+    a.i[1] = __builtin_amdgcn_readlane(a.i[1], l);
+    return a.d;
+}
+__device__ __forceinline__ double wave_sum(double v)
+{
+    v = row_sum(v);
+    return (lane_of(v, 0) + lane_of(v, 16)) + (lane_of(v, 32) + lane_of(v, 48));
+}
+
+// NDT: room for diagonals; PW: width of P's rows; RPT: rows per thread.
+template <int NDT, int PW, int RPT>
+__global__ __launch_bounds__(kT) void k_pcg_small(SmallPcg a)
+{
+    constexpr bool REG = RPT == 1;
+    extern __shared__ double lds[];
+    __shared__ double red[2][3][kT / 64];
+    const int n = a.n, T = blockDim.x, t = threadIdx.x, lane = t & 63, w = t >> 6, nw = T >> 6;
+    // lds: two exchange buffers, then the coarse vectors
+    double *const vc = lds + 2 * n, *const wc = vc + a.nc;
+    int cur = 0, phase = 0;
+    for (int e = t; e < 6 * (kT / 64); e += T) (&red[0][0][0])[e] = 0.0;  // (absent wavefronts)
+    __syncthreads();
+
+    double av[REG ? RPT : 1][NDT], pv[REG ? RPT : 1][PW], dpre[RPT], dpost[RPT];
+    unsigned pc[REG ? RPT : 1][PW / 2];
+    double x[RPT], r[RPT], z[RPT], p[RPT];
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+        const int i = t + k * T;
+        const bool in = i < n;
+        x[k] = in ? a.x[i] : 0.0;
+        dpre[k] = in && a.npre ? a.dpre[i] : 0.0;
+        dpost[k] = in && a.npost ? a.dpost[i] : 0.0;
+        r[k] = z[k] = p[k] = 0.0;
+        if (!a.fresh && in) {
+            r[k] = a.state[0][i];
+            z[k] = a.state[1][i];
+            p[k] = a.state[2][i];
+        }
+        if constexpr (REG) {
+#pragma unroll
+            for (int o = 0; o < NDT; ++o) {
+                const int q = i + a.off[o];
+                av[k][o] = in && o < a.nd && q >= 0 && q < n
+                               ? a.ad[static_cast<int64_t>(o) * n + i] : 0.0;
+            }
+            if (a.coarse) {
+#pragma unroll
+                for (int s = 0; s < PW; s += 2) {
+                    const int64_t e = static_cast<int64_t>(in ? i : 0) * PW + s;
+                    unsigned c0 = a.pc[e], c1 = a.pc[e + 1];
+                    pv[k][s] = in && c0 != 0xFFFFu ? a.p[e] : 0.0;
+                    pv[k][s + 1] = in && c1 != 0xFFFFu ? a.p[e + 1] : 0.0;
+                    c0 = c0 == 0xFFFFu ? 0 : c0;
+                    c1 = c1 == 0xFFFFu ? 0 : c1;
+                    pc[k][s / 2] = c0 | c1 << 16;
+                }
+            }
+        }
+    }
+    // the first entries of the wavefront's first row of R, and the thread's
+    // four of A_c^{-1} where each row has its 16 lanes
+    double rv[kR];
+    int rc[kR], r0 = 0, r1 = 0;
+    double m4[4];
+    const bool keep4 = a.coarse && a.nc <= T / 16;
+    if (a.coarse) {
+        if (w < a.nc) {
+            r0 = a.rrp[w];
+            r1 = a.rrp[w + 1];
+        }
+        if constexpr (REG) {
+#pragma unroll
+            for (int u = 0; u < kR; ++u) {
+                const int e = r0 + lane + 64 * u;
+                rv[u] = e < r1 ? a.rv[e] : 0.0;
+                rc[u] = e < r1 ? a.rc[e] : 0;
+            }
+        }
+        if (keep4) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                m4[b] = a.inv[min(t >> 4, a.nc - 1) * 64 + 4 * (t & 15) + b];
+            }
+        }
+    }
+
+    // (A y)_i of the thread's k-th row, y in the current exchange buffer; an
+    // offset that leaves the rows reads y_i with a zero coefficient
+    auto row_dot = [&](int k) {
+        int i = t + k * T < n ? t + k * T : 0;
+        asm volatile("" : "+v"(i));  // (addresses are formed anew, not kept)
+        const double *y = lds + cur;
+        double s = 0.0;
+#pragma unroll
+        for (int o = 0; o < NDT; ++o) {
+            if (!REG && o >= a.nd) break;
+            const int q = i + a.off[o];
+            const bool in = q >= 0 && q < n;
+            double c;
+            if constexpr (REG) c = av[k][o];
+            else c = in ? a.ad[o * n + i] : 0.0;
+            s += c * y[in ? q : i];
+        }
+        return s;
+    };
+    auto put = [&](const double (&v)[RPT]) {
+        cur = n - cur;
+#pragma unroll
+        for (int k = 0; k < RPT; ++k)
+            if (t + k * T < n) lds[cur + t + k * T] = v[k];
+        __syncthreads();
+    };
+    auto sums = [&](auto &v) {  // v: the threads' parts, then the totals
+        constexpr int NV = sizeof(v) / sizeof(double);
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+            const double s = wave_sum(v[q]);
+            if (lane == 0) red[phase][q][w] = s;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < NV; ++q) v[q] = row_sum(red[phase][q][lane & (kT / 64 - 1)]);
+        phase ^= 1;
+    };
+
+    double ff = a.ff;
+    if (a.fresh) {
+        double s[1] = {0.0};
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) {
+            const double fk = t + k * T < n ? a.f[t + k * T] : 0.0;
+            s[0] += fk * fk;
+        }
+        sums(s);
+        ff = s[0];
+    }
+    const double fn = ff == 0.0 ? 1.0 : sqrt(ff);
+    const double thr2 = (a.rtol * fn) * (a.rtol * fn);
+    auto residual = [&]() {  // r = f - A x, returns r.r
+        put(x);
+        double s[1] = {0.0};
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) {
+            r[k] = t + k * T < n ? a.f[t + k * T] - row_dot(k) : 0.0;
+            s[0] += r[k] * r[k];
+        }
+        sums(s);
+        return s[0];
+    };
+
+    int it = a.it0, code = kSmallMaxIter;
+    bool restart = a.fresh, leave = false, bad_alpha = a.bad_alpha;
+    double rz = a.rz, rr = 0.0;
+    for (;;) {
+        if (restart || leave) {
+            rr = residual();
+            if (leave) break;  // the true residual at exit
+            if (t == 0) a.hist[it - a.it0] = rr;
+            if (!isfinite(rr)) { code = kSmallBreakdown; break; }
+            if (rr <= thr2) { code = kSmallDone; break; }
+            if (it >= a.max_iter) break;
+        } else if (it - a.it0 == a.steps) {
+            code = kSmallMore;
+            break;
+        }
+        double zold[RPT];
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) zold[k] = z[k];
+        // z = B r
+        bool zero = true;
+        for (int s = 0; s < a.npre; ++s) {
+            if (!zero) put(z);
+#pragma unroll
+            for (int k = 0; k < RPT; ++k)
+                z[k] = zero ? dpre[k] * r[k] : z[k] + dpre[k] * (r[k] - row_dot(k));
+            zero = false;
+        }
+        if (a.coarse) {
+            if (zero) {
+                put(r);
+            } else {
+                put(z);
+                double res[RPT];
+#pragma unroll
+                for (int k = 0; k < RPT; ++k) res[k] = r[k] - row_dot(k);
+                put(res);
+            }
+            const double *y = lds + cur;
+            for (int j = w; j < a.nc; j += nw) {
+                const int e0 = j == w ? r0 : a.rrp[j], e1 = j == w ? r1 : a.rrp[j + 1];
+                double s = 0.0;
+                int e = e0 + lane;
+                if constexpr (REG) {
+                    if (j == w) {
+#pragma unroll
+                        for (int u = 0; u < kR; ++u) s += rv[u] * y[rc[u]];
+                        e += 64 * kR;
+                    }
+                }
+                for (; e + 192 < e1; e += 256) {
+                    double g[4], h[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        g[u] = a.rv[e + 64 * u];
+                        h[u] = y[a.rc[e + 64 * u]];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) s += g[u] * h[u];
+                }
+                for (; e < e1; e += 64) s += a.rv[e] * y[a.rc[e]];
+                s = wave_sum(s);
+                if (lane == 0) vc[j] = s;
+            }
+            __syncthreads();
+            // A_c^{-1} (its one tile, zero past nc), 16 lanes to a row
+            const int h = t & 15;
+            for (int j = t >> 4; j < a.nc; j += T >> 4) {
+                double s = 0.0;
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    s += (keep4 ? m4[b] : a.inv[j * 64 + 4 * h + b]) * vc[min(4 * h + b, a.nc - 1)];
+                s = row_sum(s);
+                if (h == 0) wc[j] = s;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < RPT; ++k) {
+                double s = 0.0;
+                int i = t + k * T < n ? t + k * T : 0;
+                asm volatile("" : "+v"(i));
+#pragma unroll
+                for (int q = 0; q < PW; ++q) {
+                    if constexpr (REG) {
+                        s += pv[k][q] * wc[(pc[k][q / 2] >> (16 * (q & 1))) & 0xFFFFu];
+                    } else {
+                        const unsigned c = a.pc[i * PW + q];
+                        const double v = a.p[i * PW + q];
+                        s += c != 0xFFFFu ? v * wc[c] : 0.0;
+                    }
+                }
+                z[k] = zero ? s : z[k] + s;
+            }
+            zero = false;
+        }
+        for (int s = 0; s < a.npost; ++s) {
+            if (!zero) put(z);
+#pragma unroll
+            for (int k = 0; k < RPT; ++k)
+                z[k] = zero ? dpost[k] * r[k] : z[k] + dpost[k] * (r[k] - row_dot(k));
+            zero = false;
+        }
+        double d[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) {
+            const bool in = t + k * T < n;
+            z[k] = zero || !in ? 0.0 : z[k];
+            d[0] += r[k] * z[k];
+            d[1] += r[k] * (z[k] - zold[k]);
+            d[2] += r[k] * r[k];
+        }
+        sums(d);
+        double beta = 0.0;
+        if (!restart) {
+            // (r.r of the step, known only here: its sum goes with the others')
+            if (t == 0) a.hist[it - a.it0] = d[2];
+            bool bad;
+            beta = beta_of(d[1], rz, bad);
+            const bool broken = bad_alpha || !isfinite(d[2]);
+            restart = !broken && d[2] <= thr2;
+            leave = broken || (!restart && (it >= a.max_iter || bad));
+            if (broken || (leave && it < a.max_iter)) code = kSmallBreakdown;
+            if (restart || leave) continue;
+        }
+        restart = false;
+        rz = d[0];
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) p[k] = beta == 0.0 ? z[k] : z[k] + beta * p[k];
+        put(p);
+        double q[RPT], s[1] = {0.0};
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) {
+            q[k] = t + k * T < n ? row_dot(k) : 0.0;
+            s[0] += p[k] * q[k];
+        }
+        sums(s);
+        const double alpha = alpha_of(rz, s[0], bad_alpha);
+        ++it;
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) {
+            x[k] += alpha * p[k];
+            r[k] -= alpha * q[k];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+        const int i = t + k * T;
+        if (i >= n) continue;
+        a.x[i] = x[k];
+        if (code == kSmallMore) {
+            a.state[0][i] = r[k];
+            a.state[1][i] = z[k];
+            a.state[2][i] = p[k];
+        }
+    }
+    if (t == 0) {
+        a.out[0] = code;
+        a.out[1] = it;
+        a.out[2] = ff;
+        a.out[3] = rr;
+        a.out[4] = rz;
+        a.out[5] = bad_alpha;
+    }
+}
+
+template <int NDT, int PW>
+void launch_small(hipStream_t s, const SmallPcg &a)
+{
+    const int T = std::min(kT, (a.n + 63) / 64 * 64);  // whole wavefronts
+    const size_t lds = (2 * static_cast<size_t>(a.n) + 2 * a.nc) * sizeof(double);  // 33 KB at most
+    if (a.n <= kT) k_pcg_small<NDT, PW, 1><<<1, T, lds, s>>>(a);
+    else k_pcg_small<NDT, PW, 2><<<1, T, lds, s>>>(a);
+}
+
+}  // namespace
+
+void launch_pcg_small(hipStream_t s, const SmallPcg &a, int pw)
+{
+    if (a.nd <= 5) pw == 8 ? launch_small<5, 8>(s, a) : launch_small<5, 4>(s, a);
+    else pw == 8 ? launch_small<9, 8>(s, a) : launch_small<9, 4>(s, a);
+}
+
+}  // namespace msrsb

@@ -797,6 +797,92 @@ static msrsb_status read_scalars(msrsb_ctx *c, int first, int count)
     return hipStreamSynchronize(c->stream) == hipSuccess ? MSRSB_OK : MSRSB_E_HIP;
 }
 
+// Whether PCG runs in one work-group (k_small.hip): a stencil operator with
+// Jacobi-type sweeps in FP64 and a coarse stage that is symmetric and dense,
+// up to the sizes at which that is faster (both sides' times stand there).
+static bool pcg_fits_small(const msrsb_ctx *c, const Op &op, const msrsb_solve_opts *o)
+{
+    auto diag = [](int k, int sweeps) {
+        return sweeps == 0 || k == MSRSB_SMOOTH_NONE || is_diag(k);
+    };
+    return op.d.n > 0 && op.d.n <= kSmallDiags && c->n <= kSmallRows && !o->fp32_smoother &&
+           diag(o->pre_smoother, o->pre_sweeps) && diag(o->post_smoother, o->post_sweeps) &&
+           (!o->use_multiscale ||
+            (!c->child && c->acinv_sym && c->nc <= kSmallCoarse && !c->p_is32 && c->pcol16 &&
+             (c->pw == 4 || c->pw == 8)));
+}
+
+static msrsb_status pcg_small(msrsb_ctx *c, const Op &op, const double *f, double *x,
+                              const msrsb_solve_opts *o, msrsb_solve_info *info, bool trans)
+{
+    hipStream_t s = c->stream;
+    SmallPcg a{};
+    a.n = c->n;
+    a.nd = op.d.n;
+    for (int k = 0; k < a.nd; ++k) a.off[k] = op.d.off[k];
+    a.ad = op.ad;
+    auto dinv = [&](int k) { return k == MSRSB_SMOOTH_L1JACOBI ? op.dl1 : op.dj; };
+    a.npre = is_diag(o->pre_smoother) ? o->pre_sweeps : 0;
+    a.npost = is_diag(o->post_smoother) ? o->post_sweeps : 0;
+    a.dpre = dinv(o->pre_smoother);
+    a.dpost = dinv(o->post_smoother);
+    if (trans) {
+        std::swap(a.npre, a.npost);
+        std::swap(a.dpre, a.dpost);
+    }
+    a.coarse = o->use_multiscale != 0;
+    if (a.coarse) {
+        a.nc = c->nc;
+        a.p = c->p64[c->pcur];
+        a.pc = c->pcol16;
+        a.rrp = c->rrp;
+        a.rc = c->rci;
+        a.rv = c->r64;
+        a.inv = c->acinv_pk;
+    }
+    a.f = f;
+    a.x = x;
+    for (int k = 0; k < 3; ++k) a.state[k] = c->w[k];
+    a.out = c->scal;
+    a.hist = c->partials;
+    a.rtol = o->rtol;
+    a.max_iter = o->max_iter;
+    a.steps = kSmallSteps;
+    a.fresh = true;
+    double *hist = info ? info->history : nullptr;
+    const int hcap = info ? info->history_cap : 0;
+    for (;;) {
+        launch_pcg_small(s, a, a.coarse ? c->pw : 4);
+        if (read_scalars(c, 0, 6)) return MSRSB_E_HIP;
+        const double *out = c->h_pinned;
+        const int code = static_cast<int>(out[0]), it = static_cast<int>(out[1]);
+        const double fn = out[2] == 0.0 ? 1.0 : std::sqrt(out[2]);
+        const int m = hist ? std::min(it + 1, hcap) - a.it0 : 0;
+        if (m > 0) {
+            // (each step's entry, the last one's not yet where more follow)
+            if (hipMemcpy(hist + a.it0, a.hist, m * sizeof(double), hipMemcpyDeviceToHost) !=
+                hipSuccess)
+                return MSRSB_E_HIP;
+            for (int k = 0; k < m; ++k) hist[a.it0 + k] = std::sqrt(hist[a.it0 + k]) / fn;
+        }
+        if (code == kSmallMore) {
+            a.it0 = it;
+            a.ff = out[2];
+            a.rz = out[4];
+            a.bad_alpha = out[5] != 0.0;
+            a.fresh = false;
+            continue;
+        }
+        if (info) {
+            info->iters = it;
+            info->true_rel_res = std::sqrt(out[3]) / fn;
+        }
+        return code == kSmallDone      ? MSRSB_OK
+               : code == kSmallMaxIter ? MSRSB_E_NOT_CONVERGED
+                                       : MSRSB_E_BREAKDOWN;
+    }
+}
+
 // Preconditioned CG with flexible beta.  f, x device pointers (x = x0 on entry).
 // r.r of iteration k is posted by the restriction of its preconditioner, and
 // the host queues iteration k+1 while the rest of iteration k (the coarse
@@ -808,6 +894,7 @@ msrsb_status pcg(msrsb_ctx *c, const double *f, double *x, const msrsb_solve_opt
     hipStream_t s = c->stream;
     const int n = c->n;
     const Op op = fine_op(c, trans);
+    if (pcg_fits_small(c, op, o)) return pcg_small(c, op, f, x, o, info, trans);
     // r and p each alternate between two buffers: the kernels that update
     // them read the old values at neighbouring rows
     double *r = c->w[0], *z = c->w[1], *zold = c->w[2], *p = c->w[3], *q = c->w[4],
