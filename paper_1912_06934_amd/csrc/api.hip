@@ -1526,7 +1526,8 @@ msrsb_status msrsb_setup_basis(msrsb_ctx *c, const msrsb_basis_opts *o, msrsb_ba
     const SplitRows &pg = c->psplit;
     const int gx = pg.nx, gxy = pg.nx * pg.ny;
     phase_begin(c, MSRSB_PHASE_SMOOTH);
-    const bool split = pg.tab && o->max_iter > 0 && jsym && c->jw == 7 && c->pw == 8 &&
+    const bool small = smooth_fits_small(sa, fp32);
+    const bool split = !small && pg.tab && o->max_iter > 0 && jsym && c->jw == 7 && c->pw == 8 &&
                        c->jmap_kind == 1 && static_cast<int64_t>(gxy) * pg.nz == c->n &&
                        c->j_off.off[0] == -gxy && c->j_off.off[1] == -gx &&
                        c->j_off.off[2] == -1 && c->j_off.off[3] == 0 && c->j_off.off[4] == 1 &&
@@ -1544,17 +1545,31 @@ msrsb_status msrsb_setup_basis(msrsb_ctx *c, const msrsb_basis_opts *o, msrsb_ba
     float *const *q32 = split ? c->ps32 : c->p32;
     int it = 0;
     double e_last = -1.0;
+    // without a tolerance only the last e_it is looked at (and a value that is
+    // not finite stays so), so the earlier ones are not formed: each costs its
+    // reduction, 4.5 us, and its part of the kernel
+    auto checked = [&](int k) {
+        return k % o->check_every == 0 &&
+               (o->tol >= 0.0 || k + static_cast<int64_t>(o->check_every) >= o->max_iter);
+    };
+    sa.eit_out = c->eit_val;
     for (it = 0; it < o->max_iter; ++it) {
-        // without a tolerance only the last e_it is looked at (and a value
-        // that is not finite stays so), so the earlier ones are not formed:
-        // each costs its reduction, 4.5 us, and its part of the kernel
-        const bool check = it % o->check_every == 0 &&
-                           (o->tol >= 0.0 || it + static_cast<int64_t>(o->check_every) >= o->max_iter);
-        sa.eit_part = check ? c->partials : nullptr;
-        sa.eit_out = c->eit_val;
         const int src = c->pcur, dst = 1 - c->pcur;
-        launch_smooth(s, sa, fp32, c->jv, c->jv32, q64[src], q64[dst], q32[src], q32[dst]);
-        c->pcur = dst;
+        bool check = checked(it);
+        if (small) {
+            // up to the next step whose e_it the host reads, or the end
+            int last = it, eit = check ? 0 : -1;
+            while (last + 1 < o->max_iter && !(o->tol >= 0.0 && checked(last)))
+                if (checked(++last)) eit = last - it;
+            launch_smooth_small(s, sa, fp32, c->jv, c->jv32, c->p64[src], c->p32[src],
+                                last - it + 1, eit);
+            check = checked(last);
+            it = last;
+        } else {
+            sa.eit_part = check ? c->partials : nullptr;
+            launch_smooth(s, sa, fp32, c->jv, c->jv32, q64[src], q64[dst], q32[src], q32[dst]);
+            c->pcur = dst;
+        }
         if (check && o->tol >= 0.0) {
             hipMemcpyAsync(c->h_pinned, c->eit_val, sizeof(double), hipMemcpyDeviceToHost, s);
             if (hipStreamSynchronize(s) != hipSuccess)

@@ -636,6 +636,11 @@ struct SmallPcg {
     double ff, rz;
 };
 void launch_pcg_small(hipStream_t s, const SmallPcg &a, int pw);
+// steps of the smoothing iteration on P in place, in one launch, where it
+// fits; eit_step (-1: none) forms e_it
+bool smooth_fits_small(const SmoothArgs &a, bool fp32);
+void launch_smooth_small(hipStream_t s, const SmoothArgs &a, bool fp32, const double *jv64,
+                         const float *jv32, double *p64, float *p32, int steps, int eit_step);
 
 // ---- DIA / fused PCG kernels (k_krylov.hip) ----
 void launch_dia_spmv(hipStream_t s, int n, const DiaOffsets &d, const double *a, const double *x,

@@ -22,6 +22,9 @@
 // the line lies at 2048 rows and 64 coarse unknowns.
 #include "internal.h"
 
+#include <algorithm>
+#include <type_traits>
+
 namespace msrsb {
 
 namespace {
@@ -366,6 +369,134 @@ __global__ __launch_bounds__(kT) void k_pcg_small(SmallPcg a)
     }
 }
 
+// Smoothing of P on small problems, all steps in one launch (the arithmetic of
+// k_smooth_map, in its order): P lies in LDS, slot-major and with a zero row
+// for absent slots, in two buffers in turn; a thread keeps its rows' weights
+// and, two to a register, the places of its neighbours' slots.  Bound by the
+// LDS reads, one per coefficient and slot, against a launch per step before:
+// see smooth_fits_small.
+template <typename T, int NDT, int PW, int RPT>
+__global__ __launch_bounds__(kT) void k_smooth_small(SmoothArgs a, const T *__restrict__ jv,
+                                                     T *__restrict__ p, int steps, int eit_step)
+{
+    extern __shared__ char lds_raw[];
+    __shared__ double red[kT / 64];
+    T *const lds = reinterpret_cast<T *>(lds_raw);
+    const int n = a.n, W = blockDim.x, t = threadIdx.x, lane = t & 63;
+    const int half = (PW + 1) * n;  // one buffer
+    const uint8_t *jmap = static_cast<const uint8_t *>(a.jmap_idx);
+    T w[RPT][NDT];
+    unsigned at[RPT][NDT][PW / 2];
+    bool inner[RPT];
+    const int mid = a.jw / 2;
+#pragma unroll
+    for (int q = 0; q < RPT; ++q) {
+        const int i = t + q * W;
+        const bool in = i < n;
+        const T si = in && a.sym ? jv[static_cast<int64_t>(mid) * n + i] : T(0);
+        inner[q] = in && a.interior[in ? i : 0] != 0;
+#pragma unroll
+        for (int o = 0; o < NDT; ++o) {
+            const bool have = in && o < a.jw;
+            const int64_t e = static_cast<int64_t>(o) * n + i;
+            const uint32_t m = have ? a.jmap_tab[jmap[e]] : 0xFFFFFFFFu;
+            int k = !have ? 0 : a.jcol ? a.jcol[e] : i + a.joff.off[o];
+            const bool inside = k >= 0 && k < n;
+            w[q][o] = T(0);
+            if (have && !a.sym) w[q][o] = jv[e];
+            if (have && a.sym) {
+                if (o < mid)
+                    w[q][o] = inside ? si * jv[static_cast<int64_t>(a.jw - 1 - o) * n + k] : T(0);
+                else if (o == mid)
+                    w[q][o] = si == T(0) ? T(1) : static_cast<T>(1.0 - a.omega);
+                else
+                    w[q][o] = si * jv[e];
+            }
+            if (!inside) k = in ? i : 0;
+#pragma unroll
+            for (int s = 0; s < PW; s += 2) {
+                const int c0 = min(static_cast<int>(m >> (4 * s) & 0xFu), PW);
+                const int c1 = min(static_cast<int>(m >> (4 * s + 4) & 0xFu), PW);
+                at[q][o][s / 2] = static_cast<unsigned>(c0 * n + k) |
+                                  static_cast<unsigned>(c1 * n + k) << 16;
+            }
+        }
+        if (!in) continue;
+#pragma unroll
+        for (int s = 0; s < PW; ++s) lds[s * n + i] = p[static_cast<int64_t>(i) * PW + s];
+        lds[PW * n + i] = lds[half + PW * n + i] = T(0);
+    }
+    int cur = 0;
+    for (int step = 0; step < steps; ++step) {
+        __syncthreads();
+        const T *from = lds + cur;
+        T *to = lds + (half - cur);
+        double emax = 0.0;
+#pragma unroll
+        for (int q = 0; q < RPT; ++q) {
+            const int i = t + q * W;
+            T acc[PW];
+#pragma unroll
+            for (int s = 0; s < PW; ++s) acc[s] = T(0);
+#pragma unroll
+            for (int o = 0; o < NDT; ++o) {  // (past a.jw: zeros)
+#pragma unroll
+                for (int s = 0; s < PW; ++s)
+                    acc[s] += w[q][o] * from[at[q][o][s / 2] >> (16 * (s & 1)) & 0xFFFFu];
+            }
+            if (i >= n) continue;
+            double rs = 0.0;
+#pragma unroll
+            for (int s = 0; s < PW; ++s) rs += static_cast<double>(acc[s]);
+            const double rinv = 1.0 / rs;
+#pragma unroll
+            for (int s = 0; s < PW; ++s) {
+                if (step == eit_step && inner[q]) {
+                    const double dlt = fabs(static_cast<double>(acc[s]) -
+                                            static_cast<double>(from[s * n + i]));
+                    emax = (dlt > emax || dlt != dlt) ? dlt : emax;
+                }
+                to[s * n + i] = static_cast<T>(static_cast<double>(acc[s]) * rinv);
+            }
+        }
+        cur = half - cur;
+        if (step != eit_step) continue;
+        auto larger = [](double x, double y) { return (y > x || y != y) ? y : x; };
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) emax = larger(emax, __shfl_xor(emax, off, 64));
+        if (lane == 0) red[t >> 6] = emax;
+        __syncthreads();
+        if (t == 0) {
+            for (int u = 1; u < W >> 6; ++u) emax = larger(emax, red[u]);
+            a.eit_out[0] = emax;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < RPT; ++q) {
+        const int i = t + q * W;
+        if (i >= n) continue;
+#pragma unroll
+        for (int s = 0; s < PW; ++s) p[static_cast<int64_t>(i) * PW + s] = lds[cur + s * n + i];
+    }
+}
+
+template <typename T, int NDT, int PW>
+void smooth_small(hipStream_t s, const SmoothArgs &a, const T *jv, T *p, int steps, int eit_step)
+{
+    const int W = std::min(kT, (a.n + 63) / 64 * 64);
+    const int lds = 2 * (PW + 1) * a.n * static_cast<int>(sizeof(T));
+    auto go = [&](auto kern) {
+        if (lds > 60000)
+            hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        kern<<<1, W, lds, s>>>(a, jv, p, steps, eit_step);
+    };
+    if constexpr (PW == 4) {
+        if (a.n > kT) return go(k_smooth_small<T, NDT, PW, 2>);
+    }
+    go(k_smooth_small<T, NDT, PW, 1>);
+}
+
 template <int NDT, int PW>
 void launch_small(hipStream_t s, const SmallPcg &a)
 {
@@ -376,6 +507,38 @@ void launch_small(hipStream_t s, const SmallPcg &a)
 }
 
 }  // namespace
+
+// 100 steps, launch by launch against one launch, set-up of J and the
+// statistics included (FP64 / FP32):
+//   32 x 32, 5 slots of J, rows of 4      0.46 / 0.42 ms   0.14 / 0.13 ms
+//   45 x 43, 5 slots, rows of 4           0.48 / 0.47      0.22 / 0.21
+//   10 x 10 x 10, 7 slots, rows of 8      0.67 / 0.59      0.36 / 0.24
+// The limits are LDS (two buffers) and registers: two rows per thread of 8
+// slots, or 9 slots of J by 8, would be held in scratch memory.
+bool smooth_fits_small(const SmoothArgs &a, bool fp32)
+{
+    return a.n <= (a.pw == 8 ? kSmallThreads : kSmallRows) && (a.pw == 4 || a.pw == 8) &&
+           a.jw <= (a.pw == 8 ? 7 : kSmallDiags) && a.jmap_kind == 1 &&
+           2 * (a.pw + 1) * a.n * (fp32 ? 4 : 8) <= 155000;  // of 160 KB of LDS
+}
+
+void launch_smooth_small(hipStream_t s, const SmoothArgs &a, bool fp32, const double *jv64,
+                         const float *jv32, double *p64, float *p32, int steps, int eit_step)
+{
+    auto go = [&](auto nd, auto pw) {
+        constexpr int N = decltype(nd)::value, PW = decltype(pw)::value;
+        if (fp32) smooth_small<float, N, PW>(s, a, jv32, p32, steps, eit_step);
+        else smooth_small<double, N, PW>(s, a, jv64, p64, steps, eit_step);
+    };
+    typedef std::integral_constant<int, 4> c4;
+    typedef std::integral_constant<int, 5> c5;
+    typedef std::integral_constant<int, 7> c7;
+    typedef std::integral_constant<int, 8> c8;
+    typedef std::integral_constant<int, 9> c9;
+    if (a.jw <= 5) a.pw == 8 ? go(c5{}, c8{}) : go(c5{}, c4{});
+    else if (a.jw <= 7) a.pw == 8 ? go(c7{}, c8{}) : go(c7{}, c4{});
+    else go(c9{}, c4{});
+}
 
 void launch_pcg_small(hipStream_t s, const SmallPcg &a, int pw)
 {

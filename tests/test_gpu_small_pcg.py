@@ -157,3 +157,41 @@ def test_more_steps_than_a_launch():
     np.testing.assert_allclose(h[:201], ref, rtol=1e-6)
     step = np.abs(np.diff(np.log(h[900:1150])))
     assert step[[123, 124, 125]].max() <= 2.0 * step.max() and step[120:130].max() < 1.0
+
+
+@pytest.mark.parametrize("n,offs,wide", [
+    (1, (), False), (64, (1, 8), True), (65, (1, 8), False), (1000, (1, 37), False),
+    (1024, (1, 30), True), (1024, (1, 7, 80, 81), True), (1025, (1, 7, 80), True),
+    (1025, (1, 7, 80, 81), False), (1900, (1, 45), False), (1937, (1, 13, 200), False),
+    (1938, (1, 13, 200), False), (2048, (1, 45), False)], ids=str)
+@pytest.mark.parametrize("unsym", [False, True], ids=["symmetric", "unsymmetric"])
+def test_smoothing_against_oracle(n, offs, wide, unsym):
+    """The basis after a fixed number of steps, checked or not, and to a
+    tolerance: the steps add at most nine products, each step divides by a row
+    sum of order one, so 40 steps differ by 1e-12 at most (FP32: the same
+    argument with its precision, 1e-4)."""
+    from paper_1912_06934_amd import Msrsb
+    A = _stencil(n, offs, np.random.default_rng(n + 2))
+    if unsym:
+        A.data *= 1.0 + 0.3 * (A.indices > np.repeat(np.arange(n), np.diff(A.indptr)))
+    rp, ci, a = A.indptr.astype(np.int32), A.indices.astype(np.int32), A.data
+    coarse = _coarse(n, max(1, min(n // 40, 60)), wide)
+    # rows that no check looks at
+    coarse[4][::7] = 0
+    s = Msrsb(device=0)
+    s.set_matrix(rp, ci, a)
+    s.set_coarse(*coarse)
+    jv, _ = oracle.filter_jacobi(rp, ci, a)
+    pv0 = oracle.init_basis(coarse[2], coarse[3], coarse[1])
+    for kmax, tol, every in ((1, -1.0, 1), (40, -1.0, 1), (40, -1.0, 7), (40, 1e-2, 1),
+                             (40, 1e-2, 3), (5, -1.0, 9)):
+        pv, it, e, _ = oracle.basis(rp, ci, jv, coarse[2], coarse[3], pv0, coarse[4], kmax=kmax,
+                                    tol=tol, nit=every)
+        info = s.setup_basis(max_iter=kmax, tol=tol, check_every=every)
+        assert info["iters"] == it
+        assert np.max(np.abs(s.get_prolongation()[2] - pv)) <= 1e-12
+        if every <= kmax:
+            assert abs(info["e_it"] - e) <= 1e-12
+    s.setup_basis(max_iter=40, fp32_basis=True)
+    pv = oracle.basis(rp, ci, jv, coarse[2], coarse[3], pv0, coarse[4], kmax=40)[0]
+    assert np.max(np.abs(s.get_prolongation()[2] - pv)) <= 1e-4
