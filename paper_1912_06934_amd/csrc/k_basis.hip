@@ -698,6 +698,145 @@ __global__ __launch_bounds__(kBlock) void k_smooth_map(
     if (eit_part != nullptr) eit_block(emax, eit_part);
 }
 
+// The smoothing step for a J of 27 diagonals in nine lines of three, offsets
+// base - s, base, base + s (trilinear elements, s components per node, and the
+// 27-point stencil, s = 1), rows of 8 slots.
+//
+// Read row by row, a wavefront's neighbour rows make four loads that each touch
+// every one of its cache lines: 80 L1 accesses a row, which kept the L1 busy
+// for four fifths of the time.  Here a work-group reads a line's rows (its own,
+// s more on either side) once and in consecutive places, while the line before
+// is worked on, and its three neighbours take them from LDS: 126 -> 66 us a
+// step at 824k rows in FP64 (4.6 TB/s), 15.8 -> 11.2 us at 14k rows in FP32.
+// The rows stand LD entries apart (odd, so that a slot of 32 rows lies in
+// different banks), the ninth entry zero for absent slots; the map table holds
+// each slot's byte offset.  Sums as in k_smooth_map.
+// Bound by the memory traffic (J is half of it) and the LDS reads.
+template <typename T, bool SYM>
+__global__ __launch_bounds__(kBlock) void k_smooth_lines(
+    int n, DiaOffsets joff, const T *__restrict__ jv, const uint8_t *__restrict__ jmap,
+    const uint32_t *__restrict__ tab, int ntab, const T *__restrict__ pin, T *__restrict__ pout,
+    const uint8_t *__restrict__ interior, double *__restrict__ eit_part, double omega)
+{
+    constexpr int PW = 8, NL = 9, MID = 13, LD = PW + 1, SMAX = 3;
+    constexpr int L = 16 / sizeof(T), CH = PW / L;  // 16-byte pieces of a row
+    constexpr int K = ((kBlock + 2 * SMAX) * CH + kBlock - 1) / kBlock;
+    typedef T vec __attribute__((ext_vector_type(L)));
+    __shared__ uint64_t stab[256];
+    __shared__ T rows[(kBlock + 2 * SMAX) * LD];
+    const int t = threadIdx.x, s = joff.off[1] - joff.off[0];
+    const int row0 = xcd_group(blockIdx.x, gridDim.x) * kBlock, i = row0 + t;
+    const int ic = i < n ? i : n - 1;
+    const int pieces = (kBlock + 2 * s) * CH;
+    vec next[K];
+    T w[3];
+    int m[3];
+    auto fetch = [&](int g) {
+        const int first = row0 + joff.off[3 * g];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int p = min(t + k * kBlock, pieces - 1), r = p / CH, c = p % CH;
+            // (rows outside the matrix are no one's neighbours)
+            const int at = min(max(first + r, 0), n - 1);
+            next[k] = reinterpret_cast<const vec *>(pin + static_cast<int64_t>(at) * PW)[c];
+        }
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            const int o = 3 * g + u;
+            const int64_t e = static_cast<int64_t>(o) * n + ic;
+            m[u] = jmap[e];
+            if constexpr (SYM) {
+                const int kn = ic + joff.off[o];
+                const bool in = kn >= 0 && kn < n;
+                w[u] = o < MID ? jv[static_cast<int64_t>(26 - o) * n + (in ? kn : ic)] : jv[e];
+                if (o < MID && !in) w[u] = T(0);
+            } else {
+                w[u] = jv[e];
+            }
+        }
+    };
+    T si = T(0);
+    if constexpr (SYM) si = jv[static_cast<int64_t>(MID) * n + ic];
+    fetch(0);
+    for (int q = t; q < ntab; q += kBlock) {
+        const uint32_t mq = tab[q];
+        uint64_t b = 0;
+#pragma unroll
+        for (int sl = 0; sl < PW; ++sl)
+            b |= static_cast<uint64_t>(min(mq >> (4 * sl) & 0xFu, 8u) * sizeof(T)) << (8 * sl);
+        stab[q] = b;
+    }
+    for (int r = t; r < kBlock + 2 * SMAX; r += kBlock) rows[r * LD + PW] = T(0);
+    T acc[PW];
+#pragma unroll
+    for (int sl = 0; sl < PW; ++sl) acc[sl] = T(0);
+#pragma nounroll
+    for (int g = 0; g < NL; ++g) {
+        __syncthreads();  // the line before is done with
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int p = t + k * kBlock;
+            if (p < pieces) {
+#pragma unroll
+                for (int l = 0; l < L; ++l) rows[p / CH * LD + p % CH * L + l] = next[k][l];
+            }
+        }
+        __syncthreads();
+        T wg[3];
+        uint64_t mg[3];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            wg[u] = w[u];
+            if constexpr (SYM) {
+                const int o = 3 * g + u;
+                wg[u] = o == MID ? (si == T(0) ? T(1) : static_cast<T>(1.0 - omega)) : si * w[u];
+            }
+            mg[u] = stab[m[u]];
+        }
+        if (g + 1 < NL) fetch(g + 1);
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            const char *row = reinterpret_cast<const char *>(rows + (t + u * s) * LD);
+            const uint32_t lo = static_cast<uint32_t>(mg[u]), hi = static_cast<uint32_t>(mg[u] >> 32);
+#pragma unroll
+            for (int sl = 0; sl < PW; ++sl) {
+                const uint32_t b = (sl < 4 ? lo >> (8 * sl) : hi >> (8 * sl - 32)) & 0xFFu;
+                acc[sl] += wg[u] * *reinterpret_cast<const T *>(row + b);
+            }
+        }
+    }
+    double rs = 0.0;
+#pragma unroll
+    for (int sl = 0; sl < PW; ++sl) rs += static_cast<double>(acc[sl]);
+    const double rinv = 1.0 / rs;
+    const bool inner = eit_part != nullptr && i < n && interior[ic] != 0;
+    double emax = 0.0;
+    __syncthreads();
+#pragma unroll
+    for (int sl = 0; sl < PW; ++sl) {
+        if (inner) {
+            const double old = static_cast<double>(pin[static_cast<int64_t>(i) * PW + sl]);
+            const double dlt = fabs(static_cast<double>(acc[sl]) - old);
+            emax = (dlt > emax || dlt != dlt) ? dlt : emax;
+        }
+        rows[t * LD + sl] = static_cast<T>(static_cast<double>(acc[sl]) * rinv);
+    }
+    __syncthreads();
+    // whole cache lines leave, in FP64 past the L2 (see k_smooth_map)
+#pragma unroll
+    for (int k = 0; k < CH; ++k) {
+        const int p = t + k * kBlock, r = p / CH, c = p % CH;
+        vec x;
+#pragma unroll
+        for (int l = 0; l < L; ++l) x[l] = rows[r * LD + c * L + l];
+        vec *at = reinterpret_cast<vec *>(pout + static_cast<int64_t>(row0 + r) * PW) + c;
+        if (row0 + r >= n) continue;
+        if constexpr (sizeof(T) == 8) __builtin_nontemporal_store(x, at);
+        else *at = x;
+    }
+    if (eit_part != nullptr) eit_block(emax, eit_part);
+}
+
 // Fallback for rows wider than the slot maps allow: row i's pattern (W
 // slots) in registers, every entry of every neighbour row compared against it.
 template <typename T, int W>
@@ -962,9 +1101,35 @@ void smooth_map_launch(hipStream_t s, const SmoothArgs &a, const T *jv, const T 
         a.jmap_ntab, pin, pout, a.interior, a.eit_part, a.omega, a.go, SplitRows{});
 }
 
+// J's diagonals come as k_smooth_lines takes them
+static bool smooth_in_lines(const SmoothArgs &a)
+{
+    if (a.jw != 27 || a.joff.n != 27 || a.jcol) return false;
+    const int st = a.joff.off[1] - a.joff.off[0];
+    bool ok = st >= 1 && st <= 3 && a.joff.off[13] == 0;
+    for (int g = 0; g < 9; ++g)
+        ok = ok && a.joff.off[3 * g + 1] - a.joff.off[3 * g] == st &&
+             a.joff.off[3 * g + 2] - a.joff.off[3 * g + 1] == st;
+    return ok;
+}
+
 template <typename T, typename IDX, int PW>
 void smooth_map_pw(hipStream_t s, const SmoothArgs &a, const T *jv, const T *pin, T *pout)
 {
+    if constexpr (sizeof(IDX) == 1 && PW == 8) {
+        if (smooth_in_lines(a)) {
+            const uint8_t *jmap = static_cast<const uint8_t *>(a.jmap_idx);
+            if (a.sym)
+                k_smooth_lines<T, true><<<grid_n(a.n), kBlock, 0, s>>>(
+                    a.n, a.joff, jv, jmap, a.jmap_tab, a.jmap_ntab, pin, pout, a.interior,
+                    a.eit_part, a.omega);
+            else
+                k_smooth_lines<T, false><<<grid_n(a.n), kBlock, 0, s>>>(
+                    a.n, a.joff, jv, jmap, a.jmap_tab, a.jmap_ntab, pin, pout, a.interior,
+                    a.eit_part, a.omega);
+            return;
+        }
+    }
     if constexpr (sizeof(IDX) == 1) {
         // the slot counts of 1D, 2D and 3D stencils and of the 27-point
         // same-component pattern of trilinear elements
