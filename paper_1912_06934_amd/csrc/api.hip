@@ -223,6 +223,7 @@ void free_coarse(msrsb_ctx *c)
     c->jmap_idx = nullptr;
     dfree(c->jmap_tab);
     c->jmap_kind = 0;
+    c->j_grid_nx = 0;
     c->jmap_ntab = 0;
     c->pw = 0;
     c->has_coarse = c->has_basis = c->has_coarse_op = false;
@@ -1288,6 +1289,20 @@ msrsb_status msrsb_set_coarse(msrsb_ctx *c, int32_t nc, const int32_t *part,
             dfree(dmaps);
             return fail(c, MSRSB_E_HIP, "building the slot maps failed");
         }
+        // J on a 2D grid: offsets to the neighbours of a row x + nx y, and no
+        // coupling across a line's ends
+        if (c->j_dia && (c->jw == 5 || c->jw == 9)) {
+            const int jw = c->jw, nx = c->j_off.off[jw - 1] - (jw == 9 ? 1 : 0);
+            bool grid = nx >= 16 && n % nx == 0 && n / nx >= 16;
+            for (int o = 0; o < jw && grid; ++o) {
+                const int dx = jw == 5 ? (o == 1 ? -1 : o == 3 ? 1 : 0) : o % 3 - 1;
+                const int dy = jw == 5 ? (o == 0 ? -1 : o == 4 ? 1 : 0) : o / 3 - 1;
+                grid = c->j_off.off[o] == dx + nx * dy;
+                for (int i = dx < 0 ? 0 : nx - 1; i < n && dx != 0 && grid; i += nx)
+                    grid = hm[static_cast<size_t>(o) * n + i] == 0xFFFFFFFFu;
+            }
+            c->j_grid_nx = grid ? nx : 0;
+        }
         std::unordered_map<uint32_t, uint32_t> dict;
         std::vector<uint32_t> table;
         std::vector<uint16_t> idx(m);
@@ -1553,23 +1568,29 @@ msrsb_status msrsb_setup_basis(msrsb_ctx *c, const msrsb_basis_opts *o, msrsb_ba
                (o->tol >= 0.0 || k + static_cast<int64_t>(o->check_every) >= o->max_iter);
     };
     sa.eit_out = c->eit_val;
+    const int most = small ? INT32_MAX : std::max(smooth_tile_steps(sa, c->j_grid_nx), 1);
     for (it = 0; it < o->max_iter; ++it) {
         const int src = c->pcur, dst = 1 - c->pcur;
         bool check = checked(it);
+        // several steps a launch: up to the next one whose e_it the host reads,
+        // the most the launch takes, or the end
+        int last = it, eit = check ? 0 : -1;
+        while (last + 1 < o->max_iter && last + 1 - it < most && !(o->tol >= 0.0 && checked(last)))
+            if (checked(++last)) eit = last - it;
+        sa.eit_part = eit >= 0 ? c->partials : nullptr;
         if (small) {
-            // up to the next step whose e_it the host reads, or the end
-            int last = it, eit = check ? 0 : -1;
-            while (last + 1 < o->max_iter && !(o->tol >= 0.0 && checked(last)))
-                if (checked(++last)) eit = last - it;
             launch_smooth_small(s, sa, fp32, c->jv, c->jv32, c->p64[src], c->p32[src],
                                 last - it + 1, eit);
-            check = checked(last);
-            it = last;
         } else {
-            sa.eit_part = check ? c->partials : nullptr;
-            launch_smooth(s, sa, fp32, c->jv, c->jv32, q64[src], q64[dst], q32[src], q32[dst]);
+            if (last > it)
+                launch_smooth_tile(s, sa, c->j_grid_nx, fp32, c->jv, c->jv32, q64[src], q64[dst],
+                                   q32[src], q32[dst], last - it + 1, eit);
+            else
+                launch_smooth(s, sa, fp32, c->jv, c->jv32, q64[src], q64[dst], q32[src], q32[dst]);
             c->pcur = dst;
         }
+        check = checked(last);
+        it = last;
         if (check && o->tol >= 0.0) {
             hipMemcpyAsync(c->h_pinned, c->eit_val, sizeof(double), hipMemcpyDeviceToHost, s);
             if (hipStreamSynchronize(s) != hipSuccess)

@@ -213,6 +213,7 @@ struct msrsb_ctx {
     // s of row i, the slot of row k's pattern that holds the same coarse
     // column (4 bits each, 0xF = none), stored as indices into a table
     int jmap_kind = 0;                  // 0 none, 1 uint8 index, 2 uint16 index, 3 full
+    int j_grid_nx = 0;                  // J couples 2D grid neighbours, lines of this length
     void *jmap_idx = nullptr;
     uint32_t *jmap_tab = nullptr;
     int jmap_ntab = 0;
@@ -430,6 +431,8 @@ void launch_filter_jacobi(hipStream_t s, int n, int bs, int filter, double omega
                           const double *nsv = nullptr);
 void launch_init_basis(hipStream_t s, int n, int pw, const int *pcol, const int *part,
                        double *p64, float *p32);
+// e_it from nb work-groups' maxima
+void launch_eit_final(hipStream_t s, int nb, const double *part, double *out);
 void launch_smooth(hipStream_t s, const SmoothArgs &a, bool fp32, const double *jv64,
                    const float *jv32, const double *pin64, double *pout64, const float *pin32,
                    float *pout32);
@@ -639,6 +642,12 @@ void launch_pcg_small(hipStream_t s, const SmallPcg &a, int pw);
 // steps of the smoothing iteration on P in place, in one launch, where it
 // fits; eit_step (-1: none) forms e_it
 bool smooth_fits_small(const SmoothArgs &a, bool fp32);
+// up to smooth_tile_steps (0: not served) steps per launch on a 2D grid of nx
+// cells a line (0: none); eit_part is used with eit_step
+int smooth_tile_steps(const SmoothArgs &a, int nx);
+void launch_smooth_tile(hipStream_t s, const SmoothArgs &a, int nx, bool fp32, const double *jv64,
+                        const float *jv32, const double *pin64, double *pout64,
+                        const float *pin32, float *pout32, int steps, int eit_step);
 void launch_smooth_small(hipStream_t s, const SmoothArgs &a, bool fp32, const double *jv64,
                          const float *jv32, double *p64, float *p32, int steps, int eit_step);
 

@@ -1389,6 +1389,11 @@ void launch_init_basis(hipStream_t s, int n, int pw, const int *pcol, const int 
         k_init_basis<double><<<grid_for(m), kBlock, 0, s>>>(m, pw, pcol, part, p64);
 }
 
+void launch_eit_final(hipStream_t s, int nb, const double *part, double *out)
+{
+    k_eit_final<<<1, 1024, 0, s>>>(nb, part, out);
+}
+
 void launch_smooth(hipStream_t s, const SmoothArgs &a, bool fp32, const double *jv64,
                    const float *jv32, const double *pin64, double *pout64, const float *pin32,
                    float *pout32)
@@ -1397,7 +1402,7 @@ void launch_smooth(hipStream_t s, const SmoothArgs &a, bool fp32, const double *
         smooth_t<float>(s, a, jv32, pin32, pout32);
     else
         smooth_t<double>(s, a, jv64, pin64, pout64);
-    if (a.eit_part) k_eit_final<<<1, 1024, 0, s>>>(grid_n(a.n), a.eit_part, a.eit_out);
+    if (a.eit_part) launch_eit_final(s, grid_n(a.n), a.eit_part, a.eit_out);
 }
 
 void launch_basis_stats(hipStream_t s, int n, int pw, const int *pcol, bool fp32,
