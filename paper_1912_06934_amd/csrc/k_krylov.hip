@@ -696,7 +696,7 @@ __device__ __forceinline__ double step_beta(const PcgSums &p)
 // ascending order, the mirrored reads missed the L2: 580 MB fetched for the
 // 290 MB of upper entries, against 418 MB in pairs.)  Bound by memory: one
 // product of the 3D Q1 operator at 275k nodes took 109 us reading all 534 MB
-// of entries, a thread per row, and takes 65 us; at 23k nodes 12.3 -> 8.7 us.
+// of entries, a thread per row, and takes 65 us; at 23k nodes 12.3 -> 7.3 us.
 //
 // A work-group covers kNbsNodes nodes (each XCD one contiguous range) with KS
 // threads each: the thread's part of the offsets is one of KS nearly equal
@@ -712,7 +712,8 @@ __device__ __forceinline__ int nbs_node()
 inline int nbs_grid(const NodeStencil &ns) { return (ns.nn + kNbsNodes - 1) / kNbsNodes; }
 
 // s[c] += the products of the node's row c: the offsets part, part + KS, ...,
-// or with SYM the diagonal block (part 0) and the pairs part, part + KS, ...
+// or with SYM the pairs part, part + KS, ... and the diagonal block (the last
+// part, which has the fewest pairs)
 template <int BS, bool SYM, int KS, typename MT>
 __device__ __forceinline__ void nbs_part(int part, int node, const NodeStencil &ns,
                                          const MT *__restrict__ v, const double *__restrict__ x,
@@ -743,7 +744,7 @@ __device__ __forceinline__ void nbs_part(int part, int node, const NodeStencil &
     };
     if constexpr (SYM) {
         const int mid = ns.n / 2;
-        if (part == 0) {
+        if (part == KS - 1) {
             MT a[BS][BS], xv[BS];
             block(mid, node, false, a);
             vec(node, xv);
@@ -806,6 +807,19 @@ __device__ __forceinline__ void nbs_dot(int node, const NodeStencil &ns,
     }
 }
 
+// a node's BS entries of a vector, in the wavefront that finishes the rows: its
+// loads are issued before the products, which the split forms are short of
+template <int BS, int KS, typename T>
+struct NodeRow {
+    T v[BS] = {};
+    __device__ __forceinline__ NodeRow(const T *__restrict__ x, int node, int nn)
+    {
+        if (node >= nn || (KS > 1 && threadIdx.x >= kNbsNodes)) return;
+#pragma unroll
+        for (int c = 0; c < BS; ++c) v[c] = x[static_cast<int64_t>(node) * BS + c];
+    }
+};
+
 template <int BS, bool SYM, int KS>
 __global__ __launch_bounds__(KS *kNbsNodes) void k_nbs_spmv(NodeStencil ns,
                                                             const double *__restrict__ v,
@@ -828,13 +842,14 @@ __global__ __launch_bounds__(KS *kNbsNodes) void k_nbs_residual(NodeStencil ns,
                                                                 double *__restrict__ res)
 {
     const int node = nbs_node();
+    const NodeRow<BS, KS, double> fr(f, node, ns.nn);
     MT s[BS];
     nbs_dot<BS, SYM, KS, MT>(node, ns, v, x, s);
     if (node >= ns.nn || threadIdx.x >= kNbsNodes) return;
 #pragma unroll
     for (int c = 0; c < BS; ++c) {
         const int64_t r = static_cast<int64_t>(node) * BS + c;
-        res[r] = static_cast<double>(static_cast<MT>(f[r]) - s[c]);
+        res[r] = static_cast<double>(static_cast<MT>(fr.v[c]) - s[c]);
     }
 }
 
@@ -845,13 +860,15 @@ __global__ __launch_bounds__(KS *kNbsNodes) void k_nbs_sweep(
     const double *__restrict__ vin, const double *__restrict__ zin, double *__restrict__ zout)
 {
     const int node = nbs_node();
+    const NodeRow<BS, KS, double> vr(vin, node, ns.nn), zr(zin, node, ns.nn);
+    const NodeRow<BS, KS, MT> dr(dinv, node, ns.nn);
     MT s[BS];
     nbs_dot<BS, SYM, KS, MT>(node, ns, a, zin, s);
     if (node >= ns.nn || threadIdx.x >= kNbsNodes) return;
 #pragma unroll
     for (int c = 0; c < BS; ++c) {
         const int64_t r = static_cast<int64_t>(node) * BS + c;
-        zout[r] = zin[r] + static_cast<double>(dinv[r] * (static_cast<MT>(vin[r]) - s[c]));
+        zout[r] = zr.v[c] + static_cast<double>(dr.v[c] * (static_cast<MT>(vr.v[c]) - s[c]));
     }
 }
 
@@ -864,6 +881,8 @@ __global__ __launch_bounds__(KS *kNbsNodes) void k_nbs_sweep_dots(
     const double *__restrict__ zold, double *__restrict__ part)
 {
     const int node = nbs_node();
+    const NodeRow<BS, KS, double> rr(rv, node, ns.nn), zr(zin, node, ns.nn), zo(zold, node, ns.nn);
+    const NodeRow<BS, KS, MT> dr(dinv, node, ns.nn);
     MT s[BS];
     nbs_dot<BS, SYM, KS, MT>(node, ns, a, zin, s);
     if (threadIdx.x >= kNbsNodes) return;
@@ -872,11 +891,11 @@ __global__ __launch_bounds__(KS *kNbsNodes) void k_nbs_sweep_dots(
 #pragma unroll
         for (int c = 0; c < BS; ++c) {
             const int64_t r = static_cast<int64_t>(node) * BS + c;
-            const double ri = rv[r];
-            const double z = zin[r] + static_cast<double>(dinv[r] * (static_cast<MT>(ri) - s[c]));
+            const double ri = rr.v[c];
+            const double z = zr.v[c] + static_cast<double>(dr.v[c] * (static_cast<MT>(ri) - s[c]));
             zout[r] = z;
             v[0] += ri * z;
-            v[1] += ri * (z - zold[r]);
+            v[1] += ri * (z - zo.v[c]);
         }
     }
 #pragma unroll
@@ -920,6 +939,7 @@ __global__ __launch_bounds__(KS *kNbsNodes) void k_nbs_spmv_dot(NodeStencil ns,
                                                                 double *__restrict__ part)
 {
     const int node = nbs_node();
+    const NodeRow<BS, KS, double> pr(p, node, ns.nn);
     double s[BS];
     nbs_dot<BS, SYM, KS, double>(node, ns, v, p, s);
     if (threadIdx.x >= kNbsNodes) return;
@@ -929,7 +949,7 @@ __global__ __launch_bounds__(KS *kNbsNodes) void k_nbs_spmv_dot(NodeStencil ns,
         for (int c = 0; c < BS; ++c) {
             const int64_t r = static_cast<int64_t>(node) * BS + c;
             q[r] = s[c];
-            pq += p[r] * s[c];
+            pq += pr.v[c] * s[c];
         }
     }
 #pragma unroll
@@ -2019,11 +2039,13 @@ void launch_check_symmetric_stencil(hipStream_t s, int n, const DiaOffsets &d, c
 
 // ---- node-block stencil launchers ----
 // f(BS, SYM, KS) as integral constants, and the work-group size.  The
-// 27-offset operators take three threads per node below kNbsSplitNodes, where
-// a thread per node leaves fewer than two wavefronts per SIMD; above it the
-// three parts' streams only compete for the L2 (a product at 275k nodes: 72 us
-// with three threads per node, 66 us with one).
-constexpr int kNbsSplitNodes = 131072;
+// 27-offset operators take seven threads per node (two pairs of offsets each)
+// below kNbsSplitNodes, where a thread per node leaves too few loads in flight;
+// above it the parts' streams only compete for the L2.  A symmetric sweep with
+// one, three and seven threads: 8.2 / 6.4 / 5.1 us at 3.4k nodes, 12.0 / 7.4 /
+// 7.3 at 24k, 18.3 / 17.0 / 16.8 at 69k, 22.4 / 24.7 / 24.0 at 104k (five: as
+// seven; 13: 5.2, 8.7, 21.5 and 31.3).
+constexpr int kNbsSplitNodes = 90000;
 template <typename F>
 void with_ns(const NodeStencil &ns, F &&f)
 {
@@ -2036,7 +2058,7 @@ void with_ns(const NodeStencil &ns, F &&f)
     if (ns.bs == 2)
         sym(integral_constant<int, 2>{}, integral_constant<int, 1>{});
     else if (ns.n == 27 && ns.nn < kNbsSplitNodes)
-        sym(integral_constant<int, 3>{}, integral_constant<int, 3>{});
+        sym(integral_constant<int, 3>{}, integral_constant<int, 7>{});
     else
         sym(integral_constant<int, 3>{}, integral_constant<int, 1>{});
 }

@@ -29,8 +29,10 @@ def _sweeps(s, v, fp32):
     ((2, 2, 6), True), ((2, 2, 6), False),        # 63
     ((4, 12, 2), True),                           # 195: three wavefronts and three nodes
     ((19, 8, 11), True), ((19, 8, 11), False),
-    ((51, 51, 47), True),                         # 129,792: three threads per node
-    ((51, 51, 48), True), ((51, 51, 48), False),  # 132,496: one
+    ((43, 44, 44), True), ((43, 44, 44), False),  # 89,100: seven threads per node
+    ((44, 44, 44), True),                         # 91,125: one
+    ((51, 51, 47), True),                         # 129,792
+    ((51, 51, 48), True), ((51, 51, 48), False),  # 132,496
 ], ids=lambda x: str(x))
 def test_sweeps_match_sparse_algebra(elems, symmetric):
     from paper_1912_06934_amd import Msrsb
