@@ -156,6 +156,7 @@ void free_matrix(msrsb_ctx *c)
     dfree(c->a_ns_val32);
     c->a_ns = NodeStencil();
     c->a_off = DiaOffsets();
+    c->a_grid_nx = 0;
     c->at_off = DiaOffsets();
     c->j_off = DiaOffsets();
     c->j_dia = false;
@@ -369,6 +370,13 @@ msrsb_status install_pattern(msrsb_ctx *c, int n, int64_t nnz, std::vector<int> 
             if (!dalloc(c->a_slot, nnz) || !dalloc(c->a_dia, static_cast<size_t>(n) * offs.size()))
                 return fail(c, MSRSB_E_NOMEM, "device allocation of A (DIA) failed");
             hipMemcpy(c->a_slot, slot.data(), nnz, hipMemcpyHostToDevice);
+            // a 2D grid's operator: no entry across a line's ends
+            const int nx = grid2d_width(c->a_off, n);
+            bool grid = nx > 0;
+            for (int i = 0; i < n && grid; i += (i % nx == 0 ? nx - 1 : 1))
+                for (int e = c->h_rp[i]; e < c->h_rp[i + 1] && grid; ++e)
+                    grid = std::abs(c->h_ci[e] % nx - i % nx) <= 1;
+            c->a_grid_nx = grid ? nx : 0;
         }
     }
     // NBS form of a vector operator that is no DIA stencil: every entry's node
@@ -1291,13 +1299,11 @@ msrsb_status msrsb_set_coarse(msrsb_ctx *c, int32_t nc, const int32_t *part,
         }
         // J on a 2D grid: offsets to the neighbours of a row x + nx y, and no
         // coupling across a line's ends
-        if (c->j_dia && (c->jw == 5 || c->jw == 9)) {
-            const int jw = c->jw, nx = c->j_off.off[jw - 1] - (jw == 9 ? 1 : 0);
-            bool grid = nx >= 16 && n % nx == 0 && n / nx >= 16;
-            for (int o = 0; o < jw && grid; ++o) {
-                const int dx = jw == 5 ? (o == 1 ? -1 : o == 3 ? 1 : 0) : o % 3 - 1;
-                const int dy = jw == 5 ? (o == 0 ? -1 : o == 4 ? 1 : 0) : o / 3 - 1;
-                grid = c->j_off.off[o] == dx + nx * dy;
+        if (c->j_dia) {
+            const int nx = grid2d_width(c->j_off, n);
+            bool grid = nx > 0;
+            for (int o = 0; o < c->jw && grid; ++o) {
+                const int dx = c->jw == 5 ? (o == 1 ? -1 : o == 3 ? 1 : 0) : o % 3 - 1;
                 for (int i = dx < 0 ? 0 : nx - 1; i < n && dx != 0 && grid; i += nx)
                     grid = hm[static_cast<size_t>(o) * n + i] == 0xFFFFFFFFu;
             }

@@ -187,6 +187,7 @@ struct msrsb_ctx {
     float *a_ns_val32 = nullptr;
     // DIA form of A (when its rows use few distinct column offsets)
     msrsb::DiaOffsets a_off;
+    int a_grid_nx = 0;                  // A couples 2D grid neighbours, lines of this length
     int8_t *a_slot = nullptr;           // DIA slot of every CSR entry
     double *a_dia = nullptr;            // [a_off.n][n]
     float *a_dia32 = nullptr;
@@ -642,6 +643,16 @@ void launch_pcg_small(hipStream_t s, const SmallPcg &a, int pw);
 // steps of the smoothing iteration on P in place, in one launch, where it
 // fits; eit_step (-1: none) forms e_it
 bool smooth_fits_small(const SmoothArgs &a, bool fp32);
+// the line length of a 2D grid (16 x 16 cells at least) whose rows couple to
+// their four or eight neighbours by these offsets; 0: no such grid
+int grid2d_width(const DiaOffsets &d, int n);
+// z = z_in (null: 0) + P w_c, the sweeps and the partials of r.z, r.(z - zold)
+// on such a grid (a32, p32 null: FP64); returns the number of partials
+constexpr int kPostSweeps = 2;  // at most
+int launch_tile_post(hipStream_t s, int n, const DiaOffsets &d, const double *a, const float *a32,
+                     const double *dinv, const float *dinv32, const double *r, const double *zin,
+                     const double *p64, const float *p32, const uint16_t *pcol, const double *wc,
+                     int nx, int sweeps, double *zout, const double *zold, double *part);
 // up to smooth_tile_steps (0: not served) steps per launch on a 2D grid of nx
 // cells a line (0: none); eit_part is used with eit_step
 int smooth_tile_steps(const SmoothArgs &a, int nx);

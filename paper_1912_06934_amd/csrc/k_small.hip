@@ -630,6 +630,93 @@ void launch_small(hipStream_t s, const SmallPcg &a)
     else k_pcg_small<NDT, PW, 2><<<1, T, lds, s>>>(a);
 }
 
+// The end of the preconditioner on a 2D grid (as k_smooth_tile's: rows
+// x + nx y, rows of P of 4 slots) in one launch: z1 = z + P w_c, one or two
+// sweeps z + dinv (r - A z), and the partials of r.z and r.(z - z_old).  A
+// work-group takes a tile with a halo of two cells, which its two sweeps use
+// up; z and the coefficients are read 1.5 times instead of once per stage.
+// Bound by the launch and three dependent round trips.
+// 250 x 187 in FP64, two sweeps: 3.0 + 3.0 + 3.7 us in three launches, 3.9 here.
+constexpr int kPostX = 32, kPostY = 16, kPostHalo = 2, kPostT = kPostX * kPostY;
+template <int ND, bool SYM, typename MT, typename PT>
+__global__ __launch_bounds__(kPostT) void k_tile_post(
+    int n, DiaOffsets d, const MT *__restrict__ a, const MT *__restrict__ dinv,
+    const double *__restrict__ r, const double *__restrict__ zin, const PT *__restrict__ pv,
+    const uint16_t *__restrict__ pcol, const double *__restrict__ wc, int nx, int ny, int ntx,
+    int sweeps, double *__restrict__ zout, const double *__restrict__ zold,
+    double *__restrict__ part)
+{
+    __shared__ double ex[2][kPostT];
+    __shared__ double red[2][kPostT / 64];
+    constexpr int TX = kPostX - 2 * kPostHalo, TY = kPostY - 2 * kPostHalo;
+    const int t = threadIdx.x, tx = t % kPostX, ty = t / kPostX;
+    const int b = xcd_group(blockIdx.x, gridDim.x);
+    const int x = b % ntx * TX - kPostHalo + tx, y = b / ntx * TY - kPostHalo + ty;
+    const bool in = x >= 0 && x < nx && y >= 0 && y < ny;
+    const int i = in ? x + nx * y : 0;
+    const bool own = in && tx >= kPostHalo && tx < kPostX - kPostHalo && ty >= kPostHalo &&
+                     ty < kPostY - kPostHalo;
+    typedef uint16_t c4 __attribute__((ext_vector_type(4)));
+    const c4 cs = reinterpret_cast<const c4 *>(pcol)[i];
+    PT p[4];
+    load_slots(pv + static_cast<int64_t>(i) * 4, p);
+    double z = zin ? zin[i] : 0.0;
+    const MT ri = static_cast<MT>(r[i]);
+    const MT di = dinv[i];
+    const double zo = zold[i], rd = r[i];
+    MT av[ND];
+    int at[ND];
+#pragma unroll
+    for (int o = 0; o < ND; ++o) {
+        const int k = i + d.off[o];
+        const bool have = in && k >= 0 && k < n;
+        MT v;
+        if constexpr (SYM) {
+            v = o < ND / 2 ? a[static_cast<int64_t>(ND - 1 - o) * n + (have ? k : i)]
+                           : a[static_cast<int64_t>(o) * n + i];
+        } else {
+            v = a[static_cast<int64_t>(o) * n + i];
+        }
+        av[o] = have ? v : MT(0);
+        const int dx = ND == 5 ? (o == 1 ? -1 : o == 3 ? 1 : 0) : o % 3 - 1;
+        const int dy = ND == 5 ? (o == 0 ? -1 : o == 4 ? 1 : 0) : o / 3 - 1;
+        const bool there = tx + dx >= 0 && tx + dx < kPostX && ty + dy >= 0 && ty + dy < kPostY;
+        at[o] = there ? t + dx + kPostX * dy : t;
+    }
+    double g[4], s = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) g[q] = wc[cs[q] == 0xFFFFu ? 0 : cs[q]];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s += cs[q] == 0xFFFFu ? 0.0 : static_cast<double>(p[q]) * g[q];
+    z = zin ? z + s : s;
+    if (!in) z = 0.0;
+    for (int k = 0; k < sweeps; ++k) {
+        ex[k & 1][t] = z;
+        __syncthreads();
+        MT dot = MT(0);
+#pragma unroll
+        for (int o = 0; o < ND; ++o) dot += av[o] * static_cast<MT>(ex[k & 1][at[o]]);
+        z += static_cast<double>(di * (ri - dot));
+    }
+    double v[2] = {0.0, 0.0};
+    if (own) {
+        zout[i] = z;
+        v[0] = rd * z;
+        v[1] = rd * (z - zo);
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const double w = wave_sum(v[q]);
+        if ((t & 63) == 0) red[q][t >> 6] = w;
+    }
+    __syncthreads();
+    if (t < 2) {
+        double w = 0.0;
+        for (int u = 0; u < kPostT / 64; ++u) w += red[t][u];
+        part[static_cast<int64_t>(t) * gridDim.x + blockIdx.x] = w;
+    }
+}
+
 }  // namespace
 
 // 100 steps, launch by launch against one launch, set-up of J and the
@@ -687,6 +774,45 @@ void launch_smooth_tile(hipStream_t s, const SmoothArgs &a, int nx, bool fp32, c
     if (a.jw == 5) go(std::integral_constant<int, 5>{});
     else go(std::integral_constant<int, 9>{});
     if (eit_step >= 0) launch_eit_final(s, grid, a.eit_part, a.eit_out);
+}
+
+int launch_tile_post(hipStream_t s, int n, const DiaOffsets &d, const double *a, const float *a32,
+                     const double *dinv, const float *dinv32, const double *r, const double *zin,
+                     const double *p64, const float *p32, const uint16_t *pcol, const double *wc,
+                     int nx, int sweeps, double *zout, const double *zold, double *part)
+{
+    constexpr int TX = kPostX - 2 * kPostHalo, TY = kPostY - 2 * kPostHalo;
+    const int ny = n / nx, ntx = (nx + TX - 1) / TX, grid = ntx * ((ny + TY - 1) / TY);
+    auto go = [&](auto nd, auto sym, auto *ap, auto *dp, auto *pp) {
+        k_tile_post<decltype(nd)::value, decltype(sym)::value><<<grid, kPostT, 0, s>>>(
+            n, d, ap, dp, r, zin, pp, pcol, wc, nx, ny, ntx, sweeps, zout, zold, part);
+    };
+    auto with_types = [&](auto nd, auto sym) {
+        if (a32 && p32) go(nd, sym, a32, dinv32, p32);
+        else if (a32) go(nd, sym, a32, dinv32, p64);
+        else if (p32) go(nd, sym, a, dinv, p32);
+        else go(nd, sym, a, dinv, p64);
+    };
+    auto with_sym = [&](auto nd) {
+        if (d.sym) with_types(nd, std::true_type{});
+        else with_types(nd, std::false_type{});
+    };
+    if (d.n == 5) with_sym(std::integral_constant<int, 5>{});
+    else with_sym(std::integral_constant<int, 9>{});
+    return grid;
+}
+
+int grid2d_width(const DiaOffsets &d, int n)
+{
+    if (d.n != 5 && d.n != 9) return 0;
+    const int nx = d.off[d.n - 1] - (d.n == 9 ? 1 : 0);
+    if (nx < 16 || n % nx != 0 || n / nx < 16) return 0;
+    for (int o = 0; o < d.n; ++o) {
+        const int dx = d.n == 5 ? (o == 1 ? -1 : o == 3 ? 1 : 0) : o % 3 - 1;
+        const int dy = d.n == 5 ? (o == 0 ? -1 : o == 4 ? 1 : 0) : o / 3 - 1;
+        if (d.off[o] != dx + nx * dy) return 0;
+    }
+    return nx;
 }
 
 void launch_pcg_small(hipStream_t s, const SmallPcg &a, int pw)

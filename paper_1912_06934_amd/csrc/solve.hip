@@ -651,11 +651,16 @@ void apply_two_stage(msrsb_ctx *c, const msrsb_solve_opts *o, const double *v, d
     }
     if (pre_k == MSRSB_SMOOTH_NONE) pre_n = 0;
     if (post_k == MSRSB_SMOOTH_NONE) post_n = 0;
+    // the stages after the coarse solve in one launch, inside PCG on a 2D grid
+    bool post_tile = dots && o->use_multiscale && c->a_grid_nx > 0 && op.d.n == c->a_off.n &&
+                     c->pw == 4 && c->pcol16 && is_diag(post_k) && post_n >= 1 &&
+                     post_n <= kPostSweeps;
+    for (int k = 0; post_tile && k < op.d.n; ++k) post_tile = op.d.off[k] == c->a_off.off[k];
     double *z = b.z, *spare = b.spare, *tmp = b.tmp;
     // the sweeps that exchange z and spare are known beforehand, so the last
     // one can write zout itself (unless v, read until then, lies there)
     if (zout + n <= v || v + n <= zout) {
-        int swaps = is_diag(post_k) ? post_n : 0;
+        int swaps = post_tile ? 1 : is_diag(post_k) ? post_n : 0;
         if (is_diag(pre_k)) swaps += pre_n - (pre_n >= 2 && op.d.n > 0 ? 2 : 0);
         (swaps & 1 ? spare : z) = zout;
     }
@@ -724,6 +729,16 @@ void apply_two_stage(msrsb_ctx *c, const msrsb_solve_opts *o, const double *v, d
         launch_restrict(s, c->nc, c->rrp, c->rci, c->roff16, c->rbase, c->p_is32, c->r64, c->r32,
                         res, b.vc, restrict_boxes(c), post);
         coarse_apply(c, trans, b);
+        if (post_tile) {
+            // (z is not zout, whose neighbouring rows it would still read)
+            const bool l1 = post_k == MSRSB_SMOOTH_L1JACOBI;
+            finish(launch_tile_post(s, n, op.d, op.ad, fp32 ? op.ad32 : nullptr,
+                                    l1 ? op.dl1 : op.dj, l1 ? op.dl132 : op.dj32, v,
+                                    zero ? nullptr : z, c->p64[c->pcur],
+                                    c->p_is32 ? c->p32[c->pcur] : nullptr, c->pcol16, b.wc,
+                                    c->a_grid_nx, post_n, zout, dots->zold, dots->part));
+            return;
+        }
         launch_prolong_ell(s, n, c->pw, c->pcol_ell, c->pcol16, c->p_is32, prolong_p64(c),
                            prolong_p32(c),
                            b.wc, z, zero, prolong_axes(c));
