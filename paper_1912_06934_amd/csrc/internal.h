@@ -718,6 +718,12 @@ void launch_dia_sweep(hipStream_t s, int n, const DiaOffsets &d, bool fp32, cons
                       const float *a32, const double *dinv64, const float *dinv32,
                       const double *v, const double *zin, double *zout, bool zero2,
                       const UpdArgs *upd = nullptr);
+// upd, two sweeps from zero into zout and the residual res = r - A zout on a 2D
+// grid of nx cells a line (grid2d_width); one r.r partial per work-group
+int tile_pre_groups(int n, int nx);
+void launch_tile_pre(hipStream_t s, int n, const DiaOffsets &d, const double *a, const float *a32,
+                     const double *dinv, const float *dinv32, int nx, double *zout, double *res,
+                     const UpdArgs &upd);
 // the last sweep with the partials of r.z and r.(z - zold); these return the
 // number of partials per product
 int launch_dia_sweep_dots(hipStream_t s, int n, const DiaOffsets &d, bool fp32,

@@ -463,7 +463,9 @@ msrsb_status ensure_workspace(msrsb_ctx *c)
                                         64 * static_cast<size_t>(std::max(c->nc, 1)) + 64,
                                         static_cast<size_t>(64 * 66),
                                         static_cast<size_t>(3 * 2048)});
-    if (dev_alloc(&c->partials, np) || dev_alloc(&c->partials_rr, n / kBlock + 2) ||
+    // (the r.r ones: at most one per 64 rows and 16 more, where a 2D grid's tiles
+    // are mostly edge)
+    if (dev_alloc(&c->partials, np) || dev_alloc(&c->partials_rr, n / 64 + 16) ||
         dev_alloc(&c->scal, S_COUNT) ||
         dev_alloc(&c->vc, std::max(c->nc, 1)) || dev_alloc(&c->wc, std::max(c->nc, 1)) ||
         dev_alloc(&c->eit_val, 1) || dev_alloc(&c->dev_flag, 4))
@@ -651,11 +653,13 @@ void apply_two_stage(msrsb_ctx *c, const msrsb_solve_opts *o, const double *v, d
     }
     if (pre_k == MSRSB_SMOOTH_NONE) pre_n = 0;
     if (post_k == MSRSB_SMOOTH_NONE) post_n = 0;
-    // the stages after the coarse solve in one launch, inside PCG on a 2D grid
-    bool post_tile = dots && o->use_multiscale && c->a_grid_nx > 0 && op.d.n == c->a_off.n &&
-                     c->pw == 4 && c->pcol16 && is_diag(post_k) && post_n >= 1 &&
-                     post_n <= kPostSweeps;
-    for (int k = 0; post_tile && k < op.d.n; ++k) post_tile = op.d.off[k] == c->a_off.off[k];
+    // the stages after the coarse solve, and the update with two pre-sweeps and
+    // their residual, in one launch each, inside PCG on a 2D grid
+    bool grid2d = dots && o->use_multiscale && c->a_grid_nx > 0 && op.d.n == c->a_off.n;
+    for (int k = 0; grid2d && k < op.d.n; ++k) grid2d = op.d.off[k] == c->a_off.off[k];
+    const bool post_tile = grid2d && c->pw == 4 && c->pcol16 && is_diag(post_k) && post_n >= 1 &&
+                           post_n <= kPostSweeps;
+    const bool pre_tile = grid2d && upd && is_diag(pre_k) && pre_n == 2;
     double *z = b.z, *spare = b.spare, *tmp = b.tmp;
     // the sweeps that exchange z and spare are known beforehand, so the last
     // one can write zout itself (unless v, read until then, lies there)
@@ -680,6 +684,10 @@ void apply_two_stage(msrsb_ctx *c, const msrsb_solve_opts *o, const double *v, d
         dots->sums.ndots = 0;
     };
     // the step's post goes with the restriction, or right after the update
+    if (dots) {
+        const bool tiles = pre_tile && !f32_path;
+        dots->post.nrr = tiles ? tile_pre_groups(n, c->a_grid_nx) : (n + kBlock - 1) / kBlock;
+    }
     const PostArgs post = dots && !dots->last ? dots->post : PostArgs{};
     if (f32_path) {
         const float *dinv = pre_k == MSRSB_SMOOTH_L1JACOBI ? op.dl132 : op.dj32;
@@ -708,7 +716,13 @@ void apply_two_stage(msrsb_ctx *c, const msrsb_solve_opts *o, const double *v, d
             launch_pcg_update(s, n, *upd);
         }
     }
-    if (sweep2) {
+    if (pre_tile) {
+        const bool l1 = pre_k == MSRSB_SMOOTH_L1JACOBI;
+        launch_tile_pre(s, n, op.d, op.ad, fp32 ? op.ad32 : nullptr, l1 ? op.dl1 : op.dj,
+                        l1 ? op.dl132 : op.dj32, c->a_grid_nx, z, tmp, *upd);
+        zero = false;
+        t = 2;
+    } else if (sweep2) {
         const bool l1 = pre_k == MSRSB_SMOOTH_L1JACOBI;
         launch_dia_sweep(s, n, op.d, fp32, op.ad, op.ad32, l1 ? op.dl1 : op.dj,
                          l1 ? op.dl132 : op.dj32, v, nullptr, z, true, upd);
@@ -723,7 +737,7 @@ void apply_two_stage(msrsb_ctx *c, const msrsb_solve_opts *o, const double *v, d
     if (o->use_multiscale) {
         const double *res = v;
         if (!zero) {
-            op_residual(s, n, op, v, z, tmp, fp32);
+            if (!pre_tile) op_residual(s, n, op, v, z, tmp, fp32);
             res = tmp;
         }
         launch_restrict(s, c->nc, c->rrp, c->rci, c->roff16, c->rbase, c->p_is32, c->r64, c->r32,
@@ -937,7 +951,6 @@ msrsb_status pcg(msrsb_ctx *c, const double *f, double *x, const msrsb_solve_opt
     dots.part = c->partials;
     dots.sums.scal = sc;
     dots.post.rr = c->partials_rr;
-    dots.post.nrr = (n + kBlock - 1) / kBlock;
     dots.post.scal = sc;
     dots.post.host_out = c->h_pinned + 8;
     while (it <= o->max_iter) {
