@@ -889,9 +889,8 @@ static msrsb_status pcg_small(msrsb_ctx *c, const Op &op, const double *f, doubl
         const int m = hist ? std::min(it + 1, hcap) - a.it0 : 0;
         if (m > 0) {
             // (each step's entry, the last one's not yet where more follow)
-            if (hipMemcpy(hist + a.it0, a.hist, m * sizeof(double), hipMemcpyDeviceToHost) !=
-                hipSuccess)
-                return MSRSB_E_HIP;
+            hipMemcpyAsync(hist + a.it0, a.hist, m * sizeof(double), hipMemcpyDeviceToHost, s);
+            if (hipStreamSynchronize(s) != hipSuccess) return MSRSB_E_HIP;
             for (int k = 0; k < m; ++k) hist[a.it0 + k] = std::sqrt(hist[a.it0 + k]) / fn;
         }
         if (code == kSmallMore) {
