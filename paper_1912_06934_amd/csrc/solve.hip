@@ -1058,9 +1058,12 @@ msrsb_status gmres(msrsb_ctx *c, const double *f, double *x, const msrsb_solve_o
     double *part[2] = {gsc + (m + 2), gsc + (m + 2) + kOrthoCols * kOrthoBlocks};
     double *w = c->w[0], *zt = c->w[1], *r = c->w[2];
     double *sc = c->scal;
-    // two mailbox slots in coherent pinned memory (steps alternate)
+    // two mailbox slots in coherent pinned memory (steps alternate).  The tags
+    // number the steps queued in all cycles: a cycle that ends early leaves the
+    // post of the step queued ahead, which is no step of the next cycle
     volatile double *mbox[2] = {c->h_pinned + 16, c->h_pinned + 24};
     mbox[0][2] = mbox[1][2] = -1.0;
+    int posts = 0, want[2] = {0, 0};
     launch_dot(s, n, f, f, c->partials, sc + S_FF);
     if (read_scalars(c, S_FF, 1)) return MSRSB_E_HIP;
     double fn = std::sqrt(c->h_pinned[0]);
@@ -1081,15 +1084,16 @@ msrsb_status gmres(msrsb_ctx *c, const double *f, double *x, const msrsb_solve_o
         launch_norm_scale(s, n, r, V, c->partials, sc + S_RR);
         k_gmres_init_g<<<1, 64, 0, s>>>(m, g, sc + S_RR);
         // one Arnoldi step: v_{j+1} and column j of H, its Givens rotation,
-        // and the residual estimate posted to mailbox slot j mod 2 with tag
-        auto step = [&](int jj, int tag) {
+        // and the residual estimate posted to mailbox slot j mod 2
+        auto step = [&](int jj) {
             const double *vj = V + jj * ldv;
             double *vn = V + (jj + 1) * ldv;
             apply_two_stage(c, o, vj, zt, trans, nullptr);
             op_spmv(s, n, op, zt, w);
             // CGS2: h = V^T w; w -= V h; h2 = V^T w; w -= V h2; h += h2
+            want[jj & 1] = ++posts;
             const GivensArgs ga{jj, m, H, hc, cs, sn, g, gsc, const_cast<double *>(mbox[jj & 1]),
-                                static_cast<double>(tag)};
+                                static_cast<double>(posts)};
             if (jj < kOrthoCols) {
                 ortho(s, n, jj + 1, ldv, V, w, vn, hc, part, ga);
                 return;
@@ -1104,15 +1108,15 @@ msrsb_status gmres(msrsb_ctx *c, const double *f, double *x, const msrsb_solve_o
         };
         int j = 0;
         bool brk = false;
-        if (it < o->max_iter) step(0, it + 1);
+        if (it < o->max_iter) step(0);
         for (j = 0; j < m && it < o->max_iter; ++j) {
             // step j + 1 goes into the queue before step j's residual is read,
             // so the device does not wait for the host; it writes only column
             // j + 1 of H, g[j + 1 ..] and v_{j + 2}, none of which the solution
             // after step j uses
-            if (j + 1 < m && it + 1 < o->max_iter) step(j + 1, it + 2);
+            if (j + 1 < m && it + 1 < o->max_iter) step(j + 1);
             double mail[2];
-            if (!wait_mailbox(s, mbox[j & 1], it + 1, mail)) {
+            if (!wait_mailbox(s, mbox[j & 1], want[j & 1], mail)) {
                 c->err = "the device did not report the residual of a Krylov step";
                 return MSRSB_E_HIP;
             }
