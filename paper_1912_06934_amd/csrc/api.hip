@@ -336,7 +336,7 @@ msrsb_status refresh_values(msrsb_ctx *c)
     c->smoother_valid = c->smoother32_valid = false;
     c->smoother_t_valid = c->smoother32_t_valid = false;
     c->ilu_ok[0] = c->ilu_ok[1] = c->ic_ok[0] = c->ic_ok[1] = false;
-    c->tri[0].v[TRI_GS].ok = c->tri[1].v[TRI_GS].ok = false;
+    tri_values_changed(c);
     return MSRSB_OK;
 }
 

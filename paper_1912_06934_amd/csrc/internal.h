@@ -134,6 +134,7 @@ struct TriOrder {
     int8_t *ilu_map = nullptr; // (k_ilu_map), natural order
     bool wave = false;         // the solves run in one wavefront (k_tri_wave)
     TriValues v[3];            // TRI_*
+    bool gs_used = false;      // SGS has run in this order: A's values are kept packed
 };
 
 // P's rows in two halves for the smoothing iteration, when the supports are
@@ -798,6 +799,7 @@ void tri_apply(msrsb_ctx *c, int ordering, int kind, const double *res, double *
 // the same with (D + L)^{-1} (lower) or (D + U)^{-1}, A's values
 void tri_gs_half(msrsb_ctx *c, int ordering, bool lower, const double *res, double *z, bool set,
                  double *x);
+void tri_values_changed(msrsb_ctx *c);  // A's values are new
 // R's values of the MsFV restriction: 1 where the entry's fine row lies in
 // the coarse row's block, else 0
 void launch_r_indicator(hipStream_t s, int nc, int64_t rnnz, const int *rrp, const int *rci,

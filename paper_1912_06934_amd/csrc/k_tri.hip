@@ -1007,14 +1007,29 @@ void tri_apply(msrsb_ctx *c, int ordering, int kind, const double *res, double *
               z, set, x);
 }
 
-// A's values are packed by the first half sweep after they change
+// A's values are packed by the first half sweep of an order and from then on
+// whenever they change, so that a graph that holds this launch and not the
+// packing follows them
 void tri_gs_half(msrsb_ctx *c, int ordering, bool lower, const double *res, double *z, bool set,
                  double *x)
 {
     TriOrder &t = c->tri[ordering];
-    if (!t.v[TRI_GS].ok) pack_values(c->stream, t, TRI_GS, c->a);
+    if (!t.v[TRI_GS].ok) {
+        pack_values(c->stream, t, TRI_GS, c->a);
+        t.gs_used = true;
+        // (recorded into a graph, the packing has not been done yet)
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)
+            t.v[TRI_GS].ok = false;
+    }
     const int side = lower ? 0 : 1;
     run_solve(c->stream, t, TRI_GS, side, side, res, z, set, x);
+}
+
+void tri_values_changed(msrsb_ctx *c)
+{
+    for (TriOrder &t : c->tri)
+        if (t.gs_used) pack_values(c->stream, t, TRI_GS, c->a);
 }
 
 }  // namespace msrsb
