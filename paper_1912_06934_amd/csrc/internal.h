@@ -85,16 +85,20 @@ struct TriSegment {
 
 // One triangle (the earlier or the later entries) of a sweep order, packed by
 // dependency level: position u = lev[l] + t holds row[u], and its entries
-// k < width[l] sit at off[l] + k * (rows of level l) + t.
+// k < width[l] sit at off[l] + k * (rows of level l) + t, further ones from
+// tail[u] to tail[u + 1] behind all levels.
 struct TriSide {
     std::vector<int> lev;        // level pointers
-    std::vector<int> width;      // most entries of a level's rows
-    std::vector<int64_t> off;    // first packed place of a level (and the total)
+    std::vector<int> width;      // packed width of a level (see level_width)
+    std::vector<int64_t> off;    // first packed place of a level (and of the tails)
+    std::vector<char> tails;     // levels with rows longer than their width
+    int64_t places = 0;          // packed places, tails included
     std::vector<TriSegment> seg;
     bool merged = false;         // levels 0 and 1 go in one launch (kTriFirst)
     int max_w = 0, max_cnt = 0;  // widest row, largest level
     int *d_lev = nullptr, *d_width = nullptr;  // device copies
     int64_t *d_off = nullptr;
+    int64_t *tail = nullptr;     // null: no level has tails
     int *row = nullptr;
     int *col = nullptr;          // columns; kTriFirst marks a level-0 column of a
                                  // level-1 row when the two are merged; padding:

@@ -255,11 +255,13 @@ __device__ __forceinline__ void tri_end(const TriPass &p, int i, double s)
 
 // positions [u0, u0 + skip + cnt): `skip` rows without entries (level 0, when
 // the first two levels go together), then the cnt rows of one level with their
-// entries from place `at` on.  W: the width, or 0 for any.  FIRST: a first
-// pass (marked columns are read from `in`; a second pass has in = x).
+// entries from place `at` on.  W: the width, or 0 for any; tail: null unless
+// rows of the level are longer.  FIRST: a first pass (marked columns are read
+// from `in`; a second pass has in = x).
 template <int W, bool FIRST>
 __global__ __launch_bounds__(256) void k_tri_level(TriPass p, int u0, int skip, int cnt,
-                                                   int64_t at, int width)
+                                                   int64_t at, int width,
+                                                   const int64_t *__restrict__ tail)
 {
     const int tt = blockIdx.x * 256 + threadIdx.x, t = tt - skip;
     if (t >= cnt) return;
@@ -285,6 +287,14 @@ __global__ __launch_bounds__(256) void k_tri_level(TriPass p, int u0, int skip, 
 #pragma unroll
         for (int k = 0; k < C; ++k) s -= v[k] * xv[k];
     }
+    if (tail && t >= 0) {
+        const int64_t e1 = tail[u + 1];
+#pragma unroll 8
+        for (int64_t e = tail[u]; e < e1; ++e) {
+            const int c = p.col[e];
+            s -= p.val[e] * (FIRST && c < 0 ? p.in : p.x)[c & ~kTriFirst];
+        }
+    }
     s *= di;
     const bool end = p.last || fo != 0.0;
     if (fo != 0.0) s *= fo;
@@ -299,13 +309,16 @@ __global__ __launch_bounds__(256) void k_tri_level(TriPass p, int u0, int skip, 
 constexpr int kNarrowLdsRows = 16384;  // 128 KB of LDS
 constexpr int kRowRegs = 8;
 
-template <bool LDS>
+// TAIL: rows of these levels may have tails, whose entries need registers too.
+template <bool LDS, bool TAIL>
 __global__ __launch_bounds__(kNarrowThreads) void k_tri_run(TriPass p,
                                                             const int *__restrict__ lev,
                                                             const int *__restrict__ width,
                                                             const int64_t *__restrict__ off,
+                                                            const int64_t *__restrict__ tail,
                                                             int lev0, int lev1, int n, bool second)
 {
+    constexpr int REGS = TAIL ? kRowRegs / 2 : kRowRegs;
     extern __shared__ double sx[];
     const int tid = threadIdx.x;
     double *x = LDS ? sx : p.x;
@@ -315,8 +328,8 @@ __global__ __launch_bounds__(kNarrowThreads) void k_tri_run(TriPass p,
     }
     const double *in = second ? x : p.in;
     struct Row {
-        int i, c[kRowRegs];
-        double v[kRowRegs], d, fo;
+        int i, c[REGS];
+        double v[REGS], d, fo;
     };
     auto load = [&](int l, int t, Row &q) {
         q.i = -1;
@@ -328,7 +341,7 @@ __global__ __launch_bounds__(kNarrowThreads) void k_tri_run(TriPass p,
         q.d = p.dinv[u0 + t];
         q.fo = p.fold ? p.fold[u0 + t] : 0.0;
 #pragma unroll
-        for (int k = 0; k < kRowRegs; ++k) {
+        for (int k = 0; k < REGS; ++k) {
             // (marked: padding; the first level's columns are marked in wide
             // levels only)
             q.c[k] = k < w ? p.col[at + static_cast<int64_t>(k) * cnt] : kTriFirst;
@@ -339,15 +352,21 @@ __global__ __launch_bounds__(kNarrowThreads) void k_tri_run(TriPass p,
         double s = in[q.i];
         const int w = width[l];
 #pragma unroll
-        for (int k = 0; k < kRowRegs; ++k)
+        for (int k = 0; k < REGS; ++k)
             if (q.c[k] >= 0) s -= q.v[k] * x[q.c[k]];
-        if (w > kRowRegs) {
+        if (w > REGS) {
             const int cnt = lev[l + 1] - lev[l];
-            for (int k = kRowRegs; k < w; ++k) {
+            for (int k = REGS; k < w; ++k) {
                 const int64_t e = off[l] + static_cast<int64_t>(k) * cnt + t;
                 const int c = p.col[e];
                 if (c >= 0) s -= p.val[e] * x[c];
             }
+        }
+        if constexpr (TAIL) {
+            const int u = lev[l] + t;
+            const int64_t e1 = tail[u + 1];
+#pragma unroll 4
+            for (int64_t e = tail[u]; e < e1; ++e) s -= p.val[e] * x[p.col[e]];
         }
         s *= q.d;
         const bool end = p.last || q.fo != 0.0;
@@ -620,6 +639,25 @@ void segments(const std::vector<int> &ptr, std::vector<TriSegment> &seg)
     }
 }
 
+// The packed width of a level of cnt rows with sum entries, the longest row
+// `widest`; len gives a row's entries.  A level is padded to its longest row
+// where that takes no more than kRowRegs places a row or three per entry; else
+// to the width that all but an eighth of its rows keep to, at most eight places
+// per entry, and the longer rows' further entries go to the tails.
+// A row of 2,500 entries in a level of 20,001 short ones: padded to it, 50 M
+// places (2.3 GB with the values of ILU(0) and SGS in two orders), 160 ms for a
+// first ILU(0) application and 375 us for each; with tails 18 MB, 13 ms and 100 us.
+template <typename Len>
+int level_width(int cnt, int64_t sum, int widest, std::vector<int> &lengths, Len len)
+{
+    if (widest <= kRowRegs || static_cast<int64_t>(cnt) * widest <= 3 * sum) return widest;
+    lengths.assign(widest + 1, 0);  // rows of each length
+    for (int u = 0; u < cnt; ++u) lengths[len(u)]++;
+    int w = widest;
+    for (int longer = 0; w > 0 && longer + lengths[w] <= cnt / 8; --w) longer += lengths[w];
+    return w;
+}
+
 // Arrays that live and die together, in one device allocation (the host
 // vectors must outlive upload()).
 struct Slab {
@@ -692,13 +730,13 @@ int wave_levels(const TriSide &q)
 int wave_rows(const TriOrder &t) { return std::max(t.s[0].max_cnt, t.s[1].max_cnt) <= 64 ? 1 : 2; }
 
 void launch_level(hipStream_t s, const TriPass &p, bool first, int u0, int skip, int cnt,
-                  int64_t at, int width)
+                  int64_t at, int width, const int64_t *tail)
 {
     auto go = [&](auto w) {
         constexpr int W = decltype(w)::value;
         const int nb = (skip + cnt + 255) / 256;
-        if (first) k_tri_level<W, true><<<nb, 256, 0, s>>>(p, u0, skip, cnt, at, width);
-        else k_tri_level<W, false><<<nb, 256, 0, s>>>(p, u0, skip, cnt, at, width);
+        if (first) k_tri_level<W, true><<<nb, 256, 0, s>>>(p, u0, skip, cnt, at, width, tail);
+        else k_tri_level<W, false><<<nb, 256, 0, s>>>(p, u0, skip, cnt, at, width, tail);
     };
     using std::integral_constant;
     switch (width) {
@@ -727,19 +765,23 @@ void run_side(hipStream_t s, const TriOrder &t, const TriSide &q, const TriPass 
             if (merged && lev0 == 0) continue;  // in level 1's launch
             const int skip = merged && lev0 == 1 ? q.lev[1] : 0;
             launch_level(s, p, !second, q.lev[lev0] - skip, skip, q.lev[lev0 + 1] - q.lev[lev0],
-                         q.off[lev0], q.width[lev0]);
+                         q.off[lev0], q.width[lev0], q.tails[lev0] ? q.tail : nullptr);
             continue;
         }
         const size_t sh = t.n <= kNarrowLdsRows ? static_cast<size_t>(t.n) * sizeof(double) : 0;
-        if (sh > 65536)
-            hipFuncSetAttribute(reinterpret_cast<const void *>(k_tri_run<true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(sh));
-        if (sh)
-            k_tri_run<true><<<1, kNarrowThreads, sh, s>>>(p, q.d_lev, q.d_width, q.d_off, lev0,
-                                                          g.lev1, t.n, second);
+        auto go = [&](auto kern) {
+            if (sh > 65536)
+                hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    static_cast<int>(sh));
+            kern<<<1, kNarrowThreads, sh, s>>>(p, q.d_lev, q.d_width, q.d_off, q.tail, lev0, g.lev1,
+                                               t.n, second);
+        };
+        if (std::find(q.tails.begin() + lev0, q.tails.begin() + g.lev1, 1) !=
+            q.tails.begin() + g.lev1)
+            sh ? go(k_tri_run<true, true>) : go(k_tri_run<false, true>);
         else
-            k_tri_run<false><<<1, kNarrowThreads, 0, s>>>(p, q.d_lev, q.d_width, q.d_off, lev0,
-                                                          g.lev1, t.n, second);
+            sh ? go(k_tri_run<true, false>) : go(k_tri_run<false, false>);
     }
 }
 
@@ -756,7 +798,7 @@ bool alloc_values(const TriOrder &t, TriValues &v)
     size_t val[2], dinv[2], wave[2];
     for (int side = 0; side < 2; ++side) {
         const TriSide &q = t.s[side];
-        val[side] = place(q.off.back() * sizeof(double));
+        val[side] = place(q.places * sizeof(double));
         dinv[side] = place(t.n * sizeof(double));
         wave[side] = place(!t.wave ? 0
                                    : static_cast<size_t>(wave_levels(q) + kTriDepth) *
@@ -781,7 +823,7 @@ void pack_values(hipStream_t s, TriOrder &t, int kind, const double *f)
         const TriSide &q = t.s[side];
         const bool unit = kind == TRI_ILU && side == 0;
         const bool first = side == 0 || kind == TRI_GS;
-        const int64_t m = q.off.back();
+        const int64_t m = q.places;
         if (m > 0)
             k_tri_pack<<<static_cast<int>((m + 255) / 256), 256, 0, s>>>(
                 m, q.src, q.col, t.dpos, first && !unit, f, v.val[side]);
@@ -893,7 +935,8 @@ msrsb_status tri_order_setup(msrsb_ctx *c, int ordering)
     }
     t.sym_pattern = std::all_of(tpos.begin(), tpos.end(), [](int p) { return p >= 0; });
     Slab slab;
-    std::vector<int> rows_of[2], col_of[2], src_of[2], fold;
+    std::vector<int> rows_of[2], col_of[2], src_of[2], fold, lengths;
+    std::vector<int64_t> tail_of[2];
     slab.add(&t.side, side);
     slab.add(&t.lord, lord);
     slab.add(&t.nlow, nlow);
@@ -911,29 +954,57 @@ msrsb_status tri_order_setup(msrsb_ctx *c, int ordering)
             for (int u = 0; u < q.lev[1]; ++u) level[rows[u]] = 1;  // marks level 0
         q.width.assign(nlev, 0);
         q.off.assign(nlev + 1, 0);
+        q.tails.assign(nlev, 0);
+        std::vector<int64_t> &tail = tail_of[sd];
         for (int l = 0; l < nlev; ++l) {
-            for (int u = q.lev[l]; u < q.lev[l + 1]; ++u)
-                q.width[l] = std::max(q.width[l], count[sd][rows[u]]);
             const int cnt = q.lev[l + 1] - q.lev[l];
+            auto len = [&](int u) { return count[sd][rows[q.lev[l] + u]]; };
+            int widest = 0;
+            int64_t sum = 0;
+            for (int u = 0; u < cnt; ++u) {
+                widest = std::max(widest, len(u));
+                sum += len(u);
+            }
+            q.width[l] = level_width(cnt, sum, widest, lengths, len);
             q.off[l + 1] = q.off[l] + static_cast<int64_t>(cnt) * q.width[l];
-            q.max_w = std::max(q.max_w, q.width[l]);
+            q.max_w = std::max(q.max_w, widest);
             q.max_cnt = std::max(q.max_cnt, cnt);
+            if (q.width[l] == widest) continue;
+            q.tails[l] = 1;
+            tail.resize(n + 1);
         }
-        col.resize(q.off[nlev]);
-        src.assign(q.off[nlev], -1);
+        q.places = q.off[nlev];
+        if (!tail.empty()) {
+            for (int l = 0; l < nlev; ++l)
+                for (int u = q.lev[l]; u < q.lev[l + 1]; ++u) {
+                    tail[u] = q.places;
+                    q.places += std::max(count[sd][rows[u]] - q.width[l], 0);
+                }
+            tail[n] = q.places;
+            slab.add(&q.tail, tail);
+        }
+        col.resize(q.places);
+        src.assign(q.places, -1);
         for (int l = 0; l < nlev; ++l) {
             const int cnt = q.lev[l + 1] - q.lev[l];
             const bool marks = q.merged && l == 1;
             for (int u = 0; u < cnt; ++u) {
                 const int i = rows[q.lev[l] + u];
-                int64_t at = q.off[l] + u;
+                int k = 0;
+                auto place = [&] {
+                    const int64_t at = k < q.width[l]
+                                           ? q.off[l] + static_cast<int64_t>(k) * cnt + u
+                                           : tail[q.lev[l] + u] + k - q.width[l];
+                    ++k;
+                    return at;
+                };
                 for (int e = rp[i]; e < rp[i + 1]; ++e) {
                     if (side[e] != want) continue;
+                    const int64_t at = place();
                     col[at] = marks && level[ci[e]] ? ci[e] | kTriFirst : ci[e];
                     src[at] = e;
-                    at += cnt;
                 }
-                for (int k = count[sd][i]; k < q.width[l]; ++k, at += cnt) col[at] = i | kTriFirst;
+                while (k < q.width[l]) col[place()] = i | kTriFirst;
             }
         }
         if (sd == 0) {

@@ -7,6 +7,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <new>
 #include <type_traits>
 
 #include "internal.h"
@@ -533,7 +534,13 @@ msrsb_status ensure_smoother(msrsb_ctx *c, const msrsb_solve_opts *o, bool trans
     }
     if (need_tri) {
         const int ord = o->ordering;
-        msrsb_status st = tri_order_setup(c, ord);
+        msrsb_status st;
+        try {
+            st = tri_order_setup(c, ord);
+        } catch (const std::bad_alloc &) {
+            free_tri_order(c->tri[ord]);
+            st = MSRSB_E_NOMEM;
+        }
         if (st) {
             c->err = "sweep order set-up failed";
             return st;
