@@ -81,6 +81,7 @@ __host__ __device__ __forceinline__ int64_t nbs_pos(int st, int r, int bs, int n
 struct TriSegment {
     int lev0, lev1;
     bool wide;
+    int64_t map0 = 0;  // a run's first row in TriOrder::ilu_at and ilu_map
 };
 
 // One triangle (the earlier or the later entries) of a sweep order, packed by

@@ -149,7 +149,7 @@ __global__ __launch_bounds__(kNarrowThreads) void k_tri_narrow(TriArgs t, RowOp 
 constexpr int kIluLanes = 16;
 constexpr int kIluLow = 8;
 
-// of row position u's w-th earlier neighbour k: the row's entry of that
+// of the u-th row's w-th earlier neighbour k: the row's entry of that
 // column, k's diagonal entry and first entry (at[u * kIluLow + w], x < 0:
 // none), and per entry f of the row the offset in row k of its column when
 // that comes later than k, else -1 (map[(u * kIluLow + w) * kIluLanes + f])
@@ -187,6 +187,7 @@ __global__ __launch_bounds__(kNarrowThreads) void k_ilu_run(TriArgs t,
 {
     const int f = threadIdx.x % kIluLanes, g = threadIdx.x / kIluLanes;
     constexpr int ROWS = kNarrowThreads / kIluLanes;
+    const int first = lev[lev0];  // the maps' row 0
     for (int l = lev0; l < lev1; ++l) {
         for (int u = lev[l] + g; u < lev[l + 1]; u += ROWS) {
             const int i = rows[u], e0 = t.rp[i], len = t.rp[i + 1] - e0;
@@ -195,7 +196,7 @@ __global__ __launch_bounds__(kNarrowThreads) void k_ilu_run(TriArgs t,
             int m[LOW];
 #pragma unroll
             for (int w = 0; w < LOW; ++w) {
-                const int64_t uw = static_cast<int64_t>(u) * kIluLow + w;
+                const int64_t uw = static_cast<int64_t>(u - first) * kIluLow + w;
                 a[w] = at[uw];
                 m[w] = map[uw * kIluLanes + f];
             }
@@ -680,7 +681,7 @@ void segments(const std::vector<int> &ptr, std::vector<TriSegment> &seg)
             seg.back().lev1 = l + 1;
             continue;
         }
-        seg.push_back(TriSegment{l, l + 1, wide});
+        seg.push_back(TriSegment{l, l + 1, wide, 0});
     }
 }
 
@@ -738,21 +739,36 @@ struct Slab {
     }
 };
 
-// the maps of k_ilu_run, once per pattern: natural order, rows that fit its
-// lanes, and at most 512 MB of them
-bool ilu_maps(hipStream_t s, TriOrder &t)
+// the maps of k_ilu_run, once per pattern, of the rows in runs of narrow levels:
+// natural order, rows that fit its lanes, and at most 512 MB of them.  Without
+// them, also where they cannot be allocated, the runs take k_tri_narrow.
+void ilu_maps(hipStream_t s, TriOrder &t)
 {
-    if (t.ilu_at || t.ncolours > 0 || t.max_row > kIluLanes || t.s[0].max_w > kIluLow ||
-        static_cast<int64_t>(t.n) * kIluLow * kIluLanes > (int64_t(1) << 29))
-        return true;
-    const int64_t m = static_cast<int64_t>(t.n) * kIluLow;
-    if (hipMalloc(&t.ilu_at, m * sizeof(int4)) != hipSuccess ||
-        hipMalloc(&t.ilu_map, m * kIluLanes) != hipSuccess)
-        return false;
+    TriSide &q = t.s[0];
+    if (t.ilu_at || t.ncolours > 0 || t.max_row > kIluLanes || q.max_w > kIluLow) return;
+    int64_t m = 0;
+    for (TriSegment &g : q.seg)
+        if (!g.wide) {
+            g.map0 = m;
+            m += q.lev[g.lev1] - q.lev[g.lev0];
+        }
+    const size_t at = m * kIluLow * sizeof(int4), map = m * kIluLow * kIluLanes;
+    if (m == 0 || at + map > (size_t(1) << 29)) return;
+    if (hipMalloc(&t.ilu_at, at) != hipSuccess || hipMalloc(&t.ilu_map, map) != hipSuccess) {
+        (void)hipGetLastError();
+        if (t.ilu_at) hipFree(t.ilu_at);
+        t.ilu_at = nullptr;
+        t.ilu_map = nullptr;
+        return;
+    }
     const TriArgs a{t.rp, t.ci, t.dpos, t.side, t.lord, t.nlow};
-    k_ilu_map<<<static_cast<int>((m * kIluLanes + 255) / 256), 256, 0, s>>>(
-        a, t.s[0].row, t.n, t.ilu_at, t.ilu_map);
-    return true;
+    for (const TriSegment &g : q.seg) {
+        if (g.wide) continue;
+        const int64_t cnt = q.lev[g.lev1] - q.lev[g.lev0];
+        k_ilu_map<<<static_cast<int>((cnt * kIluLow * kIluLanes + 255) / 256), 256, 0, s>>>(
+            a, q.row + q.lev[g.lev0], static_cast<int>(cnt), t.ilu_at + g.map0 * kIluLow,
+            t.ilu_map + g.map0 * kIluLow * kIluLanes);
+    }
 }
 
 void run_factor(hipStream_t s, const TriOrder &t, const RowOp &r)
@@ -765,8 +781,10 @@ void run_factor(hipStream_t s, const TriOrder &t, const RowOp &r)
             k_tri_wide<<<(cnt + 255) / 256, 256, 0, s>>>(a, r, q.row + q.lev[g.lev0], cnt);
         } else if (r.op == OP_ILU && t.ilu_map) {
             auto kern = q.max_w <= 4 ? k_ilu_run<4> : k_ilu_run<kIluLow>;
-            kern<<<1, kNarrowThreads, 0, s>>>(a, q.row, q.d_lev, g.lev0, g.lev1, t.ilu_at,
-                                              t.ilu_map, r.f, r.flag);
+            kern<<<1, kNarrowThreads, 0, s>>>(a, q.row, q.d_lev, g.lev0, g.lev1,
+                                              t.ilu_at + g.map0 * kIluLow,
+                                              t.ilu_map + g.map0 * kIluLow * kIluLanes, r.f,
+                                              r.flag);
         } else {
             k_tri_narrow<<<1, kNarrowThreads, 0, s>>>(a, r, q.d_lev, q.row, g.lev0, g.lev1);
         }
@@ -1046,6 +1064,8 @@ msrsb_status tri_order_setup(msrsb_ctx *c, int ordering)
     t.wave = t.ncolours == 0 && n <= kNarrowLdsRows &&
              std::max(t.s[0].max_w, t.s[1].max_w) <= kTriWaveW &&
              std::max(t.s[0].max_cnt, t.s[1].max_cnt) <= 128;
+    // (SGS needs no factors, so the allocation-free application takes it on any
+    // order that is set up: its room comes with the order)
     if (!slab.upload(&t.slab) || !alloc_values(t, t.v[TRI_GS])) {
         free_tri_order(t);
         return MSRSB_E_NOMEM;
@@ -1076,7 +1096,7 @@ msrsb_status tri_factor(msrsb_ctx *c, int ordering, int kind)
     r.flag = flag;
     const int nb = static_cast<int>((c->nnz + 255) / 256);
     if (k == TRI_ILU) {
-        if (!ilu_maps(s, t)) return MSRSB_E_NOMEM;
+        ilu_maps(s, t);
         k_copy_vals<<<nb, 256, 0, s>>>(c->nnz, c->a, f);
         r.op = OP_ILU;
         run_factor(s, t, r);
