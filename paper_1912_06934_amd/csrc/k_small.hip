@@ -325,7 +325,7 @@ __global__ __launch_bounds__(kT) void k_pcg_small(SmallPcg a)
             const bool broken = bad_alpha || !isfinite(d[2]);
             restart = !broken && d[2] <= thr2;
             leave = broken || (!restart && (it >= a.max_iter || bad));
-            if (broken || (leave && it < a.max_iter)) code = kSmallBreakdown;
+            if (broken || (leave && bad)) code = kSmallBreakdown;
             if (restart || leave) continue;
         }
         restart = false;
