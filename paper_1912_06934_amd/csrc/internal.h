@@ -109,10 +109,10 @@ struct TriSide {
                                  // nothing on the upper side, else -1
 };
 
-// Values of one smoother on the packed sides: the entries, the diagonal's
-// reciprocals, the folded ones and the single-wavefront records.
+// Values of one smoother on the packed sides: the entries, the diagonals, the
+// folded ones (0: none) and the single-wavefront records.
 struct TriValues {
-    double *val[2] = {nullptr, nullptr}, *dinv[2] = {nullptr, nullptr}, *fold = nullptr;
+    double *val[2] = {nullptr, nullptr}, *diag[2] = {nullptr, nullptr}, *fold = nullptr;
     void *wave[2] = {nullptr, nullptr};
     void *slab = nullptr;  // the allocation they all lie in
     bool ok = false;

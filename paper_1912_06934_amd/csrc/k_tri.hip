@@ -223,7 +223,7 @@ __global__ __launch_bounds__(kNarrowThreads) void k_ilu_run(TriArgs t,
 
 // --- solves on the packed sides (TriSide, TriValues) ---
 //
-// One side's pass: x_i = (in_i - sum val x_col) dinv, with `in` the right-hand
+// One side's pass: x_i = (in_i - sum val x_col) / diag, with `in` the right-hand
 // side of the first pass or the first pass's x for the second.  A level's
 // columns, values and rows are packed level by level, so a row costs two
 // memory round trips (its packed data, then x at its columns) instead of four
@@ -242,7 +242,8 @@ constexpr int kTriFirst = INT32_MIN;
 
 struct TriPass {
     const int *row, *col;
-    const double *val, *dinv, *fold;  // fold: null unless this pass ends some rows
+    const double *val, *diag, *fold;  // diag: null for a unit one; fold: null unless
+                                      // this pass ends some rows
     const double *in;
     double *x, *z;
     bool last;  // every row of the pass ends here (z is written)
@@ -267,7 +268,7 @@ __global__ __launch_bounds__(256) void k_tri_level(TriPass p, int u0, int skip, 
     const int tt = blockIdx.x * 256 + threadIdx.x, t = tt - skip;
     if (t >= cnt) return;
     const int u = u0 + tt, i = p.row[u];
-    const double di = p.dinv[u], fo = p.fold ? p.fold[u] : 0.0;
+    const double di = p.diag ? p.diag[u] : 1.0, fo = p.fold ? p.fold[u] : 0.0;
     double s = p.in[i];
     constexpr int C = W > 0 ? W : 8;  // entries per step
     const int n = t < 0 ? 0 : W > 0 ? W : width;
@@ -296,9 +297,9 @@ __global__ __launch_bounds__(256) void k_tri_level(TriPass p, int u0, int skip, 
             s -= p.val[e] * (FIRST && c < 0 ? p.in : p.x)[c & ~kTriFirst];
         }
     }
-    s *= di;
+    if (p.diag) s /= di;
     const bool end = p.last || fo != 0.0;
-    if (fo != 0.0) s *= fo;
+    if (fo != 0.0) s /= fo;
     p.x[i] = s;
     if (end) tri_end(p, i, s);
 }
@@ -339,7 +340,7 @@ __global__ __launch_bounds__(kNarrowThreads) void k_tri_run(TriPass p,
         if (t >= cnt) return;
         const int64_t at = off[l] + t;
         q.i = p.row[u0 + t];
-        q.d = p.dinv[u0 + t];
+        q.d = p.diag ? p.diag[u0 + t] : 1.0;
         q.fo = p.fold ? p.fold[u0 + t] : 0.0;
 #pragma unroll
         for (int k = 0; k < REGS; ++k) {
@@ -369,9 +370,9 @@ __global__ __launch_bounds__(kNarrowThreads) void k_tri_run(TriPass p,
 #pragma unroll 4
             for (int64_t e = tail[u]; e < e1; ++e) s -= p.val[e] * x[p.col[e]];
         }
-        s *= q.d;
+        if (p.diag) s /= q.d;
         const bool end = p.last || q.fo != 0.0;
-        if (q.fo != 0.0) s *= q.fo;
+        if (q.fo != 0.0) s /= q.fo;
         x[q.i] = s;
         if (LDS) p.x[q.i] = s;
         if (end) tri_end(p, q.i, s);
@@ -396,15 +397,16 @@ __global__ __launch_bounds__(kNarrowThreads) void k_tri_run(TriPass p,
 // operations complete in order, so a level reads the x values the previous
 // levels wrote.  Levels of at most 64 rows per H, rows of at most kTriWaveW
 // entries per side (2D 9-point stencils and narrower): each level is H x 64
-// records of 64 bytes (LDS offsets, values, the diagonal's reciprocal; lanes
-// without a row work on the spare slot), stored lane by lane and loaded
+// records of 68 bytes (LDS offsets, values, the diagonal and its reciprocal;
+// lanes without a row work on the spare slot), stored lane by lane and loaded
 // kTriDepth levels ahead, so a level costs one LDS round trip, its products
 // and the instructions of one row per lane: the wavefront is alone on its
 // SIMD and bound by their issue.  The other wavefronts of the work-group only
 // move x in and z out.
 // 2 x 134 us (rows of two per lane, 128-byte records with counts and level
 // pointers, a division per row) + 2 x 5.8 us (records packed on each call) ->
-// 69 us per application of ILU(0) on 100 x 100 cells (298 levels a side).
+// 71 us per application of ILU(0) on 100 x 100 cells (298 levels a side).
+typedef __attribute__((address_space(3))) double lds_double;
 constexpr int kTriWaveW = 4;
 constexpr int kTriDepth = 6;    // levels loaded ahead
 constexpr int kTriTrip = 24;    // levels per loop trip (a multiple of kTriDepth)
@@ -412,18 +414,19 @@ constexpr int kTriTrip = 24;    // levels per loop trip (a multiple of kTriDepth
 struct alignas(16) WaveRec {
     int c[4];       // LDS byte offsets of the columns
     double v[4];
-    double d;
-    int i, pad;     // LDS byte offset of the row
+    double d, r;    // the diagonal and its reciprocal
 };
-// the records' four 16-byte quarters of the 64 lanes one after another
+// the 64 lanes' rows (LDS byte offsets), then the records' four 16-byte quarters
+// one after another
 struct WaveLevel {
+    int i[64];
     int4 q[4][64];
 };
 
 template <int H>
-__device__ __forceinline__ void tri_wave_side(char *sx, const WaveLevel *__restrict__ rec,
-                                              int nlev)
+__device__ __forceinline__ void tri_wave_side(const WaveLevel *__restrict__ rec, int nlev)
 {
+    auto x = [](int at) -> lds_double & { return *reinterpret_cast<lds_double *>(at); };
     const int lane = threadIdx.x;
     union Slot {
         int4 q[4];
@@ -431,51 +434,63 @@ __device__ __forceinline__ void tri_wave_side(char *sx, const WaveLevel *__restr
         __device__ Slot() {}
     };
     Slot ring[kTriDepth][H];
-    auto load = [&](int l, Slot(&s)[H]) {
+    int row[kTriDepth][H];
+    auto load = [&](int l, Slot(&s)[H], int(&i)[H]) {
 #pragma unroll
-        for (int h = 0; h < H; ++h)
+        for (int h = 0; h < H; ++h) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) s[h].q[k] = rec[l * H + h].q[k][lane];
+            i[h] = rec[l * H + h].i[lane];
+        }
     };
 #pragma unroll
-    for (int k = 0; k < kTriDepth; ++k) load(k, ring[k]);
+    for (int k = 0; k < kTriDepth; ++k) load(k, ring[k], row[k]);
     // the records hold a multiple of kTriTrip levels and kTriDepth more
     for (int l = 0; l < nlev; l += kTriTrip) {
 #pragma unroll
         for (int kk = 0; kk < kTriTrip; ++kk) {
             Slot(&cur)[H] = ring[kk % kTriDepth];
+            int(&at)[H] = row[kk % kTriDepth];
             // (the scheduling barriers keep a later level's arithmetic, and
             // with it the wait for its records, below this level's)
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int h = 0; h < H; ++h) {
                 const WaveRec &r = cur[h].r;
-                double s = *reinterpret_cast<double *>(sx + r.i);
+                double s = x(at[h]);
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
-                    s -= r.v[k] * *reinterpret_cast<double *>(sx + r.c[k]);
-                *reinterpret_cast<double *>(sx + r.i) = s * r.d;
+                    s -= r.v[k] * x(r.c[k]);
+                // s / d: the product with the reciprocal and one correction
+                const double q = s * r.r;
+                x(at[h]) = fma(fma(-q, r.d, s), r.r, q);
             }
-            load(l + kk + kTriDepth, cur);
+            load(l + kk + kTriDepth, cur, at);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
 }
 
+// (one wavefront per SIMD: to make room for more, the compiler would read a
+// level's columns from LDS one after another)
 template <int H>
-__global__ __launch_bounds__(256) void k_tri_wave(int n, const double *__restrict__ in,
-                                                  double *__restrict__ z, bool set,
-                                                  const WaveLevel *__restrict__ rec0, int nlev0,
-                                                  const WaveLevel *__restrict__ rec1, int nlev1)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_tri_wave(
+    int n, const double *__restrict__ in, double *__restrict__ z, bool set,
+    const WaveLevel *__restrict__ rec0, int nlev0, const WaveLevel *__restrict__ rec1, int nlev1)
 {
     extern __shared__ double sx[];  // x and a spare slot
     for (int i = threadIdx.x; i < n; i += 256) sx[i] = in[i];
     if (threadIdx.x == 0) sx[n] = 0.0;
     __syncthreads();
+    // The records' offsets are used as LDS addresses: sx is the kernel's only LDS
+    // and begins at address 0 (adding its base took 5 instructions a level, 75.3
+    // against 70.5 us).  The compiler is told that sx is reached by addresses.
+    asm volatile("" ::"v"(sx) : "memory");
     if (threadIdx.x < 64) {
-        if (rec0) tri_wave_side<H>(reinterpret_cast<char *>(sx), rec0, nlev0);
-        if (rec1) tri_wave_side<H>(reinterpret_cast<char *>(sx), rec1, nlev1);
+        if (rec0) tri_wave_side<H>(rec0, nlev0);
+        if (rec1) tri_wave_side<H>(rec1, nlev1);
     }
+    asm volatile("" ::: "memory");
     __syncthreads();
     for (int i = threadIdx.x; i < n; i += 256) z[i] = set ? sx[i] : z[i] + sx[i];
 }
@@ -547,13 +562,13 @@ __global__ __launch_bounds__(256) void k_tri_pack_diag(int n, const int *__restr
                                                        const int *__restrict__ dpos,
                                                        const int *__restrict__ foldsrc, bool unit,
                                                        const double *__restrict__ f,
-                                                       double *__restrict__ dinv,
+                                                       double *__restrict__ diag,
                                                        double *__restrict__ fold)
 {
     const int u = blockIdx.x * 256 + threadIdx.x;
     if (u >= n) return;
-    dinv[u] = unit ? 1.0 : 1.0 / f[dpos[row[u]]];
-    if (fold) fold[u] = foldsrc[u] < 0 ? 0.0 : 1.0 / f[foldsrc[u]];
+    diag[u] = unit ? 1.0 : f[dpos[row[u]]];
+    if (fold) fold[u] = foldsrc[u] < 0 ? 0.0 : f[foldsrc[u]];
 }
 
 // the wavefront's records of level blockIdx.x (levels past nlev: no rows)
@@ -565,7 +580,7 @@ __global__ __launch_bounds__(64 * H) void k_tri_pack_wave(int n, int nlev,
                                                           const int *__restrict__ row,
                                                           const int *__restrict__ col,
                                                           const double *__restrict__ val,
-                                                          const double *__restrict__ dinv,
+                                                          const double *__restrict__ diag,
                                                           WaveLevel *__restrict__ rec)
 {
     const int l = blockIdx.x, t = threadIdx.x;
@@ -573,9 +588,8 @@ __global__ __launch_bounds__(64 * H) void k_tri_pack_wave(int n, int nlev,
         int4 q[4];
         WaveRec r;
     } s;
-    s.r.i = 8 * n;
-    s.r.pad = 0;
-    s.r.d = 0.0;
+    int i = 8 * n;
+    s.r.d = s.r.r = 0.0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         s.r.c[k] = 8 * n;
@@ -583,8 +597,10 @@ __global__ __launch_bounds__(64 * H) void k_tri_pack_wave(int n, int nlev,
     }
     if (l < nlev && t < lev[l + 1] - lev[l]) {
         const int u = lev[l] + t, cnt = lev[l + 1] - lev[l], w = width[l];
-        s.r.i = 8 * row[u];
-        s.r.d = dinv[u];
+        i = 8 * row[u];
+        // (an infinite pivot: x = 0, by a correction of s * 0 with d = 0 as well)
+        s.r.r = 1.0 / diag[u];
+        s.r.d = s.r.r == 0.0 ? 0.0 : diag[u];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int64_t e = off[l] + static_cast<int64_t>(k) * cnt + t;
@@ -596,6 +612,7 @@ __global__ __launch_bounds__(64 * H) void k_tri_pack_wave(int n, int nlev,
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k) rec[l * H + t / 64].q[k][t & 63] = s.q[k];
+    rec[l * H + t / 64].i[t & 63] = i;
 }
 
 // upper entries of the IC(0) array take the factor value of their transpose
@@ -865,11 +882,11 @@ bool alloc_values(const TriOrder &t, TriValues &v)
         bytes += (m + 255) / 256 * 256;
         return at;
     };
-    size_t val[2], dinv[2], wave[2];
+    size_t val[2], diag[2], wave[2];
     for (int side = 0; side < 2; ++side) {
         const TriSide &q = t.s[side];
         val[side] = place(q.places * sizeof(double));
-        dinv[side] = place(t.n * sizeof(double));
+        diag[side] = place(t.n * sizeof(double));
         wave[side] = place(!t.wave ? 0
                                    : static_cast<size_t>(wave_levels(q) + kTriDepth) *
                                          wave_rows(t) * sizeof(WaveLevel));
@@ -879,7 +896,7 @@ bool alloc_values(const TriOrder &t, TriValues &v)
     char *base = static_cast<char *>(v.slab);
     for (int side = 0; side < 2; ++side) {
         v.val[side] = reinterpret_cast<double *>(base + val[side]);
-        v.dinv[side] = reinterpret_cast<double *>(base + dinv[side]);
+        v.diag[side] = reinterpret_cast<double *>(base + diag[side]);
         v.wave[side] = base + wave[side];
     }
     v.fold = reinterpret_cast<double *>(base + fold);
@@ -899,16 +916,16 @@ void pack_values(hipStream_t s, TriOrder &t, int kind, const double *f)
                 m, q.src, q.col, t.dpos, first && !unit, f, v.val[side]);
         const bool fold = side == 0 && kind != TRI_GS && t.sym_pattern;
         k_tri_pack_diag<<<(t.n + 255) / 256, 256, 0, s>>>(t.n, q.row, t.dpos, q.fold, unit, f,
-                                                          v.dinv[side], fold ? v.fold : nullptr);
+                                                          v.diag[side], fold ? v.fold : nullptr);
         if (!t.wave) continue;
         const int nlev = static_cast<int>(q.lev.size()) - 1, nl = wave_levels(q) + kTriDepth;
         auto *rec = static_cast<WaveLevel *>(v.wave[side]);
         if (wave_rows(t) == 1)
             k_tri_pack_wave<1><<<nl, 64, 0, s>>>(t.n, nlev, q.d_lev, q.d_width, q.d_off, q.row,
-                                                 q.col, v.val[side], v.dinv[side], rec);
+                                                 q.col, v.val[side], v.diag[side], rec);
         else
             k_tri_pack_wave<2><<<nl, 128, 0, s>>>(t.n, nlev, q.d_lev, q.d_width, q.d_off, q.row,
-                                                  q.col, v.val[side], v.dinv[side], rec);
+                                                  q.col, v.val[side], v.diag[side], rec);
     }
     v.ok = true;
 }
@@ -939,7 +956,8 @@ void run_solve(hipStream_t s, const TriOrder &t, int kind, int side0, int side1,
     for (int side = side0;; side = side1) {
         const TriSide &q = t.s[side];
         const bool second = side != side0, last = side == side1;
-        const TriPass p{q.row, q.col, v.val[side], v.dinv[side],
+        const bool unit = kind == TRI_ILU && side == 0;
+        const TriPass p{q.row, q.col, v.val[side], unit ? nullptr : v.diag[side],
                         !last && t.sym_pattern ? v.fold : nullptr,
                         second ? x : res, x, z, last, set};
         run_side(s, t, q, p, second);
