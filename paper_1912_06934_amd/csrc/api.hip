@@ -1574,7 +1574,7 @@ msrsb_status msrsb_setup_basis(msrsb_ctx *c, const msrsb_basis_opts *o, msrsb_ba
                (o->tol >= 0.0 || k + static_cast<int64_t>(o->check_every) >= o->max_iter);
     };
     sa.eit_out = c->eit_val;
-    const int most = small ? INT32_MAX : std::max(smooth_tile_steps(sa, c->j_grid_nx), 1);
+    const int most = small ? INT32_MAX : std::max(smooth_tile_steps(sa, c->j_grid_nx, fp32), 1);
     for (it = 0; it < o->max_iter; ++it) {
         const int src = c->pcur, dst = 1 - c->pcur;
         bool check = checked(it);

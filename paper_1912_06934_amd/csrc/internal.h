@@ -661,7 +661,7 @@ int launch_tile_post(hipStream_t s, int n, const DiaOffsets &d, const double *a,
                      int nx, int sweeps, double *zout, const double *zold, double *part);
 // up to smooth_tile_steps (0: not served) steps per launch on a 2D grid of nx
 // cells a line (0: none); eit_part is used with eit_step
-int smooth_tile_steps(const SmoothArgs &a, int nx);
+int smooth_tile_steps(const SmoothArgs &a, int nx, bool fp32);
 void launch_smooth_tile(hipStream_t s, const SmoothArgs &a, int nx, bool fp32, const double *jv64,
                         const float *jv32, const double *pin64, double *pout64,
                         const float *pin32, float *pout32, int steps, int eit_step);
@@ -727,6 +727,7 @@ void launch_dia_sweep(hipStream_t s, int n, const DiaOffsets &d, bool fp32, cons
 // upd, two sweeps from zero into zout and the residual res = r - A zout on a 2D
 // grid of nx cells a line (grid2d_width); one r.r partial per work-group
 int tile_pre_groups(int n, int nx);
+constexpr int kTileCells = 28 * 12;  // of a tile of launch_tile_pre and launch_tile_post
 void launch_tile_pre(hipStream_t s, int n, const DiaOffsets &d, const double *a, const float *a32,
                      const double *dinv, const float *dinv32, int nx, double *zout, double *res,
                      const UpdArgs &upd);

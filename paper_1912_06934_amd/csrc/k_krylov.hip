@@ -1150,6 +1150,7 @@ __global__ __launch_bounds__(kBlock) void k_pcg_update_sweep2(int n, DiaOffsets 
 // and one for the residual.  250 x 187 in FP64: 4.2 + 2.7 us in two launches,
 // 4.8 us here.
 constexpr int kPreX = 32, kPreY = 16, kPreHalo = 2, kPreT = kPreX * kPreY;
+static_assert((kPreX - 2 * kPreHalo) * (kPreY - 2 * kPreHalo) == kTileCells);
 template <int ND, bool SYM, typename MT>
 __global__ __launch_bounds__(kPreT) void k_tile_pre(int n, DiaOffsets d, const MT *__restrict__ a,
                                                     const MT *__restrict__ dinv, int nx, int ny,

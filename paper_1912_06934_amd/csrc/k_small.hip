@@ -621,6 +621,11 @@ void smooth_small(hipStream_t s, const SmoothArgs &a, const T *jv, T *p, int ste
     go(k_smooth_small<T, NDT, PW, 1>);
 }
 
+int smooth_tiles(int n, int nx)
+{
+    return ((nx + kTile - 1) / kTile) * ((n / nx + kTile - 1) / kTile);
+}
+
 template <int NDT, int PW>
 void launch_small(hipStream_t s, const SmallPcg &a)
 {
@@ -638,6 +643,7 @@ void launch_small(hipStream_t s, const SmallPcg &a)
 // Bound by the launch and three dependent round trips.
 // 250 x 187 in FP64, two sweeps: 3.0 + 3.0 + 3.7 us in three launches, 3.9 here.
 constexpr int kPostX = 32, kPostY = 16, kPostHalo = 2, kPostT = kPostX * kPostY;
+static_assert((kPostX - 2 * kPostHalo) * (kPostY - 2 * kPostHalo) == kTileCells);
 template <int ND, bool SYM, typename MT, typename PT>
 __global__ __launch_bounds__(kPostT) void k_tile_post(
     int n, DiaOffsets d, const MT *__restrict__ a, const MT *__restrict__ dinv,
@@ -751,9 +757,32 @@ void launch_smooth_small(hipStream_t s, const SmoothArgs &a, bool fp32, const do
     else go(c9{}, c4{});
 }
 
-int smooth_tile_steps(const SmoothArgs &a, int nx)
+// Where the launches no longer bound the steps, the tiles' arithmetic (1.8 times
+// a step's, and more where the last tile of a line is nearly empty) does.
+// Microseconds a step, launch by launch / tiles:
+//   five neighbours   FP64                     FP32
+//   512 x 512         6.8 /  4.2 (484 tiles)   5.3 /  3.0
+//   25 x 10,900       7.3 /  7.1 (910)         5.3 /  4.8
+//   1000 x 1000      22.6 / 15.0 (1,764)      11.1 /  8.9
+//   49 x 20,400      21.1 / 19.7 (2,550)      11.1 / 11.6   tiles 1.5 times the grid
+//   30 x 33,334      21.6 / 20.8 (2,778)      11.0 / 12.5   1.6 times
+//   25 x 40,000      21.7 / 25.0 (3,334)      10.9 / 15.0   1.9 times
+//   nine neighbours
+//   512 x 512        13.9 /  6.9               6.6 /  5.4
+//   25 x 6,250        8.8 /  8.1 (522)         5.7 /  7.2
+//   600 x 600        19.0 / 10.5 (625)         7.8 /  7.8
+//   1000 x 1000      54.5 / 23.9              14.1 / 21.7
+//   25 x 40,000      54.5 / 39.6              13.7 / 36.7
+// So nine neighbours in FP32 take the tiles while all of them run at once (two to
+// each of 256 compute units), five neighbours up to twice that or while the tiles
+// are little larger than the grid, nine in FP64 always.
+int smooth_tile_steps(const SmoothArgs &a, int nx, bool fp32)
 {
-    return nx > 0 && a.pw == 4 && a.jmap_kind == 1 && (a.jw == 5 || a.jw == 9) ? kHalo : 0;
+    if (nx <= 0 || a.pw != 4 || a.jmap_kind != 1 || (a.jw != 5 && a.jw != 9)) return 0;
+    const int64_t tiles = smooth_tiles(a.n, nx);
+    if (a.jw == 9) return !fp32 || tiles <= 512 ? kHalo : 0;
+    const bool close = 10 * tiles * kTile * kTile <= (fp32 ? 13 : 17) * static_cast<int64_t>(a.n);
+    return tiles <= 1024 || close ? kHalo : 0;
 }
 
 void launch_smooth_tile(hipStream_t s, const SmoothArgs &a, int nx, bool fp32, const double *jv64,
@@ -761,7 +790,7 @@ void launch_smooth_tile(hipStream_t s, const SmoothArgs &a, int nx, bool fp32, c
                         const float *pin32, float *pout32, int steps, int eit_step)
 {
     const int ny = a.n / nx, ntx = (nx + kTile - 1) / kTile;
-    const int grid = ntx * ((ny + kTile - 1) / kTile);
+    const int grid = smooth_tiles(a.n, nx);
     auto go = [&](auto nd) {
         constexpr int ND = decltype(nd)::value;
         if (fp32)

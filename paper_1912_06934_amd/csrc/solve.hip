@@ -661,8 +661,15 @@ void apply_two_stage(msrsb_ctx *c, const msrsb_solve_opts *o, const double *v, d
     if (pre_k == MSRSB_SMOOTH_NONE) pre_n = 0;
     if (post_k == MSRSB_SMOOTH_NONE) post_n = 0;
     // the stages after the coarse solve, and the update with two pre-sweeps and
-    // their residual, in one launch each, inside PCG on a 2D grid
-    bool grid2d = dots && o->use_multiscale && c->a_grid_nx > 0 && op.d.n == c->a_off.n;
+    // their residual, in one launch each, inside PCG on a 2D grid.  In FP64 they
+    // are faster from 64 x 64 (18.5 us an iteration, 23.9 without the one and 20.4
+    // without the other) to 2000 x 2000 (288 us, 309 and 303) and on long narrow
+    // grids; in FP32 not on large grids whose tiles are half empty (30 x 33,334:
+    // 74 us, 72 without the first; 1000 x 1000: 64.7, 70.7 and 69.8).
+    bool grid2d = dots && o->use_multiscale && c->a_grid_nx > 0 && op.d.n == c->a_off.n &&
+                  (!fp32 || n <= 200000 ||
+                   2 * static_cast<int64_t>(tile_pre_groups(n, c->a_grid_nx)) * kTileCells <=
+                       3 * static_cast<int64_t>(n));
     for (int k = 0; grid2d && k < op.d.n; ++k) grid2d = op.d.off[k] == c->a_off.off[k];
     const bool post_tile = grid2d && c->pw == 4 && c->pcol16 && is_diag(post_k) && post_n >= 1 &&
                            post_n <= kPostSweeps;
