@@ -564,6 +564,13 @@ __device__ inline void sum_partials_block(int nb, const double *__restrict__ par
     }
 }
 
+// whether the last step's beta broke down: its direction is not taken (the
+// host, which is told with this step's post, ends there)
+__device__ __forceinline__ bool step_stopped(const double *__restrict__ scal)
+{
+    return scal[S_BREAK_BETA] != 0.0;
+}
+
 // (the first step that breaks down is kept)
 __device__ inline void note_break(double *__restrict__ flag, double tag)
 {
@@ -574,13 +581,15 @@ __global__ __launch_bounds__(kFinThreads) void k_fin_alpha(int nb, const double 
                                                            double *__restrict__ scal, int rzs,
                                                            double tag)
 {
-    // the scalar read first, so that its load overlaps the partials' loads
+    // the scalars read first, so that their loads overlap the partials' loads
     const double rz = scal[rzs];
+    const bool stop = step_stopped(scal);
     double t[1];
     sum_partials_block<1>(nb, part, t);
     if (threadIdx.x != 0) return;
     bool bad;
-    scal[S_ALPHA] = alpha_of(rz, t[0], bad);
+    const double alpha = alpha_of(rz, t[0], bad);
+    scal[S_ALPHA] = stop ? 0.0 : alpha;
     scal[S_PQ] = t[0];
     if (bad) note_break(scal + S_BREAK, tag);
 }
@@ -639,12 +648,14 @@ __device__ __forceinline__ void group_totals(const double *const (&src)[NV], con
 }
 
 // alpha of the update, from the partials or from scal (every thread of the
-// work-group calls it); work-group 0 records a breakdown
+// work-group calls it); work-group 0 records a breakdown.  With alpha = 0 the
+// update leaves x alone (p need not be finite).
 template <int B = kBlock>
 __device__ __forceinline__ double step_alpha(const UpdArgs &u)
 {
     if (u.npq == 0) return u.scal[S_ALPHA];
     const double rz = u.scal[u.rz];
+    const bool stop = step_stopped(u.scal);
     const double *const src[1] = {u.pq};
     const int m[1] = {u.npq};
     double t[1];
@@ -652,13 +663,7 @@ __device__ __forceinline__ double step_alpha(const UpdArgs &u)
     bool bad;
     const double alpha = alpha_of(rz, t[0], bad);
     if (bad && blockIdx.x == 0 && threadIdx.x == 0) note_break(u.scal + S_BREAK, u.tag);
-    return alpha;
-}
-// whether the last step's beta broke down: its direction is not taken (the
-// host, which is told with this step's post, ends there)
-__device__ __forceinline__ bool step_stopped(const UpdArgs &u)
-{
-    return u.scal[S_BREAK_BETA] != 0.0;
+    return stop ? 0.0 : alpha;
 }
 
 // beta of the direction, likewise; work-group 0 keeps the new r.z
@@ -1089,8 +1094,10 @@ __global__ __launch_bounds__(kBlock) void k_dia_sweep2_zero(int n, DiaOffsets d,
 // fused with the two sweeps from zero above (tiled form) that read the
 // updated residual: a row's own r_out goes through LDS as z1 = dinv r_out,
 // and outside the tile r_in and q are read and the update formed on the spot.
-// r_out must not alias r_in (other work-groups still read r_in).
-template <int ND, bool SYM, typename MT, typename ZT>
+// r_out must not alias r_in (other work-groups still read r_in).  SUMS: alpha is
+// formed here (in one kernel with the other form, the sums' registers cost large
+// problems a wavefront per SIMD).
+template <int ND, bool SYM, typename MT, typename ZT, bool SUMS>
 __global__ __launch_bounds__(kBlock) void k_pcg_update_sweep2(int n, DiaOffsets d,
                                                               const MT *__restrict__ a,
                                                               const MT *__restrict__ dinv,
@@ -1101,6 +1108,7 @@ __global__ __launch_bounds__(kBlock) void k_pcg_update_sweep2(int n, DiaOffsets 
     const int i = xcd_row();
     const int t = threadIdx.x;
     const int ic = i < n ? i : n - 1;
+    double alpha = SUMS ? 0.0 : u.scal[S_ALPHA];
     const TileRows<ND> r(i, ic, t, n, d);
     TileCoefs<ND, SYM, MT> c;
     c.load(a, n, ic, t, r, sa);
@@ -1115,8 +1123,7 @@ __global__ __launch_bounds__(kBlock) void k_pcg_update_sweep2(int n, DiaOffsets 
         }
     const double xi = u.x[ic], pi = u.p[ic], ri = u.rin[ic], qi = u.q[ic];
     const MT di = dinv[ic];
-    const bool stop = step_stopped(u);
-    const double alpha = step_alpha(u);  // (after the loads, which it waits with)
+    if constexpr (SUMS) alpha = step_alpha(u);  // (after the loads, which it waits with)
     const double vi = pcg_residual(ri, qi, alpha);
     sz1[t] = static_cast<MT>(static_cast<double>(di * static_cast<MT>(vi)));
     __syncthreads();
@@ -1137,7 +1144,7 @@ __global__ __launch_bounds__(kBlock) void k_pcg_update_sweep2(int n, DiaOffsets 
     if (i < n) {
         const double z1i = static_cast<double>(di * static_cast<MT>(vi));
         zout[i] = static_cast<ZT>(z1i + static_cast<double>(di * (static_cast<MT>(vi) - s)));
-        if (!stop) u.x[i] = fma(alpha, pi, xi);
+        u.x[i] = alpha != 0.0 ? fma(alpha, pi, xi) : xi;
         u.rout[i] = vi;
         rr[0] = vi * vi;
     }
@@ -1182,7 +1189,6 @@ __global__ __launch_bounds__(kPreT) void k_tile_pre(int n, DiaOffsets d, const M
         const bool there = tx + dx >= 0 && tx + dx < kPreX && ty + dy >= 0 && ty + dy < kPreY;
         at[o] = there ? t + dx + kPreX * dy : t;  // (past the edge: not right, not used)
     }
-    const bool stop = step_stopped(u);
     const double alpha = step_alpha<kPreT>(u);
     const double vi = in ? pcg_residual(ri, qi, alpha) : 0.0;
     const double z1 = static_cast<double>(di * static_cast<MT>(vi));
@@ -1201,7 +1207,7 @@ __global__ __launch_bounds__(kPreT) void k_tile_pre(int n, DiaOffsets d, const M
     if (own) {
         zout[i] = z;
         res[i] = vi - static_cast<double>(s2);
-        if (!stop) u.x[i] = fma(alpha, pi, xi);
+        u.x[i] = alpha != 0.0 ? fma(alpha, pi, xi) : xi;
         u.rout[i] = vi;
         rr = vi * vi;
     }
@@ -1348,7 +1354,8 @@ __global__ __launch_bounds__(kBlock) void k_pcg_p_spmv(
 // outside the tile (+-nx ny, the other half of +-nx, the tile-edge +-1) are
 // loaded from memory, all before the barrier.  Rows of a work-group are
 // contiguous (xcd_row).  Same arithmetic and order as the kernel above.
-template <int ND, bool SYM>
+// SUMS: beta is formed here.
+template <int ND, bool SYM, bool SUMS>
 __global__ __launch_bounds__(kBlock) void k_pcg_p_spmv_dia(
     int n, DiaOffsets d, const double *__restrict__ ad, const double *__restrict__ z,
     const double *__restrict__ pold, double *__restrict__ pnew, double *__restrict__ q,
@@ -1362,7 +1369,7 @@ __global__ __launch_bounds__(kBlock) void k_pcg_p_spmv_dia(
     const int ic = i < n ? i : n - 1;
     // beta = 0 in scal: a restart, p_old is not read; a beta formed here from
     // the partials comes after the loads, which it waits with
-    double beta = sums.ndots == 0 ? step_beta(sums) : 1.0;
+    double beta = SUMS ? 1.0 : sums.scal[S_BETA];
     const bool restart = beta == 0.0;
     double av[ND], zk[ND], pk[ND];
     bool in[ND], loc[ND];
@@ -1387,7 +1394,7 @@ __global__ __launch_bounds__(kBlock) void k_pcg_p_spmv_dia(
 #pragma unroll
         for (int o = MID + 1; o < ND; ++o) sa[o - MID - 1][t] = av[o];
     }
-    if (sums.ndots > 0) beta = step_beta(sums);
+    if constexpr (SUMS) beta = step_beta(sums);
     __syncthreads();
 #pragma unroll
     for (int o = 0; o < ND; ++o) {
@@ -1428,11 +1435,10 @@ __global__ __launch_bounds__(kBlock) void k_pcg_update(int n, UpdArgs u, double 
     const int ic = i < n ? i : n - 1;
     const double xi = u.x[ic], pi = u.p[ic], ri = u.rin[ic], qi = u.q[ic];
     const MT di = z ? dinv[ic] : MT(0);
-    const bool stop = step_stopped(u);
     const double alpha = step_alpha(u);
     double v[1] = {0.0};
     if (i < n) {
-        if (!stop) u.x[i] = fma(alpha, pi, xi);
+        u.x[i] = alpha != 0.0 ? fma(alpha, pi, xi) : xi;
         const double r = pcg_residual(ri, qi, alpha);
         u.rout[i] = r;
         if (z) z[i] = static_cast<double>(di * static_cast<MT>(r));
@@ -1852,6 +1858,14 @@ void with_ndiag(const DiaOffsets &d, F &&f)
     }
 }
 
+// f(whether a scalar is formed from this many partials by its consumer)
+template <typename F>
+static void with_sums(int partials, F &&f)
+{
+    if (partials > 0) f(std::true_type{});
+    else f(std::false_type{});
+}
+
 #define MSRSB_DIA_ARGS(nd, sym) decltype(nd)::value, decltype(sym)::value
 
 void launch_dia_spmv(hipStream_t s, int n, const DiaOffsets &d, const double *a, const double *x,
@@ -1886,12 +1900,15 @@ void launch_dia_sweep(hipStream_t s, int n, const DiaOffsets &d, bool fp32, cons
             // v is upd->rout; the tiled stencils fuse the update, others
             // take it first on its own
             if constexpr (kTiled<ND, double>) {
-                if (fp32)
-                    k_pcg_update_sweep2<MSRSB_DIA_ARGS(nd, sym), float, double>
-                        <<<grid_for(n), kBlock, 0, s>>>(n, d, a32, dinv32, zout, *upd);
-                else
-                    k_pcg_update_sweep2<MSRSB_DIA_ARGS(nd, sym), double, double>
-                        <<<grid_for(n), kBlock, 0, s>>>(n, d, a64, dinv64, zout, *upd);
+                with_sums(upd->npq, [&](auto sums) {
+                    constexpr bool SUMS = decltype(sums)::value;
+                    if (fp32)
+                        k_pcg_update_sweep2<MSRSB_DIA_ARGS(nd, sym), float, double, SUMS>
+                            <<<grid_for(n), kBlock, 0, s>>>(n, d, a32, dinv32, zout, *upd);
+                    else
+                        k_pcg_update_sweep2<MSRSB_DIA_ARGS(nd, sym), double, double, SUMS>
+                            <<<grid_for(n), kBlock, 0, s>>>(n, d, a64, dinv64, zout, *upd);
+                });
                 return;
             }
             launch_pcg_update(s, n, *upd);
@@ -1969,8 +1986,11 @@ void launch_prec_f32_pre(hipStream_t s, int n, const DiaOffsets &d, const float 
         bool fused = false;
         if constexpr (kTiled<ND, double>) {
             if (upd) {
-                k_pcg_update_sweep2<MSRSB_DIA_ARGS(nd, sym), float, float>
-                    <<<grid_for(n), kBlock, 0, s>>>(n, d, a32, dinv32, z1, *upd);
+                with_sums(upd->npq, [&](auto sums) {
+                    k_pcg_update_sweep2<MSRSB_DIA_ARGS(nd, sym), float, float,
+                                        decltype(sums)::value>
+                        <<<grid_for(n), kBlock, 0, s>>>(n, d, a32, dinv32, z1, *upd);
+                });
                 fused = true;
             }
         }
@@ -2039,8 +2059,10 @@ int launch_pcg_p_spmv(hipStream_t s, int n, const DiaOffsets &d, const double *a
         with_ndiag(d, [&](auto nd, auto sym) {
             constexpr int ND = decltype(nd)::value;
             if constexpr (ND > 0 && ND <= 9)
-                k_pcg_p_spmv_dia<MSRSB_DIA_ARGS(nd, sym)><<<grid_for(n), kBlock, 0, s>>>(
-                    n, d, ad, z, pold, pnew, q, part, sums);
+                with_sums(sums.ndots, [&](auto here) {
+                    k_pcg_p_spmv_dia<MSRSB_DIA_ARGS(nd, sym), decltype(here)::value>
+                        <<<grid_for(n), kBlock, 0, s>>>(n, d, ad, z, pold, pnew, q, part, sums);
+                });
             else
                 k_pcg_p_spmv<MSRSB_DIA_ARGS(nd, sym)><<<grid_for(n), kBlock, 0, s>>>(
                     n, d, ad, rp, ci, a, z, pold, pnew, q, part, sums);
