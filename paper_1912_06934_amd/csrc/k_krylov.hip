@@ -1222,8 +1222,8 @@ __global__ __launch_bounds__(kPreT) void k_tile_pre(int n, DiaOffsets d, const M
     }
 }
 
-// last smoothing sweep of the preconditioner inside PCG, fused with the dot
-// products r.z and r.(z - z_old) and the flexible beta
+// last smoothing sweep of the preconditioner inside PCG, with the partials of
+// r.z and r.(z - z_old) for the next direction's beta
 template <int ND, bool SYM, typename MT, typename ZT = double>
 __global__ __launch_bounds__(kBlock) void k_dia_sweep_dots(
     int n, DiaOffsets d, const MT *__restrict__ a, const MT *__restrict__ dinv,
@@ -1271,9 +1271,9 @@ __global__ __launch_bounds__(kBlock) void k_dots(int n, const double *__restrict
     block_partials<2>(v, part);
 }
 
-// p_new = z + beta p_old, q = A p_new, p_new.q and alpha = (r.z) / (p.q).
-// DIA: ND and SYM as in dia_dot; ND < 0 is the CSR form.  beta == 0 (a
-// restart) never reads p_old.
+// p_new = z + beta p_old, q = A p_new and the partials of p_new.q, of which the
+// update forms alpha.  DIA: ND and SYM as in dia_dot; ND < 0 is the CSR form.
+// beta == 0 (a restart) never reads p_old.
 template <int ND, bool SYM>
 __global__ __launch_bounds__(kBlock) void k_pcg_p_spmv(
     int n, DiaOffsets d, const double *__restrict__ ad, const int *__restrict__ rp,
@@ -2005,8 +2005,8 @@ void launch_prec_f32_pre(hipStream_t s, int n, const DiaOffsets &d, const float 
     restrict_kernels<float, float>(s, nc, rrp, rci, roff16, rbase, r32, tmp, vc, boxes, post);
 }
 
-// _post: z1 += P wc, z2 = sweep(z1), z = sweep(z2) with r.z, r.(z - zold)
-// and the flexible beta
+// _post: z1 += P wc, z2 = sweep(z1), z = sweep(z2) with the partials of r.z and
+// r.(z - zold); returns their number
 int launch_prec_f32_post(hipStream_t s, int n, const DiaOffsets &d, const float *a32,
                          const float *dinv32, const double *v, float *z1, float *z2, int pw,
                          const uint16_t *pcol16, const float *p32, const double *wc,

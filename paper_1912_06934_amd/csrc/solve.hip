@@ -459,7 +459,8 @@ msrsb_status ensure_workspace(msrsb_ctx *c)
         if (dev_alloc(&p, n)) return MSRSB_E_NOMEM;
     for (auto &p : c->wf)
         if (dev_alloc(&p, n)) return MSRSB_E_NOMEM;
-    // (PCG: two products' partials, then the p.q ones, at most one per 192 rows)
+    // (PCG: two products' partials, then the p.q ones, at most one per 128 rows: the
+    // 64 nodes of a work-group at two components each)
     const size_t np = std::max<size_t>({pq_offset(n) + n / 128 + 16, 2 * static_cast<size_t>(kReduceBlocks),
                                         64 * static_cast<size_t>(std::max(c->nc, 1)) + 64,
                                         static_cast<size_t>(64 * 66),
@@ -570,8 +571,9 @@ msrsb_status ensure_smoother(msrsb_ctx *c, const msrsb_solve_opts *o, bool trans
 // z = B v (Alg. 4): z = 0; pre-smoothing; z += P M_c^{-1} R (v - A z);
 // post-smoothing.  With trans the preconditioner of A^T is applied: A^T, the
 // smoothers of A^T, pre and post exchanged, and A_c^{-T}.  With dots (inside
-// PCG) the products r.z and r.(z - zold) and the flexible beta are formed as
-// well, fused into the last sweep when possible.
+// PCG) the partials of r.z and r.(z - zold) are formed as well, in the last
+// sweep when possible, and left to the next direction, or to the one-block
+// kernel that forms beta.
 // wc = A_c^{-1} vc (A_c^{-T} for trans): the SPD path's symmetric inverse
 // from its packed lower tiles, otherwise the dense product
 static void coarse_apply(msrsb_ctx *c, bool trans, const ApplyBufs &b)
