@@ -397,7 +397,7 @@ __global__ __launch_bounds__(kNarrowThreads) void k_tri_run(TriPass p,
 // operations complete in order, so a level reads the x values the previous
 // levels wrote.  Levels of at most 64 rows per H, rows of at most kTriWaveW
 // entries per side (2D 9-point stencils and narrower): each level is H x 64
-// records of 68 bytes (LDS offsets, values, the diagonal and its reciprocal;
+// records of 80 bytes (LDS offsets, values, the diagonal and its reciprocal;
 // lanes without a row work on the spare slot), stored lane by lane and loaded
 // kTriDepth levels ahead, so a level costs one LDS round trip, its products
 // and the instructions of one row per lane: the wavefront is alone on its
@@ -405,7 +405,7 @@ __global__ __launch_bounds__(kNarrowThreads) void k_tri_run(TriPass p,
 // move x in and z out.
 // 2 x 134 us (rows of two per lane, 128-byte records with counts and level
 // pointers, a division per row) + 2 x 5.8 us (records packed on each call) ->
-// 71 us per application of ILU(0) on 100 x 100 cells (298 levels a side).
+// 66 us per application of ILU(0) on 100 x 100 cells (298 levels a side).
 typedef __attribute__((address_space(3))) double lds_double;
 constexpr int kTriWaveW = 4;
 constexpr int kTriDepth = 6;    // levels loaded ahead
@@ -415,12 +415,13 @@ struct alignas(16) WaveRec {
     int c[4];       // LDS byte offsets of the columns
     double v[4];
     double d, r;    // the diagonal and its reciprocal
+    int i, pad[3];  // LDS byte offset of the row
 };
-// the 64 lanes' rows (LDS byte offsets), then the records' four 16-byte quarters
-// one after another
+// the records' five 16-byte parts of the 64 lanes one after another: all within
+// reach of one address, the third part's
+constexpr int kWaveParts = 5;
 struct WaveLevel {
-    int i[64];
-    int4 q[4][64];
+    int4 q[kWaveParts][64];
 };
 
 template <int H>
@@ -429,7 +430,7 @@ __device__ __forceinline__ void tri_wave_side(const WaveLevel *__restrict__ rec,
     auto x = [](int at) -> lds_double & { return *reinterpret_cast<lds_double *>(at); };
     const int lane = threadIdx.x;
     union Slot {
-        int4 q[4];
+        int4 q[kWaveParts - 1];
         WaveRec r;
         __device__ Slot() {}
     };
@@ -438,9 +439,15 @@ __device__ __forceinline__ void tri_wave_side(const WaveLevel *__restrict__ rec,
     auto load = [&](int l, Slot(&s)[H], int(&i)[H]) {
 #pragma unroll
         for (int h = 0; h < H; ++h) {
+            typedef __attribute__((address_space(1))) const int4 global_int4;
+            global_int4 *at = (global_int4 *)&rec[l * H + h].q[2][lane];
+            asm("" : "+v"(at));  // (not taken apart into one address per part)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) s[h].q[k] = rec[l * H + h].q[k][lane];
-            i[h] = rec[l * H + h].i[lane];
+            for (int k = 0; k < kWaveParts - 1; ++k) {
+                const int *part = (const int *)(at + 64 * (k - 2));
+                s[h].q[k] = *(const int4 *)part;
+            }
+            i[h] = *(const int *)(at + 64 * 2);
         }
     };
 #pragma unroll
@@ -461,9 +468,10 @@ __device__ __forceinline__ void tri_wave_side(const WaveLevel *__restrict__ rec,
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
                     s -= r.v[k] * x(r.c[k]);
-                // s / d: the product with the reciprocal and one correction
+                // s / d: the product with the reciprocal and one correction (and
+                // what zeros and infinities give)
                 const double q = s * r.r;
-                x(at[h]) = fma(fma(-q, r.d, s), r.r, q);
+                x(at[h]) = __builtin_amdgcn_div_fixup(fma(fma(-q, r.d, s), r.r, q), r.d, s);
             }
             load(l + kk + kTriDepth, cur, at);
             __builtin_amdgcn_sched_barrier(0);
@@ -585,11 +593,12 @@ __global__ __launch_bounds__(64 * H) void k_tri_pack_wave(int n, int nlev,
 {
     const int l = blockIdx.x, t = threadIdx.x;
     union {
-        int4 q[4];
+        int4 q[kWaveParts];
         WaveRec r;
     } s;
-    int i = 8 * n;
-    s.r.d = s.r.r = 0.0;
+    s.r.i = 8 * n;
+    s.r.pad[0] = s.r.pad[1] = s.r.pad[2] = 0;
+    s.r.d = s.r.r = 1.0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         s.r.c[k] = 8 * n;
@@ -597,10 +606,9 @@ __global__ __launch_bounds__(64 * H) void k_tri_pack_wave(int n, int nlev,
     }
     if (l < nlev && t < lev[l + 1] - lev[l]) {
         const int u = lev[l] + t, cnt = lev[l + 1] - lev[l], w = width[l];
-        i = 8 * row[u];
-        // (an infinite pivot: x = 0, by a correction of s * 0 with d = 0 as well)
+        s.r.i = 8 * row[u];
+        s.r.d = diag[u];
         s.r.r = 1.0 / diag[u];
-        s.r.d = s.r.r == 0.0 ? 0.0 : diag[u];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int64_t e = off[l] + static_cast<int64_t>(k) * cnt + t;
@@ -611,8 +619,7 @@ __global__ __launch_bounds__(64 * H) void k_tri_pack_wave(int n, int nlev,
         }
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) rec[l * H + t / 64].q[k][t & 63] = s.q[k];
-    rec[l * H + t / 64].i[t & 63] = i;
+    for (int k = 0; k < kWaveParts; ++k) rec[l * H + t / 64].q[k][t & 63] = s.q[k];
 }
 
 // upper entries of the IC(0) array take the factor value of their transpose

@@ -84,3 +84,16 @@ def test_infinite_pivots(pairs, stride, order):
     quot1 = quot1.copy()
     quot1[::3] = 0.0
     assert np.array_equal(z[first], quot0) and np.array_equal(z[second], quot1)
+
+
+@pytest.mark.parametrize("pairs,stride,order", FORMS, ids=str)
+def test_infinite_values(pairs, stride, order):
+    rng = np.random.default_rng(pairs)
+    A, b, first, second, quot0, quot1 = _blocks(pairs, stride, rng, False)
+    b[second[::5]] = -np.inf
+    z = _apply(A, b, ILU0, order)
+    quot1 = quot1.copy()
+    quot1[::5] = -np.inf
+    assert np.array_equal(z[second], quot1)
+    # (the first row of a block holds its stored zero times the second's result)
+    assert np.array_equal(np.delete(z[first], np.s_[::5]), np.delete(quot0, np.s_[::5]))
