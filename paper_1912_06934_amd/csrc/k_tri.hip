@@ -267,27 +267,39 @@ __global__ __launch_bounds__(256) void k_tri_level(TriPass p, int u0, int skip, 
 {
     const int tt = blockIdx.x * 256 + threadIdx.x, t = tt - skip;
     if (t >= cnt) return;
+    constexpr int C = W > 0 ? W : 8;  // entries per step
+    const int n = t < 0 ? 0 : W > 0 ? W : width;
+    int c[C];
+    double v[C];
+    // (the entries before the row that everything else waits for; rows without
+    // entries read the level's first ones and leave them)
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            // a step past the width repeats its last entry
+            const int kk = W > 0 ? k : min(k0 + k, width - 1);
+            const int64_t e = at + static_cast<int64_t>(kk) * cnt + max(t, 0);
+            c[k] = p.col[e];
+            v[k] = p.val[e];
+        }
+    };
+    if (W > 0 || n > 0) fetch(0);
     const int u = u0 + tt, i = p.row[u];
     const double di = p.diag ? p.diag[u] : 1.0, fo = p.fold ? p.fold[u] : 0.0;
     double s = p.in[i];
-    constexpr int C = W > 0 ? W : 8;  // entries per step
-    const int n = t < 0 ? 0 : W > 0 ? W : width;
     for (int k0 = 0; k0 < n; k0 += C) {
-        int c[C];
-        double v[C], xv[C];
-#pragma unroll
-        for (int k = 0; k < C; ++k) {
-            // a step past the width repeats its last entry with value 0
-            const int kk = W > 0 ? k : min(k0 + k, width - 1);
-            const int64_t e = at + static_cast<int64_t>(kk) * cnt + t;
-            c[k] = p.col[e];
-            v[k] = W > 0 || k0 + k < width ? p.val[e] : 0.0;
-        }
+        double xv[C];
+        if (W == 0 && k0 > 0) fetch(k0);
 #pragma unroll
         for (int k = 0; k < C; ++k)
             xv[k] = FIRST && c[k] < 0 ? p.in[c[k] & ~kTriFirst] : p.x[c[k] & ~kTriFirst];
+        // (what fills a row has the value 0 and its own column: 0 times an
+        // infinity would not be nothing)
 #pragma unroll
-        for (int k = 0; k < C; ++k) s -= v[k] * xv[k];
+        for (int k = 0; k < C; ++k) {
+            const bool fill = (c[k] & ~kTriFirst) == i || (W == 0 && k0 + k >= width);
+            s -= fill ? 0.0 : v[k] * xv[k];
+        }
     }
     if (tail && t >= 0) {
         const int64_t e1 = tail[u + 1];

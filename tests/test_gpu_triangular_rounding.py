@@ -97,3 +97,33 @@ def test_infinite_values(pairs, stride, order):
     assert np.array_equal(z[second], quot1)
     # (the first row of a block holds its stored zero times the second's result)
     assert np.array_equal(np.delete(z[first], np.s_[::5]), np.delete(quot0, np.s_[::5]))
+
+
+@pytest.mark.parametrize("kind", [ILU0, IC0], ids=["ilu0", "ic0"])
+@pytest.mark.parametrize("grid,stencil,order", [
+    ((64, 64, 1), "box", "natural"), ((40, 40, 12), "star", "natural"),
+    ((70, 64, 60), "star", "natural"), ((97, 89, 1), "star", "multicolor"),
+    ((97, 89, 1), "box", "multicolor"), ((28, 27, 25), "box", "multicolor")], ids=str)
+def test_infinities_spread_as_in_the_sequential_solve(grid, stencil, order, kind):
+    """Rows with fewer entries than their level's widest: what fills them must
+    not meet an infinite value.  The oracle's solves add each stored entry in
+    turn; with entries of one sign an infinite value spreads and gives no NaN."""
+    import oracle
+    from test_gpu_triangular import _grid
+    rng = np.random.default_rng(7)
+    rp, ci, a = _grid(*grid, stencil, rng, True)
+    n = rp.size - 1
+    b = rng.standard_normal(n)
+    few = np.flatnonzero(np.diff(rp) < np.diff(rp).max())
+    b[few[2 * few.size // 3]] = np.inf
+    m = oracle.Msrsb(rp, ci, a)
+    one = np.zeros(n, dtype=np.int32)
+    m.set_coarse(1, one, np.arange(n + 1, dtype=np.int32), one, np.ones(n, dtype=np.uint8))
+    m.setup_basis(kmax=1)
+    m.build_coarse()
+    ref = m.apply(b, pre=(0, 0), post=(kind, 1), use_ms=False, ordering=order)
+    z = _apply(sp.csr_matrix((a, ci, rp), shape=(n, n)), b, kind, order)
+    ok = np.isfinite(ref)
+    assert not ok.all() and np.all(ref[~ok] == np.inf)
+    np.testing.assert_array_equal(z[~ok], ref[~ok])
+    np.testing.assert_allclose(z[ok], ref[ok], rtol=0, atol=1e-12 * np.abs(b[np.isfinite(b)]).max())
