@@ -1699,9 +1699,11 @@ __global__ __launch_bounds__(256) void k_symv_rows(const double *__restrict__ pk
             m[k] = *reinterpret_cast<const d4 *>(pk + at * kBP * kBP + e);
             const int j = J * kBP + (J <= I ? 4 * h : c);
 #pragma unroll
-            for (int b = 0; b < 4; ++b) xv[k][b] = x[min(j + (J <= I ? b : 0), n - 1)];
+            for (int b = 0; b < 4; ++b) {
+                const int q = j + (J <= I ? b : 0);
+                xv[k][b] = q < n ? x[q] : 0.0;
+            }
         }
-        // (the tiles hold zeros past n)
 #pragma unroll
         for (int k = 0; k < kSymvTiles; ++k) {
             if (J0 + k >= nt) break;
