@@ -236,7 +236,7 @@ __global__ __launch_bounds__(kNarrowThreads) void k_ilu_run(TriArgs t,
 //   needs no second pass: the first one ends with its division (fold);
 // - the last pass adds x to z (or sets it).
 // The coloured ILU(0) on 65,536 rows of nine entries: 8 launches of 5.2 us, a
-// copy and a sum -> 6 launches of 3.2 us per application; the coloured IC(0)
+// copy and a sum -> 6 launches of 3.4 us per application; the coloured IC(0)
 // on 215,025 rows of seven: 4 launches of 7.9 us, a copy and a sum -> 2 of 6.5.
 constexpr int kTriFirst = INT32_MIN;
 
